@@ -301,11 +301,11 @@ int magpie_destroy(magpie_ctx* c) {
   dev_free(c->posrec);
   dev_free(c->posx);
   dev_free(c->inv);
-  dev_free(c->lrn_sd);
   dev_free(c->lrn_stats);
   dev_free(c->lrn_fine);
   dev_free(c->lrn_map);
   dev_free(c->lrn_q);
+  dev_free(c->lrn_phi);
   dev_free(c->lrn_one);
   if (c->h_pin) hipHostFree(c->h_pin);
   for (hipEvent_t ev : c->pin_done)

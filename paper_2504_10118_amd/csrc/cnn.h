@@ -56,22 +56,24 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, 
 // flipped wt[ci][co][8 - t] (the backward-data convolution), float or bf16.
 hipError_t launch_prep_weights(const float* p, void* wf, void* wt, int co, int ci, bool bf16, hipStream_t s);
 
-// Network input map.  stats[k] = (mean sqrt(d_k) * qinv, row and column
-// frequency centres of mass of d_k, 0) from sqrt(d) in natural order.
-hipError_t launch_probe_norm(const double2* q, int m, double* out, hipStream_t s);
-hipError_t launch_position_stats(const float* sqrtd, int n_pos, int m, const double* qnorm, double4* stats,
+// Network input map.  a2[i] = |Q_i|^2, out = ||Q||_2.
+hipError_t launch_probe_norm(const double2* q, int m, double* out, double* a2, hipStream_t s);
+// stats[k] = (mean sqrt(d_k) / ||Q||_2, row and column frequency centres of mass of d_k, 0) from
+// sqrt(d) in the kernel order of plan (m, rb); the sums do not depend on rb.
+hipError_t launch_position_stats(const float* sqrtd, int n_pos, int m, int rb, const double* qnorm, double4* stats,
                                  hipStream_t s);
 // fine[ch][r][c] = sum_k |Q(p-o_k)|^2 stats[k][ch] / sum_k |Q(p-o_k)|^2 over the positions
 // in the pixel's tile list (0 where uncovered), ch < 3.
-hipError_t launch_map_fine(const double4* stats, const double2* q, int m, const int* tile_ptr, const int4* tile_ent,
-                           int tiles_x, int tile_w, int tile_h, int nr, int nc, double* fine, hipStream_t s);
+hipError_t launch_map_fine(const double4* stats, const double* a2, int m, const int* tile_ptr, const int4* tile_ent,
+                           int tiles_x, int tiles_y, int tile_w, int tile_h, int nr, int nc, double* fine,
+                           hipStream_t s);
 // out[ch][i][j] = mean of fine[ch] over the fr x fc block (i, j).
 hipError_t launch_pool(const double* fine, int nr, int nc, int fr, int fc, float* out, hipStream_t s);
 // out = the S x S phase whose gradient is (sy * gy, sx * gx) in the least-squares
-// (periodic, spectral) sense, mean 0; S <= 64.
+// (periodic, spectral) sense, mean 0; S <= 64.  scratch: S * S values.
 constexpr int PHASE_MAX_SIDE = 64;
-hipError_t launch_integrate_phase(const float* gy, const float* gx, int S, double sy, double sx, float* out,
-                                  hipStream_t s);
+hipError_t launch_integrate_phase(const float* gy, const float* gx, int S, double sy, double sx, double2* scratch,
+                                  float* out, hipStream_t s);
 
 // z[r][c] = coarse[r / f][c / f]; format 0 complex64, 1 complex128, 2 planes
 // (log-amplitude, phase) float [2][sr][sc].

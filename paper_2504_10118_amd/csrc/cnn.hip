@@ -351,30 +351,45 @@ __global__ void prep_weights_kernel(const float* __restrict__ p, WT* __restrict_
 // ---------------------------------------------------------------------------
 // Network input map
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void probe_norm_kernel(const double2* __restrict__ q, int mm,
-                                                         double* __restrict__ out) {
-  __shared__ double red[256];
+// |Q|^2 per probe pixel (FP64) and ||Q||_2.
+__global__ __launch_bounds__(1024) void probe_norm_kernel(const double2* __restrict__ q, int mm,
+                                                          double* __restrict__ out, double* __restrict__ a2) {
+  __shared__ double red[1024];
   double a = 0.0;
-  for (int i = threadIdx.x; i < mm; i += 256) a += q[i].x * q[i].x + q[i].y * q[i].y;
+  for (int i = threadIdx.x; i < mm; i += 1024) {
+    const double2 v = q[i];
+    const double w = v.x * v.x + v.y * v.y;
+    a2[i] = w;
+    a += w;
+  }
   red[threadIdx.x] = a;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
+  for (int s = 512; s > 0; s >>= 1) {
     if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
     __syncthreads();
   }
   if (threadIdx.x == 0) out[0] = sqrt(red[0]);
 }
 
-__global__ __launch_bounds__(256) void position_stats_kernel(const float* __restrict__ sqrtd, int m,
+// Statistics of one position's pattern, read where the step kernel keeps sqrt(d): row
+// ky is m contiguous floats in either order, and frequency kx = g CB + c + RA k2 of it
+// sits at g RA + c RB + k2 (RA = CB RB), so a wave's reads stay inside whole rows.  The
+// frequencies are summed in natural order: the result does not depend on the plan.
+// Bound by the read of sqrt(d); a re-layout to natural order in front of it had cost a
+// second read and a write of the same bytes (18.5 us of 1600 positions of 64 x 64).
+__global__ __launch_bounds__(256) void position_stats_kernel(const float* __restrict__ sqrtd, int lm, int lrb,
                                                              const double* __restrict__ qnorm,
                                                              double4* __restrict__ stats) {
   __shared__ double red[4][256];
-  const int k = blockIdx.x;
-  const float* s = sqrtd + (size_t)k * m * m;
+  const int k = blockIdx.x, m = 1 << lm, lra = lm - lrb, lcb = lra - lrb;
+  const float* s = sqrtd + ((size_t)k << (2 * lm));
   double sa = 0.0, sd = 0.0, sy = 0.0, sx = 0.0;
+#pragma unroll 4
   for (int i = threadIdx.x; i < m * m; i += 256) {
-    const int r = i / m, c = i - r * m;
-    const double a = (double)s[i];
+    const int r = i >> lm, c = i & (m - 1);
+    const int rem = c & ((1 << lra) - 1);
+    const int at = ((rem >> lcb) << lra) + ((rem & ((1 << lcb) - 1)) << lrb) + (c >> lra);
+    const double a = (double)s[(r << lm) + at];
     const double d = a * a;
     const double fy = (r < m / 2) ? r : r - m, fx = (c < m / 2) ? c : c - m;
     sa += a;
@@ -404,133 +419,179 @@ __global__ __launch_bounds__(256) void position_stats_kernel(const float* __rest
   }
 }
 
-__global__ void map_fine_kernel(const double4* __restrict__ stats, const double2* __restrict__ q, int m,
-                                const int* __restrict__ tile_ptr, const int4* __restrict__ tile_ent, int tiles_x,
-                                int tile_w, int tile_h, int nr, int nc, double* __restrict__ fine) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = blockIdx.y;
-  if (c >= nc) return;
-  const int t = (r / tile_h) * tiles_x + c / tile_w;
-  double n0 = 0.0, n1 = 0.0, n2 = 0.0, den = 0.0;
-  for (int e = tile_ptr[t]; e < tile_ptr[t + 1]; ++e) {
-    const int4 en = tile_ent[e];
-    const int dr = r - en.y, dc = c - en.z;
-    if (dr < 0 || dr >= m || dc < 0 || dc >= m) continue;
-    const double2 qv = q[dr * m + dc];
-    const double w = qv.x * qv.x + qv.y * qv.y;
-    const double4 s = stats[en.x];
-    n0 += w * s.x;
-    n1 += w * s.y;
-    n2 += w * s.z;
-    den += w;
+// One workgroup per tile of the static position lists (tile_w = 32 columns, 8 rows of
+// it at a time): the tile's positions and their statistics are staged in LDS, then
+// every thread walks them for its pixel (the list order, as before) with one 8-byte
+// read of |Q|^2 per covering position.  Walking the list from global memory per pixel,
+// with blocks that spanned eight tiles' lists, took 36 us on a 512 x 512 object with
+// 1600 windows of 64 x 64.
+constexpr int MAP_CHUNK = 256;
+
+__global__ __launch_bounds__(256) void map_fine_kernel(const double4* __restrict__ stats,
+                                                       const double* __restrict__ a2, int m,
+                                                       const int* __restrict__ tile_ptr,
+                                                       const int4* __restrict__ tile_ent, int tiles_x, int tile_h,
+                                                       int nr, int nc, double* __restrict__ fine) {
+  __shared__ double sst[3][MAP_CHUNK];
+  __shared__ int2 soff[MAP_CHUNK];
+  const int tx = blockIdx.x, ty = blockIdx.y;
+  const int c = tx * 32 + (threadIdx.x & 31);
+  const int beg = tile_ptr[ty * tiles_x + tx], end = tile_ptr[ty * tiles_x + tx + 1];
+  const size_t plane = (size_t)nr * nc;
+  for (int r0 = ty * tile_h; r0 < (ty + 1) * tile_h; r0 += 8) {
+    const int r = r0 + (threadIdx.x >> 5);
+    double n0 = 0.0, n1 = 0.0, n2 = 0.0, den = 0.0;
+    for (int e0 = beg; e0 < end; e0 += MAP_CHUNK) {
+      const int n = min(MAP_CHUNK, end - e0);
+      __syncthreads();
+      if ((int)threadIdx.x < n) {
+        const int4 en = tile_ent[e0 + threadIdx.x];
+        const double4 s = stats[en.x];
+        soff[threadIdx.x] = make_int2(en.y, en.z);
+        sst[0][threadIdx.x] = s.x;
+        sst[1][threadIdx.x] = s.y;
+        sst[2][threadIdx.x] = s.z;
+      }
+      __syncthreads();
+#pragma unroll 4
+      for (int e = 0; e < n; ++e) {
+        const int2 o = soff[e];
+        const int dr = r - o.x, dc = c - o.y;
+        if ((unsigned)dr < (unsigned)m && (unsigned)dc < (unsigned)m) {
+          const double w = a2[dr * m + dc];
+          n0 += w * sst[0][e];
+          n1 += w * sst[1][e];
+          n2 += w * sst[2][e];
+          den += w;
+        }
+      }
+    }
+    if (r < nr && c < nc) {
+      const size_t i = (size_t)r * nc + c;
+      const bool pos = den > 0.0;
+      fine[i] = pos ? n0 / den : 0.0;
+      fine[plane + i] = pos ? n1 / den : 0.0;
+      fine[2 * plane + i] = pos ? n2 / den : 0.0;
+    }
   }
-  const size_t plane = (size_t)nr * nc, i = (size_t)r * nc + c;
-  const bool pos = den > 0.0;
-  fine[i] = pos ? n0 / den : 0.0;
-  fine[plane + i] = pos ? n1 / den : 0.0;
-  fine[2 * plane + i] = pos ? n2 / den : 0.0;
 }
 
-__global__ void pool_kernel(const double* __restrict__ fine, int nr, int nc, int fr, int fc, float* __restrict__ out) {
+// One workgroup per run of cells of one cell row and channel: each thread sums a
+// column of fr pixels (neighbouring threads read neighbouring columns), then the first
+// threads sum fc columns per cell from LDS.
+__global__ __launch_bounds__(256) void pool_kernel(const double* __restrict__ fine, int nr, int nc, int fr, int fc,
+                                                   int cells, float* __restrict__ out) {
+  __shared__ double cs[256];
   const int so = nc / fc, sr = nr / fr;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int i = blockIdx.y, ch = blockIdx.z;
-  if (j >= so || i >= sr) return;
-  const double* src = fine + (size_t)ch * nr * nc;
-  double a = 0.0;
-  for (int y = 0; y < fr; ++y)
-    for (int x = 0; x < fc; ++x) a += src[(size_t)(i * fr + y) * nc + j * fc + x];
-  out[((size_t)ch * sr + i) * so + j] = (float)(a / ((double)fr * fc));
+  const int i = blockIdx.y, ch = blockIdx.z, j0 = blockIdx.x * cells;
+  const double* src = fine + (size_t)ch * nr * nc + (size_t)i * fr * nc;
+  const int nj = min(cells, so - j0);
+  double cell = 0.0;
+  // cells = 256 / fc whole cells at a time; a cell wider than 256 columns alone, in pieces
+  for (int x0 = 0; x0 < nj * fc; x0 += 256) {
+    const int n = min(256, nj * fc - x0);
+    double a = 0.0;
+    if ((int)threadIdx.x < n)
+#pragma unroll 8
+      for (int y = 0; y < fr; ++y) a += src[(size_t)y * nc + (size_t)j0 * fc + x0 + threadIdx.x];
+    __syncthreads();
+    cs[threadIdx.x] = a;
+    __syncthreads();
+    if ((int)threadIdx.x < nj) {
+      const int w = min(fc, n);
+      for (int x = 0; x < w; ++x) cell += cs[threadIdx.x * fc + x];
+    }
+  }
+  if ((int)threadIdx.x < nj) out[((size_t)ch * sr + i) * so + j0 + threadIdx.x] = (float)(cell / ((double)fr * fc));
 }
 
 // Phase channel: least-squares integration of the gradient field the two
-// centre-of-mass channels measure (Frankot and Chellappa), in FP64 on one
-// workgroup.  The two real fields are transformed together as
-// H = DFT(gy + i gx) and separated with the conjugate-symmetric parts; then
-// phi^ = -i (wy Gy + wx Gx) / (wy^2 + wx^2) (0 at zero frequency) and
-// phi = Re IDFT(phi^).  Direct DFT sums over rows and columns (S <= 64).
+// centre-of-mass channels measure (Frankot and Chellappa), in FP64.  The two real
+// fields are transformed together as H = DFT(gy + i gx) and separated with the
+// conjugate-symmetric parts; then phi^ = -i (wy Gy + wx Gx) / (wy^2 + wx^2) (0 at zero
+// frequency) and phi = Re IDFT(phi^).  Direct DFT sums over rows and columns (S <= 64),
+// in three launches of one workgroup per row or pair of columns: on one workgroup the
+// S^3 sums of each pass ran from one CU's LDS (158 us at S = 64).
 constexpr int PHI_MAX_S = 64;
-constexpr int PHI_THREADS = 1024;
 
-__global__ __launch_bounds__(PHI_THREADS) void integrate_phase_kernel(const float* __restrict__ gy_in,
-                                                                      const float* __restrict__ gx_in, int S,
-                                                                      double sy, double sx,
-                                                                      float* __restrict__ out) {
-  __shared__ double2 A[PHI_MAX_S * PHI_MAX_S];
-  __shared__ double2 Bf[PHI_MAX_S * PHI_MAX_S];
-  __shared__ double2 W[PHI_MAX_S];
-  const int tid = threadIdx.x, SS = S * S;
-  for (int j = tid; j < S; j += PHI_THREADS) {
+// exp(-2 pi i j / S) for j < S by the first S threads
+__device__ __forceinline__ void phi_twiddles(double2* W, int S) {
+  if ((int)threadIdx.x < S) {
     double sn, cs;
-    sincospi(-2.0 * j / S, &sn, &cs);
-    W[j] = make_double2(cs, sn);   // exp(-2 pi i j / S)
+    sincospi(-2.0 * (int)threadIdx.x / S, &sn, &cs);
+    W[threadIdx.x] = make_double2(cs, sn);
   }
-  for (int e = tid; e < SS; e += PHI_THREADS) A[e] = make_double2(sy * gy_in[e], sx * gx_in[e]);
-  __syncthreads();
-  // forward: rows, then columns
-  for (int e = tid; e < SS; e += PHI_THREADS) {
-    const int y = e / S, k = e - y * S;
-    double2 acc = make_double2(0.0, 0.0);
-    for (int x = 0; x < S; ++x) {
-      const double2 a = A[y * S + x], w = W[(k * x) % S];
-      acc.x += a.x * w.x - a.y * w.y;
-      acc.y += a.x * w.y + a.y * w.x;
-    }
-    Bf[e] = acc;
+}
+
+// sum_j v[j stride] W^(k j) (CONJ: conj(W)), j < S
+template <bool CONJ>
+__device__ __forceinline__ double2 phi_sum(const double2* v, const double2* W, int S, int k) {
+  double2 acc = make_double2(0.0, 0.0);
+  int idx = 0;
+#pragma unroll 4
+  for (int j = 0; j < S; ++j) {
+    const double2 a = v[j], w = W[idx];
+    const double wy = CONJ ? -w.y : w.y;
+    acc.x += a.x * w.x - a.y * wy;
+    acc.y += a.x * wy + a.y * w.x;
+    idx += k;
+    if (idx >= S) idx -= S;
   }
+  return acc;
+}
+
+// rows of the forward transform, stored transposed: t[k][y]
+__global__ __launch_bounds__(PHI_MAX_S) void phi_rows_kernel(const float* __restrict__ gy_in,
+                                                             const float* __restrict__ gx_in, int S, double sy,
+                                                             double sx, double2* __restrict__ t) {
+  __shared__ double2 v[PHI_MAX_S], W[PHI_MAX_S];
+  const int y = blockIdx.x, k = threadIdx.x;
+  phi_twiddles(W, S);
+  if (k < S) v[k] = make_double2(sy * gy_in[y * S + k], sx * gx_in[y * S + k]);
   __syncthreads();
-  for (int e = tid; e < SS; e += PHI_THREADS) {
-    const int k0 = e / S, k1 = e - k0 * S;
-    double2 acc = make_double2(0.0, 0.0);
-    for (int y = 0; y < S; ++y) {
-      const double2 b = Bf[y * S + k1], w = W[(k0 * y) % S];
-      acc.x += b.x * w.x - b.y * w.y;
-      acc.y += b.x * w.y + b.y * w.x;
-    }
-    A[e] = acc;
-  }
+  if (k < S) t[k * S + y] = phi_sum<false>(v, W, S, k);
+}
+
+// Columns k1 and -k1 (mod S): forward over y, phi^ (which pairs the frequencies k and
+// -k), inverse over k0; in place (the workgroup owns both columns).
+__global__ __launch_bounds__(2 * PHI_MAX_S) void phi_cols_kernel(int S, double2* __restrict__ t) {
+  __shared__ double2 v[2][PHI_MAX_S], h[2][PHI_MAX_S], W[PHI_MAX_S];
+  const int which = threadIdx.x / PHI_MAX_S, k0 = threadIdx.x % PHI_MAX_S;
+  const int ka = blockIdx.x, kb = (S - ka) % S, k1 = which ? kb : ka;
+  phi_twiddles(W, S);
+  if (k0 < S) v[which][k0] = t[k1 * S + k0];
   __syncthreads();
-  // separate the two spectra, divide by |w|^2
-  for (int e = tid; e < SS; e += PHI_THREADS) {
-    const int k0 = e / S, k1 = e - k0 * S;
-    const int m0 = (S - k0) % S, m1 = (S - k1) % S;
-    const double2 h = A[e], hm = A[m0 * S + m1];
+  if (k0 < S) h[which][k0] = phi_sum<false>(v[which], W, S, k0);
+  __syncthreads();
+  if (k0 < S) {
+    const double2 a = h[which][k0], am = h[1 - which][(S - k0) % S];
     // Gy = (h + conj(hm)) / 2, Gx = (h - conj(hm)) / (2 i)
-    const double2 gy = make_double2(0.5 * (h.x + hm.x), 0.5 * (h.y - hm.y));
-    const double2 gx = make_double2(0.5 * (h.y + hm.y), -0.5 * (h.x - hm.x));
+    const double2 gy = make_double2(0.5 * (a.x + am.x), 0.5 * (a.y - am.y));
+    const double2 gx = make_double2(0.5 * (a.y + am.y), -0.5 * (a.x - am.x));
     const int f0 = (k0 < (S + 1) / 2) ? k0 : k0 - S, f1 = (k1 < (S + 1) / 2) ? k1 : k1 - S;
     const double wy = 6.283185307179586 * f0 / S, wx = 6.283185307179586 * f1 / S;
     const double den = wy * wy + wx * wx;
     double2 ph = make_double2(0.0, 0.0);
     if (den > 0.0) {
       // -i (wy gy + wx gx) / den
-      const double2 t = make_double2(wy * gy.x + wx * gx.x, wy * gy.y + wx * gx.y);
-      ph = make_double2(t.y / den, -t.x / den);
+      const double2 u = make_double2(wy * gy.x + wx * gx.x, wy * gy.y + wx * gx.y);
+      ph = make_double2(u.y / den, -u.x / den);
     }
-    Bf[e] = ph;
+    v[which][k0] = ph;
   }
   __syncthreads();
-  // inverse: columns, then rows; real part / S^2
-  for (int e = tid; e < SS; e += PHI_THREADS) {
-    const int y = e / S, k1 = e - y * S;
-    double2 acc = make_double2(0.0, 0.0);
-    for (int k0 = 0; k0 < S; ++k0) {
-      const double2 b = Bf[k0 * S + k1], w = W[(k0 * y) % S];
-      acc.x += b.x * w.x + b.y * w.y;    // times conj(w)
-      acc.y += b.y * w.x - b.x * w.y;
-    }
-    A[e] = acc;
-  }
+  if (k0 < S && (which == 0 || kb != ka)) t[k1 * S + k0] = phi_sum<true>(v[which], W, S, k0);
+}
+
+// rows of the inverse: out[y][x] = Re sum_k1 t[k1][y] conj(W)^(k1 x) / S^2
+__global__ __launch_bounds__(PHI_MAX_S) void phi_out_kernel(const double2* __restrict__ t, int S,
+                                                            float* __restrict__ out) {
+  __shared__ double2 v[PHI_MAX_S], W[PHI_MAX_S];
+  const int y = blockIdx.x, x = threadIdx.x;
+  phi_twiddles(W, S);
+  if (x < S) v[x] = t[x * S + y];
   __syncthreads();
-  for (int e = tid; e < SS; e += PHI_THREADS) {
-    const int y = e / S, x = e - y * S;
-    double acc = 0.0;
-    for (int k1 = 0; k1 < S; ++k1) {
-      const double2 a = A[y * S + k1], w = W[(k1 * x) % S];
-      acc += a.x * w.x + a.y * w.y;      // Re(a conj(w))
-    }
-    out[e] = (float)(acc / ((double)S * S));
-  }
+  if (x < S) out[y * S + x] = (float)(phi_sum<true>(v, W, S, x).x / ((double)S * S));
 }
 
 // ---------------------------------------------------------------------------
@@ -692,35 +753,48 @@ hipError_t launch_prep_weights(const float* p, void* wf, void* wt, int co, int c
   return hipGetLastError();
 }
 
-hipError_t launch_probe_norm(const double2* q, int m, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(probe_norm_kernel, dim3(1), dim3(256), 0, s, q, m * m, out);
+hipError_t launch_probe_norm(const double2* q, int m, double* out, double* a2, hipStream_t s) {
+  hipLaunchKernelGGL(probe_norm_kernel, dim3(1), dim3(1024), 0, s, q, m * m, out, a2);
   return hipGetLastError();
 }
 
-hipError_t launch_position_stats(const float* sqrtd, int n_pos, int m, const double* qnorm, double4* stats,
+hipError_t launch_position_stats(const float* sqrtd, int n_pos, int m, int rb, const double* qnorm, double4* stats,
                                  hipStream_t s) {
   if (n_pos <= 0) return hipSuccess;
-  hipLaunchKernelGGL(position_stats_kernel, dim3(n_pos), dim3(256), 0, s, sqrtd, m, qnorm, stats);
+  auto log2i = [](int x) {
+    int l = 0;
+    while ((1 << l) < x) ++l;
+    return l;
+  };
+  const int lm = log2i(m), lrb = log2i(rb);
+  if ((1 << lm) != m || (1 << lrb) != rb || 2 * lrb > lm) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(position_stats_kernel, dim3(n_pos), dim3(256), 0, s, sqrtd, lm, lrb, qnorm, stats);
   return hipGetLastError();
 }
 
-hipError_t launch_map_fine(const double4* stats, const double2* q, int m, const int* tile_ptr, const int4* tile_ent,
-                           int tiles_x, int tile_w, int tile_h, int nr, int nc, double* fine, hipStream_t s) {
-  hipLaunchKernelGGL(map_fine_kernel, dim3((nc + 255) / 256, nr), dim3(256), 0, s, stats, q, m, tile_ptr, tile_ent,
-                     tiles_x, tile_w, tile_h, nr, nc, fine);
+hipError_t launch_map_fine(const double4* stats, const double* a2, int m, const int* tile_ptr, const int4* tile_ent,
+                           int tiles_x, int tiles_y, int tile_w, int tile_h, int nr, int nc, double* fine,
+                           hipStream_t s) {
+  if (tile_w != 32 || tile_h % 8) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(map_fine_kernel, dim3(tiles_x, tiles_y), dim3(256), 0, s, stats, a2, m, tile_ptr, tile_ent,
+                     tiles_x, tile_h, nr, nc, fine);
   return hipGetLastError();
 }
 
 hipError_t launch_pool(const double* fine, int nr, int nc, int fr, int fc, float* out, hipStream_t s) {
   const int so = nc / fc, sr = nr / fr;
-  hipLaunchKernelGGL(pool_kernel, dim3((so + 63) / 64, sr, 3), dim3(64), 0, s, fine, nr, nc, fr, fc, out);
+  const int cells = fc >= 256 ? 1 : 256 / fc;
+  hipLaunchKernelGGL(pool_kernel, dim3((so + cells - 1) / cells, sr, 3), dim3(256), 0, s, fine, nr, nc, fr, fc, cells,
+                     out);
   return hipGetLastError();
 }
 
-hipError_t launch_integrate_phase(const float* gy, const float* gx, int S, double sy, double sx, float* out,
-                                  hipStream_t s) {
+hipError_t launch_integrate_phase(const float* gy, const float* gx, int S, double sy, double sx, double2* scratch,
+                                  float* out, hipStream_t s) {
   if (S < 1 || S > PHI_MAX_S) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(integrate_phase_kernel, dim3(1), dim3(PHI_THREADS), 0, s, gy, gx, S, sy, sx, out);
+  hipLaunchKernelGGL(phi_rows_kernel, dim3(S), dim3(PHI_MAX_S), 0, s, gy, gx, S, sy, sx, scratch);
+  hipLaunchKernelGGL(phi_cols_kernel, dim3(S / 2 + 1), dim3(2 * PHI_MAX_S), 0, s, S, scratch);
+  hipLaunchKernelGGL(phi_out_kernel, dim3(S), dim3(PHI_MAX_S), 0, s, (const double2*)scratch, S, out);
   return hipGetLastError();
 }
 

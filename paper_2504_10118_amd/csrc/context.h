@@ -177,15 +177,15 @@ struct magpie_ctx {
   int g_rb = 0, g_th = 0;
 
   // learned-start scratch (allocated on first use, grown as needed)
-  float* lrn_sd = nullptr;       // sqrt(d) in natural order
-  size_t lrn_sd_cap = 0;
   double4* lrn_stats = nullptr;  // per-position statistics
   size_t lrn_stats_cap = 0;
   double* lrn_fine = nullptr;    // full-resolution map, 3 channels
   size_t lrn_fine_cap = 0;
   float* lrn_map = nullptr;      // pooled map
   size_t lrn_map_cap = 0;
-  double* lrn_q = nullptr;       // ||Q||_2
+  double* lrn_q = nullptr;       // ||Q||_2, then |Q|^2 per probe pixel
+  double2* lrn_phi = nullptr;    // transforms of the integrated-phase channel
+  size_t lrn_phi_cap = 0;
   float2* lrn_one = nullptr;     // the value 1 + 0i (flat start)
 };
 

@@ -103,25 +103,23 @@ int input_map_dev(magpie_ctx* c, int side) {
   if (side < 1 || c->nr % side || c->nc % side)
     return fail(MAGPIE_ERR_INVALID_ARG, "side must divide the object's rows and columns");
   if (side > cnn::PHASE_MAX_SIDE) return fail(MAGPIE_ERR_UNSUPPORTED, "side must be at most 64");
-  const size_t mm = (size_t)c->m * c->m;
-  rc = grow(&c->lrn_sd, &c->lrn_sd_cap, (size_t)c->n_pos * mm);
-  if (!rc) rc = grow(&c->lrn_stats, &c->lrn_stats_cap, (size_t)c->n_pos);
+  const size_t mm = (size_t)c->m * c->m, ss = (size_t)side * side;
+  rc = grow(&c->lrn_stats, &c->lrn_stats_cap, (size_t)c->n_pos);
   if (!rc) rc = grow(&c->lrn_fine, &c->lrn_fine_cap, 3 * (size_t)c->nr * c->nc);
-  if (!rc) rc = grow(&c->lrn_map, &c->lrn_map_cap, 4 * (size_t)side * side);
-  if (!rc && !c->lrn_q) rc = dev_alloc(&c->lrn_q, 1);
+  if (!rc) rc = grow(&c->lrn_map, &c->lrn_map_cap, 4 * ss);
+  if (!rc) rc = grow(&c->lrn_phi, &c->lrn_phi_cap, ss);
+  if (!rc && !c->lrn_q) rc = dev_alloc(&c->lrn_q, 1 + mm);   // ||Q||_2, then |Q|^2 per pixel
   if (rc) return rc;
-  MG_HIP(mg::launch_unpermute_sqrt(c->m, c->rb, c->n_pos, c->sqrtd, c->lrn_sd, c->stream));
-  MG_HIP(cnn::launch_probe_norm(c->q64, c->m, c->lrn_q, c->stream));
-  MG_HIP(cnn::launch_position_stats(c->lrn_sd, c->n_pos, c->m, c->lrn_q, c->lrn_stats, c->stream));
-  MG_HIP(cnn::launch_map_fine(c->lrn_stats, c->q64, c->m, c->tile_ptr, c->tile_ent, c->tiles_x, mg::ACC_TILE_W, c->th,
-                              c->nr, c->nc, c->lrn_fine, c->stream));
+  MG_HIP(cnn::launch_probe_norm(c->q64, c->m, c->lrn_q, c->lrn_q + 1, c->stream));
+  MG_HIP(cnn::launch_position_stats(c->sqrtd, c->n_pos, c->m, c->rb, c->lrn_q, c->lrn_stats, c->stream));
+  MG_HIP(cnn::launch_map_fine(c->lrn_stats, c->lrn_q + 1, c->m, c->tile_ptr, c->tile_ent, c->tiles_x, c->tiles_y,
+                              mg::ACC_TILE_W, c->th, c->nr, c->nc, c->lrn_fine, c->stream));
   MG_HIP(cnn::launch_pool(c->lrn_fine, c->nr, c->nc, c->nr / side, c->nc / side, c->lrn_map, c->stream));
   // channel 3: the phase the centre-of-mass channels (slopes of 2 pi f / m per
   // object pixel, f in DFT bins) integrate to, per map cell
-  const size_t ss = (size_t)side * side;
   const double two_pi = 6.283185307179586;
   MG_HIP(cnn::launch_integrate_phase(c->lrn_map + ss, c->lrn_map + 2 * ss, side, two_pi * (c->nr / side) / c->m,
-                                     two_pi * (c->nc / side) / c->m, c->lrn_map + 3 * ss, c->stream));
+                                     two_pi * (c->nc / side) / c->m, c->lrn_phi, c->lrn_map + 3 * ss, c->stream));
   return MAGPIE_OK;
 }
 
