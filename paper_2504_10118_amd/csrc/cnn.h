@@ -1,6 +1,6 @@
-// Launch interface of the learned-start kernels (cnn.hip): 3x3 convolutions
-// and their gradients, the complex MSE head, Adam, the network input map built
-// from measured intensities, and whole-object restriction / prolongation.
+// Launch interface of the learned-start kernels: 3x3 convolutions and their
+// gradients (conv.hip); the complex MSE head, Adam, the network input map built
+// from measured intensities, and whole-object restriction / prolongation (cnn.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -9,32 +9,55 @@
 
 namespace cnn {
 
-constexpr int CONV_TILE = 16;        // output pixels per workgroup side
-constexpr int MAX_WIDTH = 32;        // channels handled by one thread (wgrad: 4 output x 32 input channels)
+// Activations of the hidden layers are channels-last, [B][H][W][32]; the network's
+// input, output and output gradient are planes, [B][c][H][W].
 
-// out = conv3x3(in) with zero padding 1.  in: [B][ci][Hi][Wi] (Hi = H/2 when up,
-// read through nearest 2x upsampling), w: [co][ci][9] float or bf16 bits,
-// out: [B][co][H][W].  mode 0: + bias, ReLU; 1: + bias; 2: no bias, zero where
-// omask <= 0 (omask has out's shape); 3: no bias.
-hipError_t launch_conv(int co, bool up, int mode, bool bf16, const float* in, const void* w, const float* bias,
-                       float* out, const float* omask, int batch, int ci, int H, int W, hipStream_t s);
+// Compute copies of the weights.  Square (32 -> 32) layers: fwd, FWD_VECS float4 each
+// ([chunk of four input channels][tap][co]), and frag, FRAG_VECS vectors of bf16 parts each
+// for backward-data; the first layer keeps its order (first[32][cin][9]); the head becomes
+// head[32][9][2] and, transposed and flipped, head_t[32][2][9].  With bf16 the
+// copies hold the weights rounded to bf16.  *wbad: nonzero if a square layer's weight is not finite.
+constexpr int FWD_VECS = 8 * 9 * 32, FRAG_VECS = 18 * 3 * 64;
+struct PrepArgs {
+  const float* p;               // parameter vector
+  int64_t off_sq[3], off_first, off_head;   // offsets of the layers' weights
+  int cin;
+  bool bf16;
+  float4* fwd;                  // [3][FWD_VECS]
+  uint4* frag;                  // [3][FRAG_VECS]
+  float *first, *head, *head_t;
+  int* wbad;
+};
+hipError_t launch_prep(const PrepArgs& a, hipStream_t s);
 
-// Per-workgroup partial weight and bias gradients of a 3x3 convolution:
-// part[wg][(co*ci + c)*9 + t] and part[wg][co*ci*9 + co]; wgrad_workgroups
-// gives the number of workgroups (rows of part).  in holds the convolution's
-// input (read through upsampling when up), dout its output gradient
-// [B][co][H][W].
-int wgrad_workgroups(int batch, int H, int W);
-constexpr int WGRAD_MAX_WORKGROUPS = 512;   // upper bound of wgrad_workgroups for any shape
-hipError_t launch_wgrad(bool up, const float* in, const float* dout, float* part, int batch, int ci, int co, int H,
-                        int W, hipStream_t s);
-// grad[j] = sum over rows of part (fixed order), j < row_len.
-hipError_t launch_rows_sum(const float* part, int n_rows, int row_len, float* grad, hipStream_t s);
+// Square layer, forward: out = relu(conv3x3(in) + bias) with zero padding 1 (H, W: the
+// output's size; up: in has half of it and is read through nearest 2x upsampling).
+hipError_t launch_conv32(bool up, const float* in, const float4* w, const float* bias, float* out, int batch, int H,
+                         int W, hipStream_t s);
+// Square layer, backward-data of in (H x W): zero where omask <= 0; up: the sum of each
+// 2 x 2 block, out and omask of half the size.  w: the layer's weights as stored.
+hipError_t launch_conv32_backward(bool up, bool bf16, const float* in, const uint4* frag, const float* w, float* out,
+                                  const float* omask, const int* wbad, int batch, int H, int W, hipStream_t s);
+// First layer (planes in; + bias, ReLU), head (planes out; + bias) and the head's
+// backward-data (planes in; zero where omask <= 0).
+hipError_t launch_conv_first(int ci, const float* in, const float* w, const float* bias, float* out, int batch, int H,
+                             int W, hipStream_t s);
+hipError_t launch_conv_head(const float* in, const float* w, const float* bias, float* out, int batch, int H, int W,
+                            hipStream_t s);
+hipError_t launch_conv_head_backward(const float* dy, const float* w, float* out, const float* omask, int batch,
+                                     int H, int W, hipStream_t s);
 
-// da[b][c][y][x] = (a > 0) ? sum of du over the 2x2 block : 0 (adjoint of the
-// upsampling followed by the ReLU mask).  da, a: [B][C][H][W]; du: [B][C][2H][2W].
-hipError_t launch_up_backward_mask(const float* du, const float* a, float* da, int batch, int C, int H, int W,
-                                   hipStream_t s);
+// Weight and bias gradients of a layer (w[co][ci][9], then b[co]) from its input and its
+// output gradient, through at most WGRAD_MAX_WORKGROUPS rows of partial sums in `part`.
+constexpr int WGRAD_MAX_WORKGROUPS = 512;
+constexpr int SQ_ROW = 9 * 32 * 32 + 32;   // floats per row of a square layer
+constexpr int thin_row(int cn, bool head) { return (9 * cn + 31) / 32 * 1024 + (head ? 0 : 32); }
+hipError_t launch_wgrad32(bool up, const float* in, const float* dout, float* part, float* grad, int batch, int H,
+                          int W, hipStream_t s);
+hipError_t launch_wgrad_first(int ci, const float* in, const float* dout, float* part, float* grad, int batch, int H,
+                              int W, hipStream_t s);
+hipError_t launch_wgrad_head(const float* in, const float* dy, float* part, float* grad, int batch, int H, int W,
+                             hipStream_t s);
 
 // Masked complex MSE of exp(y0 + i y1) against target; dy gets the gradient.
 // y, dy: [B][2][HW]; target: [B][HW] complex; mask: [HW].  Per-block FP64 loss
@@ -51,10 +74,6 @@ hipError_t launch_sum_f64(const double* x, int n, double* out, hipStream_t s);
 // Adam with bias corrections c1 = 1/(1-b1^t), c2 = 1/(1-b2^t).
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr, float b1, float b2,
                        float eps, float c1, float c2, hipStream_t s);
-
-// Compute copies of a layer's weights: wf[co][ci][t] and the transposed,
-// flipped wt[ci][co][8 - t] (the backward-data convolution), float or bf16.
-hipError_t launch_prep_weights(const float* p, void* wf, void* wt, int co, int ci, bool bf16, hipStream_t s);
 
 // Network input map.  a2[i] = |Q_i|^2, out = ||Q||_2.
 hipError_t launch_probe_norm(const double2* q, int m, double* out, double* a2, hipStream_t s);

@@ -1,9 +1,7 @@
-// Learned-start kernels for gfx950: direct 3x3 convolutions staged through
-// LDS (forward, backward-data via transposed weights, weight gradients with
-// fixed-order partial sums), the complex MSE head, Adam, the network input
-// map computed from the measured intensities, and whole-object
-// restriction / prolongation (2x2 average pooling and 2x2 replication applied
-// repeatedly, i.e. f x f block means and copies).
+// Learned-start kernels for gfx950 apart from the convolutions: the complex MSE
+// head, Adam, the network input map computed from the measured intensities,
+// and whole-object restriction / prolongation (2x2 average pooling and 2x2
+// replication applied repeatedly, i.e. f x f block means and copies).
 //
 // All reductions run in a fixed order, so every result is bitwise
 // reproducible run to run.
@@ -16,186 +14,6 @@
 namespace cnn {
 
 namespace {
-
-constexpr int CT = CONV_TILE;
-constexpr int HALO = CT + 2;     // 18
-constexpr int CCH = 8;           // input channels per LDS stage (forward)
-constexpr int CPITCH = HALO + 1; // odd row pitch of the forward halo tile
-
-__device__ __forceinline__ float wload(const float* w, size_t i) { return w[i]; }
-__device__ __forceinline__ float wload(const uint16_t* w, size_t i) {
-  return __uint_as_float((uint32_t)w[i] << 16);
-}
-
-__device__ __forceinline__ uint16_t to_bf16(float x) {
-  const uint32_t u = __float_as_uint(x);
-  return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-}
-
-// ---------------------------------------------------------------------------
-// Convolution (forward and backward-data)
-// ---------------------------------------------------------------------------
-template <int CO, bool UP, int MODE, typename WT>
-__global__ __launch_bounds__(256) void conv3x3_kernel(const float* __restrict__ in, const WT* __restrict__ w,
-                                                      const float* __restrict__ bias, float* __restrict__ out,
-                                                      const float* __restrict__ omask, int ci_n, int H, int W) {
-  __shared__ float tile[CCH][HALO][CPITCH];
-  const int tx = threadIdx.x & (CT - 1), ty = threadIdx.x / CT;
-  const int x0 = blockIdx.x * CT, y0 = blockIdx.y * CT, b = blockIdx.z;
-  const int Hi = UP ? (H >> 1) : H, Wi = UP ? (W >> 1) : W;
-  const float* inb = in + (size_t)b * ci_n * Hi * Wi;
-  float acc[CO];
-#pragma unroll
-  for (int o = 0; o < CO; ++o) acc[o] = (MODE <= 1) ? bias[o] : 0.0f;
-  for (int c0 = 0; c0 < ci_n; c0 += CCH) {
-    const int nc = min(CCH, ci_n - c0);
-    for (int i = threadIdx.x; i < nc * HALO * HALO; i += 256) {
-      const int c = i / (HALO * HALO), r = i - c * HALO * HALO;
-      const int yy = r / HALO, xx = r - yy * HALO;
-      const int gy = y0 + yy - 1, gx = x0 + xx - 1;
-      float v = 0.0f;
-      if (gy >= 0 && gy < H && gx >= 0 && gx < W) {
-        const int sy = UP ? (gy >> 1) : gy, sx = UP ? (gx >> 1) : gx;
-        v = inb[((size_t)(c0 + c) * Hi + sy) * Wi + sx];
-      }
-      tile[c][yy][xx] = v;
-    }
-    __syncthreads();
-    for (int c = 0; c < nc; ++c) {
-      float xv[9];
-#pragma unroll
-      for (int t = 0; t < 9; ++t) xv[t] = tile[c][ty + t / 3][tx + t % 3];
-      const size_t wb = (size_t)(c0 + c) * 9;
-#pragma unroll
-      for (int o = 0; o < CO; ++o) {
-#pragma unroll
-        for (int t = 0; t < 9; ++t) acc[o] = fmaf(wload(w, wb + (size_t)o * ci_n * 9 + t), xv[t], acc[o]);
-      }
-    }
-    __syncthreads();
-  }
-  const int oy = y0 + ty, ox = x0 + tx;
-  if (oy < H && ox < W) {
-    const size_t plane = (size_t)H * W;
-    const size_t base = (size_t)b * CO * plane + (size_t)oy * W + ox;
-#pragma unroll
-    for (int o = 0; o < CO; ++o) {
-      float v = acc[o];
-      if (MODE == 0) v = fmaxf(v, 0.0f);
-      if (MODE == 2) v = (omask[base + o * plane] > 0.0f) ? v : 0.0f;
-      out[base + o * plane] = v;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Weight gradients: each workgroup walks a contiguous run of 16x16 output
-// tiles; thread (cog, c) owns output channels 4*cog .. 4*cog+3 and input
-// channel c, i.e. 36 weight sums and 4 bias sums.
-// ---------------------------------------------------------------------------
-constexpr int WG_TILES_TARGET = WGRAD_MAX_WORKGROUPS;
-constexpr int IN_PITCH = HALO * HALO + 1;  // 325: odd, so the 32 input channels hit 32 banks
-constexpr int DO_PITCH = CT * CT + 1;      // 257
-
-template <bool UP>
-__global__ __launch_bounds__(256) void wgrad_kernel(const float* __restrict__ in, const float* __restrict__ dout,
-                                                    float* __restrict__ part, int ci_n, int co_n, int H, int W,
-                                                    int tiles_x, int tiles_per_sample, int total_tiles,
-                                                    int tiles_per_wg) {
-  __shared__ float sin_[MAX_WIDTH * IN_PITCH];
-  __shared__ float sdo[MAX_WIDTH * DO_PITCH];
-  const int c = threadIdx.x & 31, cog = threadIdx.x >> 5;
-  const bool active = c < ci_n && cog * 4 < co_n;
-  const int Hi = UP ? (H >> 1) : H, Wi = UP ? (W >> 1) : W;
-  float acc[4][9];
-  float bacc[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    bacc[j] = 0.0f;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) acc[j][t] = 0.0f;
-  }
-  const int t_begin = blockIdx.x * tiles_per_wg;
-  const int t_end = min(total_tiles, t_begin + tiles_per_wg);
-  for (int tile = t_begin; tile < t_end; ++tile) {
-    const int b = tile / tiles_per_sample, tr = tile - b * tiles_per_sample;
-    const int y0 = (tr / tiles_x) * CT, x0 = (tr % tiles_x) * CT;
-    const float* inb = in + (size_t)b * ci_n * Hi * Wi;
-    const float* dob = dout + (size_t)b * co_n * H * W;
-    for (int i = threadIdx.x; i < ci_n * HALO * HALO; i += 256) {
-      const int cc = i / (HALO * HALO), r = i - cc * HALO * HALO;
-      const int yy = r / HALO, xx = r - yy * HALO;
-      const int gy = y0 + yy - 1, gx = x0 + xx - 1;
-      float v = 0.0f;
-      if (gy >= 0 && gy < H && gx >= 0 && gx < W) {
-        const int sy = UP ? (gy >> 1) : gy, sx = UP ? (gx >> 1) : gx;
-        v = inb[((size_t)cc * Hi + sy) * Wi + sx];
-      }
-      sin_[cc * IN_PITCH + r] = v;
-    }
-    for (int i = threadIdx.x; i < co_n * CT * CT; i += 256) {
-      const int o = i / (CT * CT), p = i - o * CT * CT;
-      const int gy = y0 + p / CT, gx = x0 + p % CT;
-      sdo[o * DO_PITCH + p] = (gy < H && gx < W) ? dob[((size_t)o * H + gy) * W + gx] : 0.0f;
-    }
-    __syncthreads();
-    if (active) {
-      for (int p = 0; p < CT * CT; ++p) {
-        const int py = p / CT, px = p % CT;
-        float g[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) g[j] = (cog * 4 + j < co_n) ? sdo[(cog * 4 + j) * DO_PITCH + p] : 0.0f;
-        float xv[9];
-#pragma unroll
-        for (int t = 0; t < 9; ++t) xv[t] = sin_[c * IN_PITCH + (py + t / 3) * HALO + px + t % 3];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          bacc[j] += g[j];
-#pragma unroll
-          for (int t = 0; t < 9; ++t) acc[j][t] = fmaf(g[j], xv[t], acc[j][t]);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (!active) return;
-  const size_t row = (size_t)co_n * ci_n * 9 + co_n;
-  float* pr = part + (size_t)blockIdx.x * row;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int o = cog * 4 + j;
-    if (o >= co_n) break;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) pr[((size_t)o * ci_n + c) * 9 + t] = acc[j][t];
-    if (c == 0) pr[(size_t)co_n * ci_n * 9 + o] = bacc[j];
-  }
-}
-
-// grad[j] = sum_r part[r][j]: 64 columns per block, 4 strided row sets combined in order.
-__global__ __launch_bounds__(256) void rows_sum_kernel(const float* __restrict__ part, int n_rows, int row_len,
-                                                       float* __restrict__ grad) {
-  __shared__ float red[4][64];
-  const int jj = threadIdx.x & 63, s = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + jj;
-  float acc = 0.0f;
-  if (j < row_len)
-    for (int r = s; r < n_rows; r += 4) acc += part[(size_t)r * row_len + j];
-  red[s][jj] = acc;
-  __syncthreads();
-  if (s == 0 && j < row_len) grad[j] = ((red[0][jj] + red[1][jj]) + red[2][jj]) + red[3][jj];
-}
-
-__global__ void up_backward_mask_kernel(const float* __restrict__ du, const float* __restrict__ a,
-                                        float* __restrict__ da, size_t total, int H, int W) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const size_t bc = i / ((size_t)H * W);
-  const int r = (int)(i - bc * H * W);
-  const int y = r / W, x = r - y * W;
-  const float* src = du + bc * (size_t)(4 * H * W) + (size_t)(2 * y) * (2 * W) + 2 * x;
-  const float sum = (src[0] + src[1]) + (src[2 * W] + src[2 * W + 1]);
-  da[i] = (a[i] > 0.0f) ? sum : 0.0f;
-}
 
 // ---------------------------------------------------------------------------
 // Complex MSE head
@@ -315,7 +133,7 @@ __global__ __launch_bounds__(256) void sum_f64_kernel(const double* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Adam and weight copies
+// Adam
 // ---------------------------------------------------------------------------
 __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
                             float* __restrict__ v, int64_t n, float lr, float b1, float b2, float eps, float c1,
@@ -328,24 +146,6 @@ __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, 
   m[i] = mi;
   v[i] = vi;
   p[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-}
-
-template <typename WT>
-__device__ __forceinline__ WT cvt_w(float x);
-template <>
-__device__ __forceinline__ float cvt_w<float>(float x) { return x; }
-template <>
-__device__ __forceinline__ uint16_t cvt_w<uint16_t>(float x) { return to_bf16(x); }
-
-template <typename WT>
-__global__ void prep_weights_kernel(const float* __restrict__ p, WT* __restrict__ wf, WT* __restrict__ wt, int co,
-                                    int ci) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= co * ci * 9) return;
-  const int o = i / (ci * 9), r = i - o * ci * 9, c = r / 9, t = r - c * 9;
-  const WT v = cvt_w<WT>(p[i]);
-  wf[i] = v;
-  wt[((size_t)c * co + o) * 9 + (8 - t)] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -641,76 +441,6 @@ __global__ void restrict_object_kernel(const float2* __restrict__ z, int nr, int
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-template <int CO, bool UP, int MODE>
-static void conv_t(bool bf16, const float* in, const void* w, const float* bias, float* out, const float* omask,
-                   int batch, int ci, int H, int W, hipStream_t s) {
-  const dim3 grid((W + CT - 1) / CT, (H + CT - 1) / CT, batch);
-  if (bf16)
-    hipLaunchKernelGGL((conv3x3_kernel<CO, UP, MODE, uint16_t>), grid, dim3(256), 0, s, in, (const uint16_t*)w, bias,
-                       out, omask, ci, H, W);
-  else
-    hipLaunchKernelGGL((conv3x3_kernel<CO, UP, MODE, float>), grid, dim3(256), 0, s, in, (const float*)w, bias, out,
-                       omask, ci, H, W);
-}
-
-hipError_t launch_conv(int co, bool up, int mode, bool bf16, const float* in, const void* w, const float* bias,
-                       float* out, const float* omask, int batch, int ci, int H, int W, hipStream_t s) {
-  if (batch <= 0) return hipSuccess;
-  if (ci < 1 || H < 1 || W < 1 || (up && ((H | W) & 1))) return hipErrorInvalidValue;
-#define CNN_CONV(CO_, UP_, MODE_)                                                                  \
-  if (co == CO_ && up == UP_ && mode == MODE_) {                                                   \
-    conv_t<CO_, UP_, MODE_>(bf16, in, w, bias, out, omask, batch, ci, H, W, s);                    \
-    return hipGetLastError();                                                                      \
-  }
-  // forward: 0 (ReLU) for the hidden layers, 1 (linear) for the head; backward-data: 2 (masked), 3
-  CNN_CONV(32, false, 0)
-  CNN_CONV(32, true, 0)
-  CNN_CONV(2, false, 1)
-  CNN_CONV(32, false, 2)
-  CNN_CONV(32, false, 3)
-#undef CNN_CONV
-  return hipErrorInvalidValue;
-}
-
-int wgrad_workgroups(int batch, int H, int W) {
-  const int tiles = batch * ((H + CT - 1) / CT) * ((W + CT - 1) / CT);
-  const int per = (tiles + WG_TILES_TARGET - 1) / WG_TILES_TARGET;
-  return (tiles + per - 1) / per;
-}
-
-hipError_t launch_wgrad(bool up, const float* in, const float* dout, float* part, int batch, int ci, int co, int H,
-                        int W, hipStream_t s) {
-  if (batch <= 0) return hipSuccess;
-  if (ci < 1 || ci > MAX_WIDTH || co < 1 || co > MAX_WIDTH || (up && ((H | W) & 1))) return hipErrorInvalidValue;
-  const int tiles_x = (W + CT - 1) / CT;
-  const int per_sample = tiles_x * ((H + CT - 1) / CT);
-  const int tiles = batch * per_sample;
-  const int per = (tiles + WG_TILES_TARGET - 1) / WG_TILES_TARGET;
-  const int nwg = (tiles + per - 1) / per;
-  if (up)
-    hipLaunchKernelGGL(wgrad_kernel<true>, dim3(nwg), dim3(256), 0, s, in, dout, part, ci, co, H, W, tiles_x,
-                       per_sample, tiles, per);
-  else
-    hipLaunchKernelGGL(wgrad_kernel<false>, dim3(nwg), dim3(256), 0, s, in, dout, part, ci, co, H, W, tiles_x,
-                       per_sample, tiles, per);
-  return hipGetLastError();
-}
-
-hipError_t launch_rows_sum(const float* part, int n_rows, int row_len, float* grad, hipStream_t s) {
-  if (row_len <= 0) return hipSuccess;
-  hipLaunchKernelGGL(rows_sum_kernel, dim3((row_len + 63) / 64), dim3(256), 0, s, part, n_rows, row_len, grad);
-  return hipGetLastError();
-}
-
-hipError_t launch_up_backward_mask(const float* du, const float* a, float* da, int batch, int C, int H, int W,
-                                   hipStream_t s) {
-  const size_t total = (size_t)batch * C * H * W;
-  if (!total) return hipSuccess;
-  hipLaunchKernelGGL(up_backward_mask_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, du, a, da,
-                     total, H, W);
-  return hipGetLastError();
-}
-
 int cmse_blocks(int batch, int hw) { return (int)(((size_t)batch * hw + CMSE_THREADS - 1) / CMSE_THREADS); }
 
 int cmse_ip_blocks(int hw) { return (hw + CMSE_THREADS - 1) / CMSE_THREADS; }
@@ -739,17 +469,6 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, 
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, g, m, v, n, lr, b1, b2, eps,
                      c1, c2);
-  return hipGetLastError();
-}
-
-hipError_t launch_prep_weights(const float* p, void* wf, void* wt, int co, int ci, bool bf16, hipStream_t s) {
-  const int n = co * ci * 9;
-  if (bf16)
-    hipLaunchKernelGGL(prep_weights_kernel<uint16_t>, dim3((n + 255) / 256), dim3(256), 0, s, p, (uint16_t*)wf,
-                       (uint16_t*)wt, co, ci);
-  else
-    hipLaunchKernelGGL(prep_weights_kernel<float>, dim3((n + 255) / 256), dim3(256), 0, s, p, (float*)wf, (float*)wt,
-                       co, ci);
   return hipGetLastError();
 }
 

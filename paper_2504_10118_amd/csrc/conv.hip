@@ -1,0 +1,1036 @@
+// 3x3 convolutions of the coarse-object network and their gradients for gfx950.
+//
+// Activations between the layers are channels-last: [B][H][W][32] FP32 (the
+// network's input, output and output gradient keep their [B][c][H][W] planes).
+//
+// Forward: every output is the FP32 FMA chain over (input channel, tap) from the bias,
+// the 32 -> 32 layers as v_mfma_f32_32x32x1_2b_f32 products: with K = 1 each is one
+// rounding per output, so the matrix cores give the chain's own bits (tested), at twice
+// the rate of unpacked FP32 VALU.  The order is part of the interface: the phase output's
+// bias has gradient zero by the loss's phase alignment, so what Adam makes of it is this
+// rounding, and another summation would send the bias elsewhere.
+//
+// Backward: the 32 -> 32 products run as v_mfma_f32_32x32x16_bf16 of FP32 operands split
+// exactly into three bf16 parts by truncation, x = x0 + x1 + x2 (8 + 8 + 8 significant
+// bits): the six products x0 w0, x0 w1, x1 w0, x0 w2, x1 w1, x2 w0 carry the FP32 product
+// to about 2^-23, and are accumulated in FP32 smallest first.  bf16 weights are their own
+// first part, so three products are exact.  A product of split parts is not the FP32
+// product where a value is infinite (inf - inf in its second part), so a workgroup that
+// stages a non-finite value, or whose weights hold one, takes the scalar FMA form of its
+// tile instead.
+//
+// All reductions run in a fixed order: results are bitwise reproducible.
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "cmath.h"
+#include "cnn.h"
+
+namespace cnn {
+
+namespace {
+
+constexpr int C = 32;               // channels of the hidden layers
+constexpr int CT = 16;              // output tile side of the convolutions
+constexpr int HALO = CT + 2;
+constexpr int HP = HALO * HALO;     // staged pixels of a tile
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x32 __attribute__((ext_vector_type(32)));
+
+__device__ __forceinline__ f32x16 mfma(uint4 a, uint4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
+                                                 0);
+}
+
+// bf16 pairs (even element in the low half) of two FP32 values' upper halves
+__device__ __forceinline__ uint32_t pack_hi(float even, float odd) {
+  return __builtin_amdgcn_perm(__float_as_uint(odd), __float_as_uint(even), 0x07060302u);
+}
+__device__ __forceinline__ float upper(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
+
+// the three bf16 parts of eight values; `probe` becomes NaN if one is not finite
+__device__ __forceinline__ void split8(const float* v, uint4 (&s)[3], float& probe) {
+  float r[8], q[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    probe = fmaf(v[j], 0.0f, probe);
+    r[j] = v[j] - upper(v[j]);
+    q[j] = r[j] - upper(r[j]);
+  }
+  s[0] = make_uint4(pack_hi(v[0], v[1]), pack_hi(v[2], v[3]), pack_hi(v[4], v[5]), pack_hi(v[6], v[7]));
+  s[1] = make_uint4(pack_hi(r[0], r[1]), pack_hi(r[2], r[3]), pack_hi(r[4], r[5]), pack_hi(r[6], r[7]));
+  s[2] = make_uint4(pack_hi(q[0], q[1]), pack_hi(q[2], q[3]), pack_hi(q[4], q[5]), pack_hi(q[6], q[7]));
+}
+
+__device__ __forceinline__ float round_bf16(float x) {
+  const uint32_t u = __float_as_uint(x);
+  return __uint_as_float((u + 0x7FFFu + ((u >> 16) & 1u)) & 0xffff0000u);
+}
+
+// ---------------------------------------------------------------------------
+// 32 -> 32 convolution, forward
+// ---------------------------------------------------------------------------
+// One workgroup of four waves per 16 x 16 output tile.  The 18 x 18 x 32 halo is staged
+// as it is (128 bytes per pixel, its 16-byte chunks rotated by the pixel index so that a
+// read of 16 neighbouring pixels covers all banks), 41 KB: three workgroups per CU.  A wave
+// owns four rows, two blocks of 32 pixels (its lane halves), and per chunk of four input
+// channels reads nine taps of its pixels from LDS and the chunk's 9 x 32 x 4 weights from
+// memory (36 KB in all, shared through L1; the next chunk's are loaded while the current 36
+// products of 64 cycles run).  Bound: 2 * 9 * 32 * 32 flops per pixel at the FP32 matrix
+// rate, 61 us for 32 samples of 128 x 128.
+template <bool UP>
+__global__ __launch_bounds__(256, 2) void conv32_forward_kernel(const float* __restrict__ in,
+                                                                const float4* __restrict__ w,
+                                                                const float* __restrict__ bias,
+                                                                float* __restrict__ out, int H, int W) {
+  __shared__ float4 T[HP * 8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
+  const int x0 = blockIdx.x * CT, y0 = blockIdx.y * CT, b = blockIdx.z;
+  const int Hi = UP ? H >> 1 : H, Wi = UP ? W >> 1 : W;
+  const float* inb = in + (size_t)b * Hi * Wi * C;
+  // weights [chunk][tap][co] of four input channels; both lane halves hold the same
+  const float4* wl = w + n;
+  float4 wc[9], wn[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) wn[t] = wl[t * C];
+#pragma unroll
+  for (int k = 0; k < (HP * 8 + 255) / 256; ++k) {
+    const int i = tid + 256 * k, p = i >> 3, yy = p / HALO, xx = p - yy * HALO;
+    const int gy = y0 + yy - 1, gx = x0 + xx - 1;
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (i < HP * 8) {
+      if (gy >= 0 && gy < H && gx >= 0 && gx < W)
+        v = reinterpret_cast<const float4*>(inb + ((size_t)(UP ? gy >> 1 : gy) * Wi + (UP ? gx >> 1 : gx)) * C)[i & 7];
+      T[8 * p + ((i & 7) ^ ((p >> 1) & 7))] = v;
+    }
+  }
+  // lane (h, n) holds channels 8 q + 4 h + (0..3) of pixel n of both blocks
+  f32x32 acc;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 bb = *reinterpret_cast<const float4*>(bias + 8 * q + 4 * h);
+    const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[4 * q + i] = acc[16 + 4 * q + i] = bv[i];
+  }
+  __syncthreads();
+  // pixel of this lane as a column of the product: block h, rows 4 wave + 2 h + (n >> 4)
+  const int p0 = (4 * wave + 2 * h + (n >> 4)) * HALO + (n & 15);
+#pragma unroll 1
+  for (int g = 0; g < 8; ++g) {
+    float4 xv[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      wc[t] = wn[t];
+      const int p = p0 + (t / 3) * HALO + t % 3;
+      xv[t] = T[8 * p + (g ^ ((p >> 1) & 7))];
+    }
+    const float4* wg = wl + (size_t)min(g + 1, 7) * 9 * C;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) wn[t] = wg[t * C];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const float av = c == 0 ? wc[t].x : c == 1 ? wc[t].y : c == 2 ? wc[t].z : wc[t].w;
+        const float bv = c == 0 ? xv[t].x : c == 1 ? xv[t].y : c == 2 ? xv[t].z : xv[t].w;
+        acc = __builtin_amdgcn_mfma_f32_32x32x1f32(av, bv, acc, 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int y = y0 + 4 * wave + 2 * k + (n >> 4), x = x0 + (n & 15);
+    if (y < H && x < W) {
+      float4* dst = reinterpret_cast<float4*>(out + (((size_t)b * H + y) * W + x) * C + 4 * h);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        dst[2 * q] = make_float4(fmaxf(acc[16 * k + 4 * q], 0.0f), fmaxf(acc[16 * k + 4 * q + 1], 0.0f),
+                                 fmaxf(acc[16 * k + 4 * q + 2], 0.0f), fmaxf(acc[16 * k + 4 * q + 3], 0.0f));
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// 32 -> 32 convolution, backward-data
+// ---------------------------------------------------------------------------
+// One workgroup of four waves per 16 x 16 output tile: the 18 x 18 x 32 halo is split
+// while it is staged into LDS (three planes, 64 bytes per pixel, its four 16-byte
+// chunks rotated by the pixel index so that the 16 lanes of a fragment read cover all
+// banks), 62 KB, two workgroups per CU so that one's staging overlaps the other's
+// products.  Products are D[co][pixel] += W[co][ci] X[ci][pixel] per tap and half of
+// the input channels; a wave owns four rows of the tile (two blocks of 2 x 16 pixels), and
+// the weights come as prepared fragments (54 KB, shared through L1 and L2).
+// MODE 2: zero where omask <= 0.  3: sum of each 2 x 2 block (the adjoint of the
+// upsampling), zero where omask <= 0, written at half the size.
+// Bound: 2 * 9 * 32 * 32 flops per pixel at the six-product rate (23 us of MFMA issue for
+// 32 samples of 128 x 128), then the activations' traffic.
+template <int WS>
+struct Pairs;
+template <>
+struct Pairs<3> {
+  static constexpr int N = 6;
+  static constexpr int x[6] = {2, 1, 0, 1, 0, 0}, w[6] = {0, 1, 2, 0, 1, 0};
+};
+template <>
+struct Pairs<1> {
+  static constexpr int N = 3;
+  static constexpr int x[3] = {2, 1, 0}, w[3] = {0, 0, 0};
+};
+
+struct Conv32Args {
+  const float* in;        // [B][H][W][32]
+  const uint4* frag;      // prepared fragments (see prep_kernel)
+  const float* w;         // master weights of the layer [32][32][9]
+  float* out;
+  const float* omask;
+  const int* wbad;        // nonzero: the weights hold a non-finite value
+  int H, W;               // size of the convolution's output
+};
+
+// scalar form of one output value, weights transposed and flipped
+template <int WS>
+__device__ float conv32_at(const Conv32Args& a, int b, int o, int y, int x) {
+  float acc = 0.0f;
+  for (int c = 0; c < C; ++c)
+    for (int t = 0; t < 9; ++t) {
+      const int gy = y + t / 3 - 1, gx = x + t % 3 - 1;
+      const bool in = gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
+      float w = a.w[(c * C + o) * 9 + 8 - t];
+      if (WS == 1) w = round_bf16(w);
+      acc = fmaf(w, in ? a.in[(((size_t)b * a.H + gy) * a.W + gx) * C + c] : 0.0f, acc);
+    }
+  return acc;
+}
+
+template <int MODE, int WS>
+__device__ __noinline__ void conv32_scalar(const Conv32Args& a, int b, int y0, int x0) {
+  if constexpr (MODE == 3) {
+    const int H2 = a.H >> 1, W2 = a.W >> 1;
+    for (int i = threadIdx.x; i < (CT / 2) * (CT / 2) * C; i += 256) {
+      const int o = i % C, p = i / C, y = y0 / 2 + p / (CT / 2), x = x0 / 2 + p % (CT / 2);
+      if (y >= H2 || x >= W2) continue;
+      const size_t at = (((size_t)b * H2 + y) * W2 + x) * C + o;
+      float v[4];
+      for (int q = 0; q < 4; ++q) v[q] = conv32_at<WS>(a, b, o, 2 * y + q / 2, 2 * x + q % 2);
+      a.out[at] = a.omask[at] > 0.0f ? (v[0] + v[1]) + (v[2] + v[3]) : 0.0f;
+    }
+  } else {
+    for (int i = threadIdx.x; i < CT * CT * C; i += 256) {
+      const int o = i % C, p = i / C, y = y0 + p / CT, x = x0 + p % CT;
+      if (y >= a.H || x >= a.W) continue;
+      const size_t at = (((size_t)b * a.H + y) * a.W + x) * C + o;
+      const float v = conv32_at<WS>(a, b, o, y, x);
+      a.out[at] = a.omask[at] > 0.0f ? v : 0.0f;
+    }
+  }
+}
+
+__device__ __forceinline__ float lane_xor_f(float v, bool far) {
+  return far ? __int_as_float(mg::xor_lane<16>(__float_as_int(v))) : __int_as_float(mg::xor_lane<1>(__float_as_int(v)));
+}
+
+template <int MODE, int WS>
+__global__ __launch_bounds__(256, 2) void conv32_kernel(Conv32Args a) {
+  __shared__ uint4 T[3][HP * 4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int x0 = blockIdx.x * CT, y0 = blockIdx.y * CT, b = blockIdx.z;
+  const float* inb = a.in + (size_t)b * a.H * a.W * C;
+  const int wbad = *a.wbad;
+  const uint4* fr = a.frag + lane;
+
+  // staging: thread i takes 8 channels (chunk i & 3) of halo pixel i >> 2
+  constexpr int NS = (HP * 4 + 255) / 256;
+  float st[NS][8];
+#pragma unroll
+  for (int k = 0; k < NS; ++k) {
+    const int i = tid + 256 * k, p = i >> 2, yy = p / HALO, xx = p - yy * HALO;
+    const int gy = y0 + yy - 1, gx = x0 + xx - 1;
+    float4 lo = make_float4(0.0f, 0.0f, 0.0f, 0.0f), hi = lo;
+    if (i < HP * 4 && gy >= 0 && gy < a.H && gx >= 0 && gx < a.W) {
+      const float4* src = reinterpret_cast<const float4*>(inb + ((size_t)gy * a.W + gx) * C) + 2 * (i & 3);
+      lo = src[0];
+      hi = src[1];
+    }
+    st[k][0] = lo.x; st[k][1] = lo.y; st[k][2] = lo.z; st[k][3] = lo.w;
+    st[k][4] = hi.x; st[k][5] = hi.y; st[k][6] = hi.z; st[k][7] = hi.w;
+  }
+  uint4 wf[2][WS];   // the next step's fragments are loaded while the current one multiplies
+#pragma unroll
+  for (int s = 0; s < WS; ++s) wf[0][s] = fr[s * 64];
+  float probe = 0.0f;
+#pragma unroll
+  for (int k = 0; k < NS; ++k) {
+    const int i = tid + 256 * k, p = i >> 2;
+    uint4 s[3];
+    split8(st[k], s, probe);
+    if (i < HP * 4) {
+      const int at = 4 * p + ((i & 3) ^ ((p >> 2) & 3));
+#pragma unroll
+      for (int q = 0; q < 3; ++q) T[q][at] = s[q];
+    }
+  }
+  if (__syncthreads_or(!(probe == 0.0f) || wbad)) {
+    conv32_scalar<MODE, WS>(a, b, y0, x0);
+    return;
+  }
+
+  const int h = lane >> 5, n = lane & 31;
+  f32x16 acc[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[k][r] = 0.0f;
+  const int p0 = (4 * wave + (n >> 4)) * HALO + (n & 15);
+#pragma unroll
+  for (int step = 0; step < 18; ++step) {
+    const int t = step >> 1, kh = step & 1;
+    if (step + 1 < 18) {
+#pragma unroll
+      for (int s = 0; s < WS; ++s) wf[(step + 1) & 1][s] = fr[((step + 1) * WS + s) * 64];
+    }
+    uint4 x[2][3];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int p = p0 + (2 * k + t / 3) * HALO + t % 3;
+      const int at = 4 * p + ((2 * kh + h) ^ ((p >> 2) & 3));
+#pragma unroll
+      for (int q = 0; q < 3; ++q) x[k][q] = T[q][at];
+    }
+#pragma unroll
+    for (int j = 0; j < Pairs<WS>::N; ++j)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) acc[k] = mfma(wf[step & 1][Pairs<WS>::w[j]], x[k][Pairs<WS>::x[j]], acc[k]);
+  }
+
+  // lane (h, n) holds channels 8 q + 4 h + (0..3) of pixel n of each block
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int y = y0 + 4 * wave + 2 * k + (n >> 4), x = x0 + (n & 15);
+    const bool in = y < a.H && x < a.W;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int c0 = 8 * q + 4 * h;
+      float4 v = make_float4(acc[k][4 * q], acc[k][4 * q + 1], acc[k][4 * q + 2], acc[k][4 * q + 3]);
+      if constexpr (MODE == 2) {
+        if (in) {
+          const size_t at = (((size_t)b * a.H + y) * a.W + x) * C + c0;
+          const float4 mk = *reinterpret_cast<const float4*>(a.omask + at);
+          v = make_float4(mk.x > 0.0f ? v.x : 0.0f, mk.y > 0.0f ? v.y : 0.0f, mk.z > 0.0f ? v.z : 0.0f,
+                          mk.w > 0.0f ? v.w : 0.0f);
+          *reinterpret_cast<float4*>(a.out + at) = v;
+        }
+      } else {
+        // 2 x 2 sums: the horizontal neighbour, then the row below
+        v = make_float4(v.x + lane_xor_f(v.x, false), v.y + lane_xor_f(v.y, false), v.z + lane_xor_f(v.z, false),
+                        v.w + lane_xor_f(v.w, false));
+        v = make_float4(v.x + lane_xor_f(v.x, true), v.y + lane_xor_f(v.y, true), v.z + lane_xor_f(v.z, true),
+                        v.w + lane_xor_f(v.w, true));
+        if (in && !(n & 17)) {
+          const size_t at = (((size_t)b * (a.H >> 1) + (y >> 1)) * (a.W >> 1) + (x >> 1)) * C + c0;
+          const float4 mk = *reinterpret_cast<const float4*>(a.omask + at);
+          v = make_float4(mk.x > 0.0f ? v.x : 0.0f, mk.y > 0.0f ? v.y : 0.0f, mk.z > 0.0f ? v.z : 0.0f,
+                          mk.w > 0.0f ? v.w : 0.0f);
+          *reinterpret_cast<float4*>(a.out + at) = v;
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Few -> 32 channels (the first layer; backward-data of the last one)
+// ---------------------------------------------------------------------------
+// Planes in, channels-last out.  One workgroup per 16 x 4 pixels, each wave eight output
+// channels of all 64 pixels, so its weights w[co][c][t] are uniform (scalar loads); the
+// four waves share the input reads in L1.  9 CI FMAs per output value against 4 bytes
+// written (and 4 of mask read): bound by memory.
+template <int CI, bool MASK>
+__global__ __launch_bounds__(256) void conv_thin_kernel(const float* __restrict__ in, const float* __restrict__ w,
+                                                        const float* __restrict__ bias, float* __restrict__ out,
+                                                        const float* __restrict__ omask, int H, int W) {
+  const int lane = threadIdx.x & 63, cog = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int x = blockIdx.x * 16 + (lane & 15), y = blockIdx.y * 4 + (lane >> 4), b = blockIdx.z;
+  const float* inb = in + (size_t)b * CI * H * W;
+  float v[CI][9];
+#pragma unroll
+  for (int c = 0; c < CI; ++c)
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int gy = y + t / 3 - 1, gx = x + t % 3 - 1;
+      v[c][t] = (gy >= 0 && gy < H && gx >= 0 && gx < W) ? inb[((size_t)c * H + gy) * W + gx] : 0.0f;
+    }
+  float acc[8];
+#pragma unroll
+  for (int o = 0; o < 8; ++o) {
+    acc[o] = MASK ? 0.0f : bias[cog * 8 + o];
+#pragma unroll
+    for (int c = 0; c < CI; ++c)
+#pragma unroll
+      for (int t = 0; t < 9; ++t) acc[o] = fmaf(w[((cog * 8 + o) * CI + c) * 9 + t], v[c][t], acc[o]);
+  }
+  if (y >= H || x >= W) return;
+  const size_t at = (((size_t)b * H + y) * W + x) * C + cog * 8;
+  float4* dst = reinterpret_cast<float4*>(out + at);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    float4 r = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+    if constexpr (MASK) {
+      const float4 mk = reinterpret_cast<const float4*>(omask + at)[q];
+      r = make_float4(mk.x > 0.0f ? r.x : 0.0f, mk.y > 0.0f ? r.y : 0.0f, mk.z > 0.0f ? r.z : 0.0f,
+                      mk.w > 0.0f ? r.w : 0.0f);
+    } else {
+      r = make_float4(fmaxf(r.x, 0.0f), fmaxf(r.y, 0.0f), fmaxf(r.z, 0.0f), fmaxf(r.w, 0.0f));
+    }
+    dst[q] = r;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// 32 -> 2 channels (the head): channels-last in, planes out
+// ---------------------------------------------------------------------------
+// One workgroup per 16 x 16 tile, one pixel per thread; the halo is staged as it is (128
+// bytes per pixel, chunks rotated against bank conflicts), the weights w[c][t][o] are
+// uniform.  576 FMAs per 128 bytes read: bound by the read of the activations.
+__global__ __launch_bounds__(256) void conv_head_kernel(const float* __restrict__ in, const float* __restrict__ w,
+                                                        const float* __restrict__ bias, float* __restrict__ out,
+                                                        int H, int W) {
+  __shared__ float4 T[HP * 8];
+  const int x0 = blockIdx.x * CT, y0 = blockIdx.y * CT, b = blockIdx.z;
+  const float* inb = in + (size_t)b * H * W * C;
+  for (int i = threadIdx.x; i < HP * 8; i += 256) {
+    const int p = i >> 3, yy = p / HALO, xx = p - yy * HALO, gy = y0 + yy - 1, gx = x0 + xx - 1;
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (gy >= 0 && gy < H && gx >= 0 && gx < W)
+      v = reinterpret_cast<const float4*>(inb + ((size_t)gy * W + gx) * C)[i & 7];
+    T[8 * p + ((i & 7) ^ ((p >> 1) & 7))] = v;
+  }
+  __syncthreads();
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  float a0 = bias[0], a1 = bias[1];
+#pragma unroll 1
+  for (int q = 0; q < 8; ++q) {
+    float4 v[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int p = (ty + t / 3) * HALO + tx + t % 3;
+      v[t] = T[8 * p + (q ^ ((p >> 1) & 7))];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const float xv = c == 0 ? v[t].x : c == 1 ? v[t].y : c == 2 ? v[t].z : v[t].w;
+        const float* wq = w + ((4 * q + c) * 9 + t) * 2;
+        a0 = fmaf(wq[0], xv, a0);
+        a1 = fmaf(wq[1], xv, a1);
+      }
+  }
+  const int y = y0 + ty, x = x0 + tx;
+  if (y < H && x < W) {
+    const size_t at = ((size_t)b * 2 * H + y) * W + x;
+    out[at] = a0;
+    out[at + (size_t)H * W] = a1;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Weight gradients
+// ---------------------------------------------------------------------------
+// Workgroups of four waves walk runs of 16 x 8 pixel tiles.  The tensors are staged
+// transposed: channel by channel, 16 consecutive pixels of a row as split bf16 values
+// (a staging thread reads eight pixels of its channel, 32 lanes reading the 128
+// contiguous bytes of a pixel), so a row of a tile is one K = 16 step of
+// D[row channel][column channel] += A[channel][pixel] B[pixel][channel].
+constexpr int GH = 8;                                  // tile rows
+constexpr int A_PITCH = GH * 32 + 16;                  // bytes per channel of a staged tile without halo
+constexpr int B_ROW = 48;                              // bytes per row of the halo tile (24 pixels, 18 used)
+constexpr int B_PITCH = (GH + 2) * B_ROW + 16;         // odd multiples of 16 bytes: no bank conflicts
+constexpr int SQ_LDS = 3 * C * (A_PITCH + B_PITCH);    // 74 KB: two workgroups per CU
+
+struct Wgrad32Args {
+  const float* in;      // [B][Hi][Wi][32]
+  const float* dout;    // [B][H][W][32]
+  float* part;
+  int H, W, tiles_x, tiles_per_sample, total_tiles, tiles_per_wg;
+};
+
+// dout of 8 pixels (channel c, row y, from x): FP32 values, 0 outside
+template <bool UP>
+__device__ __forceinline__ void load8(const float* base, int H, int W, int y, int x, int c, int n, float* v) {
+  const int Wi = UP ? W >> 1 : W;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int gx = x + j;
+    v[j] = (j < n && y >= 0 && y < H && gx >= 0 && gx < W)
+               ? base[((size_t)(UP ? y >> 1 : y) * Wi + (UP ? gx >> 1 : gx)) * C + c]
+               : 0.0f;
+  }
+}
+
+// The scalar form of a run of tiles: element e of its part row, summed pixel by pixel.
+template <bool UP>
+__device__ __noinline__ void wgrad32_scalar(const Wgrad32Args& a, int t_begin, int t_end) {
+  const int Hi = UP ? a.H >> 1 : a.H, Wi = UP ? a.W >> 1 : a.W;
+  float* pr = a.part + (size_t)blockIdx.x * SQ_ROW;
+  for (int e = threadIdx.x; e < SQ_ROW; e += 256) {
+    const int t = e >> 10, r = (e >> 6) & 15, lane = e & 63;
+    const bool isb = e >= 9 * C * C;
+    const int co = isb ? e - 9 * C * C : 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), ci = lane & 31;
+    float acc = 0.0f;
+    for (int tile = t_begin; tile < t_end; ++tile) {
+      const int b = tile / a.tiles_per_sample, tr = tile - b * a.tiles_per_sample;
+      for (int p = 0; p < GH * 16; ++p) {
+        const int y = (tr / a.tiles_x) * GH + p / 16, x = (tr % a.tiles_x) * 16 + p % 16;
+        if (y >= a.H || x >= a.W) continue;
+        const float g = a.dout[(((size_t)b * a.H + y) * a.W + x) * C + co];
+        if (isb) {
+          acc += g;
+          continue;
+        }
+        const int gy = y + t / 3 - 1, gx = x + t % 3 - 1;
+        const bool in = gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
+        acc = fmaf(g, in ? a.in[(((size_t)b * Hi + (UP ? gy >> 1 : gy)) * Wi + (UP ? gx >> 1 : gx)) * C + ci] : 0.0f,
+                   acc);
+      }
+    }
+    pr[e] = acc;
+  }
+}
+
+// 32 x 32 channels: all nine taps of a K step from three row reads of the halo tile, the
+// horizontal shifts formed in registers (a wave holds the nine 32 x 32 sums, 144
+// registers).  Each wave takes two rows of the tile; the four waves' sums are added in
+// order through LDS at the end of the run.
+template <bool UP>
+__global__ __launch_bounds__(256, 2) void wgrad32_kernel(Wgrad32Args a) {
+  extern __shared__ uint4 smem[];
+  unsigned char* const As = reinterpret_cast<unsigned char*>(smem);         // dout
+  unsigned char* const Bs = As + 3 * C * A_PITCH;                           // in, with halo
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
+  const int Hi = UP ? a.H >> 1 : a.H, Wi = UP ? a.W >> 1 : a.W;
+  f32x16 acc[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+  float bsum = 0.0f, probe = 0.0f;   // this thread's share of channel tid & 31's bias gradient
+  const int t_begin = blockIdx.x * a.tiles_per_wg, t_end = min(a.total_tiles, t_begin + a.tiles_per_wg);
+  const int sc = tid & 31, sg = tid >> 5;
+  for (int tile = t_begin; tile < t_end; ++tile) {
+    const int b = tile / a.tiles_per_sample, tr = tile - b * a.tiles_per_sample;
+    const int y0 = (tr / a.tiles_x) * GH, x0 = (tr % a.tiles_x) * 16;
+    const float* inb = a.in + (size_t)b * Hi * Wi * C;
+    const float* dob = a.dout + (size_t)b * a.H * a.W * C;
+    float va[2][8], vb[4][8];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {   // 16 groups of 8 pixels, 8 rows x 2
+      const int i = sg + 8 * k;
+      load8<false>(dob, a.H, a.W, y0 + (i >> 1), x0 + 8 * (i & 1), sc, 8, va[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {   // 30 groups, 10 rows x 3 (the third of 2 pixels)
+      const int i = sg + 8 * k, row = i / 3, gx = i - 3 * row;
+      load8<UP>(inb, a.H, a.W, i < 30 ? y0 + row - 1 : -1, x0 + 8 * gx - 1, sc, gx == 2 ? 2 : 8, vb[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int i = sg + 8 * k;
+      uint4 s[3];
+      split8(va[k], s, probe);
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        *reinterpret_cast<uint4*>(As + (q * C + sc) * A_PITCH + 16 * i) = s[q];
+      bsum += ((va[k][0] + va[k][1]) + (va[k][2] + va[k][3])) + ((va[k][4] + va[k][5]) + (va[k][6] + va[k][7]));
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = sg + 8 * k;
+      uint4 s[3];
+      split8(vb[k], s, probe);
+      if (i < 30)
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          *reinterpret_cast<uint4*>(Bs + (q * C + sc) * B_PITCH + 16 * i) = s[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int row = 2 * wave + k;
+      uint4 g[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        g[q] = *reinterpret_cast<const uint4*>(As + (q * C + n) * A_PITCH + row * 32 + h * 16);
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy) {
+        uint4 x[3][3];   // [dx][part]
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const unsigned char* src = Bs + (q * C + n) * B_PITCH + (row + dy) * B_ROW + h * 16;
+          const uint4 d = *reinterpret_cast<const uint4*>(src);
+          const uint32_t d4 = *reinterpret_cast<const uint32_t*>(src + 16);
+          x[0][q] = d;
+          x[1][q] = make_uint4(__builtin_amdgcn_alignbit(d.y, d.x, 16), __builtin_amdgcn_alignbit(d.z, d.y, 16),
+                               __builtin_amdgcn_alignbit(d.w, d.z, 16), __builtin_amdgcn_alignbit(d4, d.w, 16));
+          x[2][q] = make_uint4(d.y, d.z, d.w, d4);
+        }
+#pragma unroll
+        for (int j = 0; j < 6; ++j)
+#pragma unroll
+          for (int dx = 0; dx < 3; ++dx)
+            acc[3 * dy + dx] = mfma(g[Pairs<3>::w[j]], x[dx][Pairs<3>::x[j]], acc[3 * dy + dx]);
+      }
+    }
+    __syncthreads();
+  }
+  if (__syncthreads_or(!(probe == 0.0f))) {
+    wgrad32_scalar<UP>(a, t_begin, t_end);
+    return;
+  }
+  // the waves' sums in order, then the row: fragment order [t][r][lane], then the bias
+  float* const red = reinterpret_cast<float*>(smem);
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w)
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float* d = red + (t * 16 + r) * 64 + lane;
+          *d = w ? *d + acc[t][r] : acc[t][r];
+        }
+    __syncthreads();
+  }
+  float* pr = a.part + (size_t)blockIdx.x * SQ_ROW;
+  for (int e = tid; e < 9 * C * C; e += 256) pr[e] = red[e];
+  __syncthreads();
+  red[tid] = bsum;
+  __syncthreads();
+  if (tid < C) {
+    float s = red[tid];
+    for (int k = 1; k < 8; ++k) s += red[tid + 32 * k];
+    pr[9 * C * C + tid] = s;
+  }
+}
+
+// A 32-channel tensor against one of few channels (the first layer's input, the head's
+// output gradient): the columns of D are the (tap, channel) pairs, t CN + c, padded to
+// 32 or 64, so one product of K = 16 covers all taps.  The few channels are staged as
+// three copies shifted by one pixel each, so that every tap's 8 pixels are aligned.
+// FLIP (head): wide = the layer's input x[p], thin = dy[p - d]; otherwise wide = dout[p],
+// thin = x[p + d].  Bound by the read of the 32-channel tensor.
+struct WgradThinArgs {
+  const float* wide;    // [B][H][W][32]
+  const float* thin;    // [B][CN][H][W]
+  float* part;
+  int H, W, tiles_x, tiles_per_sample, total_tiles, tiles_per_wg;
+};
+
+template <int CN, bool FLIP>
+__device__ __noinline__ void wgrad_thin_scalar(const WgradThinArgs& a, int t_begin, int t_end) {
+  constexpr int NB = (9 * CN + 31) / 32, ROW = thin_row(CN, FLIP);
+  float* pr = a.part + (size_t)blockIdx.x * ROW;
+  for (int e = threadIdx.x; e < ROW; e += 256) {
+    const int r = (e >> 6) & 15, lane = e & 63, nn = 32 * (e >> 10) + (lane & 31), t = nn / CN, c = nn % CN;
+    const bool isb = e >= NB * C * C;
+    const int rowc = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), bc = e - NB * C * C;
+    float acc = 0.0f;
+    if (isb || nn < 9 * CN)
+      for (int tile = t_begin; tile < t_end; ++tile) {
+        const int b = tile / a.tiles_per_sample, tr = tile - b * a.tiles_per_sample;
+        for (int p = 0; p < GH * 16; ++p) {
+          const int y = (tr / a.tiles_x) * GH + p / 16, x = (tr % a.tiles_x) * 16 + p % 16;
+          if (y >= a.H || x >= a.W) continue;
+          const float* wide = a.wide + (((size_t)b * a.H + y) * a.W + x) * C;
+          if (isb) {
+            acc += wide[bc];
+            continue;
+          }
+          const int sg = FLIP ? -1 : 1, gy = y + sg * (t / 3 - 1), gx = x + sg * (t % 3 - 1);
+          const bool in = gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
+          acc = fmaf(wide[rowc], in ? a.thin[(((size_t)b * CN + c) * a.H + gy) * a.W + gx] : 0.0f, acc);
+        }
+      }
+    pr[e] = acc;
+  }
+}
+
+template <int CN, bool FLIP>
+__global__ __launch_bounds__(256) void wgrad_thin_kernel(WgradThinArgs a) {
+  constexpr int NB = (9 * CN + 31) / 32, ROW = thin_row(CN, FLIP);
+  constexpr int COPY = (GH + 2) * 32;                            // one shifted copy: 10 rows of 16 pixels
+  __shared__ uint4 As4[3 * C * A_PITCH / 16];
+  __shared__ uint4 Ts4[3 * CN * 3 * COPY / 16];
+  __shared__ float red[NB * C * C > 256 ? NB * C * C : 256];
+  unsigned char* const As = reinterpret_cast<unsigned char*>(As4);
+  unsigned char* const Ts = reinterpret_cast<unsigned char*>(Ts4);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
+  f32x16 acc[NB];
+#pragma unroll
+  for (int k = 0; k < NB; ++k)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[k][r] = 0.0f;
+  float bsum = 0.0f, probe = 0.0f;
+  const int t_begin = blockIdx.x * a.tiles_per_wg, t_end = min(a.total_tiles, t_begin + a.tiles_per_wg);
+  const int sc = tid & 31, sg = tid >> 5;
+  // byte offset of column n's pixels in the staged copies (part 0, row 0); columns past
+  // 9 CN read column 0's and are dropped
+  int toff[NB];
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    const int nn = 32 * k + n < 9 * CN ? 32 * k + n : 0, t = nn / CN, c = nn % CN;
+    const int dy = FLIP ? 2 - t / 3 : t / 3, dx = FLIP ? 2 - t % 3 : t % 3;
+    toff[k] = (c * 3 + dx) * COPY + dy * 32 + h * 16;
+  }
+  for (int tile = t_begin; tile < t_end; ++tile) {
+    const int b = tile / a.tiles_per_sample, tr = tile - b * a.tiles_per_sample;
+    const int y0 = (tr / a.tiles_x) * GH, x0 = (tr % a.tiles_x) * 16;
+    const float* wb = a.wide + (size_t)b * a.H * a.W * C;
+    const float* tb = a.thin + (size_t)b * CN * a.H * a.W;
+    float va[2][8];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int i = sg + 8 * k;
+      load8<false>(wb, a.H, a.W, y0 + (i >> 1), x0 + 8 * (i & 1), sc, 8, va[k]);
+    }
+    // groups of 8 pixels: channel, copy dx, row, half
+    for (int i = tid; i < CN * 3 * (GH + 2) * 2; i += 256) {
+      const int half = i & 1, row = (i >> 1) % (GH + 2), cd = (i >> 1) / (GH + 2), c = cd / 3, dx = cd - 3 * c;
+      const int gy = y0 + row - 1;
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int gx = x0 + 8 * half + j + dx - 1;
+        v[j] = (gy >= 0 && gy < a.H && gx >= 0 && gx < a.W) ? tb[((size_t)c * a.H + gy) * a.W + gx] : 0.0f;
+      }
+      uint4 s[3];
+      split8(v, s, probe);
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        *reinterpret_cast<uint4*>(Ts + (q * CN * 3 + cd) * COPY + row * 32 + half * 16) = s[q];
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int i = sg + 8 * k;
+      uint4 s[3];
+      split8(va[k], s, probe);
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        *reinterpret_cast<uint4*>(As + (q * C + sc) * A_PITCH + 16 * i) = s[q];
+      if constexpr (!FLIP)
+        bsum += ((va[k][0] + va[k][1]) + (va[k][2] + va[k][3])) + ((va[k][4] + va[k][5]) + (va[k][6] + va[k][7]));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int row = 2 * wave + k;
+      uint4 g[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        g[q] = *reinterpret_cast<const uint4*>(As + (q * C + n) * A_PITCH + row * 32 + h * 16);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        uint4 x[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          x[q] = *reinterpret_cast<const uint4*>(Ts + q * CN * 3 * COPY + toff[nb] + row * 32);
+#pragma unroll
+        for (int j = 0; j < 6; ++j) acc[nb] = mfma(g[Pairs<3>::w[j]], x[Pairs<3>::x[j]], acc[nb]);
+      }
+    }
+    __syncthreads();
+  }
+  if (__syncthreads_or(!(probe == 0.0f))) {
+    wgrad_thin_scalar<CN, FLIP>(a, t_begin, t_end);
+    return;
+  }
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w)
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float* d = red + (k * 16 + r) * 64 + lane;
+          *d = w ? *d + acc[k][r] : acc[k][r];
+        }
+    __syncthreads();
+  }
+  float* pr = a.part + (size_t)blockIdx.x * ROW;
+  for (int e = tid; e < NB * C * C; e += 256) pr[e] = red[e];
+  if constexpr (!FLIP) {
+    __syncthreads();
+    red[tid] = bsum;
+    __syncthreads();
+    if (tid < C) {
+      float s = red[tid];
+      for (int k = 1; k < 8; ++k) s += red[tid + 32 * k];
+      pr[NB * C * C + tid] = s;
+    }
+  }
+}
+
+// Bias gradient of the head: its phase channel's sum is zero but for rounding (see the
+// top of this file), so the order is fixed for good: runs of 16 x 16 tiles pixel by pixel,
+// the runs in four strided sets.  One workgroup per run stages a tile's two planes and
+// two lanes add them up (256 dependent additions per tile).
+__global__ __launch_bounds__(256) void head_bias_kernel(const float* __restrict__ dy, float* __restrict__ part, int H,
+                                                        int W, int tiles_x, int tiles_per_sample, int total_tiles,
+                                                        int tiles_per_wg) {
+  __shared__ float4 v[2][CT * CT / 4];
+  const int t_begin = blockIdx.x * tiles_per_wg, t_end = min(total_tiles, t_begin + tiles_per_wg);
+  float acc = 0.0f;
+  for (int tile = t_begin; tile < t_end; ++tile) {
+    const int b = tile / tiles_per_sample, tr = tile - b * tiles_per_sample;
+    const int y = (tr / tiles_x) * CT + threadIdx.x / CT, x = (tr % tiles_x) * CT + threadIdx.x % CT;
+    const bool in = y < H && x < W;
+    const float* src = dy + ((size_t)b * 2 * H + y) * W + x;
+    const float d0 = in ? src[0] : 0.0f, d1 = in ? src[(size_t)H * W] : 0.0f;
+    __syncthreads();
+    reinterpret_cast<float*>(v[0])[threadIdx.x] = d0;
+    reinterpret_cast<float*>(v[1])[threadIdx.x] = d1;
+    __syncthreads();
+    if (threadIdx.x < 2)
+#pragma unroll 8
+      for (int i = 0; i < CT * CT / 4; ++i) {
+        const float4 q = v[threadIdx.x][i];
+        acc += q.x;
+        acc += q.y;
+        acc += q.z;
+        acc += q.w;
+      }
+  }
+  if (threadIdx.x < 2) part[2 * blockIdx.x + threadIdx.x] = acc;
+}
+
+__global__ __launch_bounds__(64) void head_bias_sum_kernel(const float* __restrict__ part, int n_rows,
+                                                           float* __restrict__ grad) {
+  __shared__ float red[4][2];
+  const int j = threadIdx.x & 1, s = threadIdx.x >> 1;
+  if (s < 4) {
+    float acc = 0.0f;
+#pragma unroll 8
+    for (int r = s; r < n_rows; r += 4) acc += part[2 * r + j];
+    red[s][j] = acc;
+  }
+  __syncthreads();
+  if (s == 0) grad[j] = ((red[0][j] + red[1][j]) + red[2][j]) + red[3][j];
+}
+
+// grad = sum of the part rows, from fragment order to the layer's parameter order:
+// column e of a row is (t, r, lane) of a square layer, (block, r, lane) of a thin one,
+// then (not the head) the bias.  64 columns per workgroup, 16 strided row sets combined in order.
+// KIND 0: square; 1: first layer (CN input channels); 2: head (CN output channels).
+template <int KIND>
+__global__ __launch_bounds__(1024) void rows_sum_kernel(const float* __restrict__ part, int n_rows, int row_len,
+                                                        int n_w, int cn, float* __restrict__ grad) {
+  __shared__ float red[16][64];
+  const int jj = threadIdx.x & 63, s = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + jj;
+  float acc = 0.0f;
+  if (e < row_len)
+#pragma unroll 8
+    for (int r = s; r < n_rows; r += 16) acc += part[(size_t)r * row_len + e];
+  red[s][jj] = acc;
+  __syncthreads();
+  if (s || e >= row_len) return;
+  acc = red[0][jj];
+#pragma unroll
+  for (int k = 1; k < 16; ++k) acc += red[k][jj];
+  if (e >= n_w) {
+    grad[(KIND == 0 ? 9 * C * C : 9 * C * cn) + e - n_w] = acc;
+    return;
+  }
+  const int r = (e >> 6) & 15, lane = e & 63, row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+  if (KIND == 0) {
+    grad[(row * C + (lane & 31)) * 9 + (e >> 10)] = acc;
+  } else {
+    const int nn = 32 * (e >> 10) + (lane & 31), t = nn / cn, c = nn % cn;
+    if (nn < 9 * cn) grad[(KIND == 1 ? (row * cn + c) : (c * C + row)) * 9 + t] = acc;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Compute copies of the weights (all layers in one launch)
+// ---------------------------------------------------------------------------
+// Forward: [chunk of four input channels][tap][co] float4 per 32 -> 32 layer.  Backward-
+// data: fragments [tap][half of its input channels][part][lane] of eight bf16 values, lane
+// (h, co) holding input channels 16 half + 8 h + (0..7).
+__global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
+  constexpr int NF = 3 * 8 * 9 * C, NB = 3 * 18 * 64;
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  bool bad = false;
+  if (i < NF) {
+    const int layer = i / (8 * 9 * C), e = i - layer * (8 * 9 * C), co = e % C, t = (e / C) % 9, g = e / (9 * C);
+    const float* w = a.p + a.off_sq[layer] + (co * C + 4 * g) * 9 + t;
+    float4 v = make_float4(w[0], w[9], w[18], w[27]);
+    if (a.bf16) v = make_float4(round_bf16(v.x), round_bf16(v.y), round_bf16(v.z), round_bf16(v.w));
+    a.fwd[i] = v;
+  } else if (i < NF + NB) {
+    const int j0 = i - NF, layer = j0 / (18 * 64), e = j0 - layer * (18 * 64), step = e >> 6, lane = e & 63;
+    const int t = step >> 1, k0 = 16 * (step & 1) + 8 * (lane >> 5), co = lane & 31;
+    const float* w = a.p + a.off_sq[layer];
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      v[j] = w[((k0 + j) * C + co) * 9 + 8 - t];
+      if (a.bf16) v[j] = round_bf16(v[j]);
+    }
+    uint4 s[3];
+    float probe = 0.0f;
+    split8(v, s, probe);
+    bad = !(probe == 0.0f);
+    const int ws = a.bf16 ? 1 : 3;
+    uint4* dst = a.frag + (size_t)layer * FRAG_VECS;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (q < ws) dst[(step * ws + q) * 64 + lane] = s[q];
+  } else {
+    // first layer as it is; head as [c][t][o] and, for backward-data, [c][o][8 - t]
+    const int j = i - NF - NB, n0 = C * a.cin * 9, n4 = 2 * C * 9;
+    if (j < n0) {
+      const float v = a.p[a.off_first + j];
+      a.first[j] = a.bf16 ? round_bf16(v) : v;
+    } else if (j < n0 + n4) {
+      const int q = j - n0, o = q / (C * 9), c = (q / 9) % C, t = q % 9;
+      float v = a.p[a.off_head + q];
+      v = a.bf16 ? round_bf16(v) : v;
+      a.head[(c * 9 + t) * 2 + o] = v;
+      a.head_t[(c * 2 + o) * 9 + 8 - t] = v;
+    }
+  }
+  if (bad) atomicOr(a.wbad, 1);
+}
+
+__global__ void clear_flag_kernel(int* p) { *p = 0; }
+
+template <int MODE>
+hipError_t conv32_t(bool bf16, const Conv32Args& a, int batch, hipStream_t s) {
+  const dim3 grid((a.W + CT - 1) / CT, (a.H + CT - 1) / CT, batch);
+  if (bf16) hipLaunchKernelGGL((conv32_kernel<MODE, 1>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((conv32_kernel<MODE, 3>), grid, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+struct Tiling {
+  int tiles_x, per_sample, total, per_wg, wgs;
+};
+Tiling wgrad_tiling(int batch, int H, int W) {
+  Tiling t;
+  t.tiles_x = (W + 15) / 16;
+  t.per_sample = t.tiles_x * ((H + GH - 1) / GH);
+  t.total = batch * t.per_sample;
+  t.per_wg = (t.total + WGRAD_MAX_WORKGROUPS - 1) / WGRAD_MAX_WORKGROUPS;
+  t.wgs = (t.total + t.per_wg - 1) / t.per_wg;
+  return t;
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------------------
+// Launchers
+// ---------------------------------------------------------------------------
+hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, s, a.wbad);
+  const int n = 3 * 8 * 9 * C + 3 * 18 * 64 + C * a.cin * 9 + 2 * C * 9;
+  hipLaunchKernelGGL(prep_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_conv32(bool up, const float* in, const float4* w, const float* bias, float* out, int batch, int H,
+                         int W, hipStream_t s) {
+  if (batch < 1 || H < 1 || W < 1 || (up && ((H | W) & 1))) return hipErrorInvalidValue;
+  const dim3 grid((W + CT - 1) / CT, (H + CT - 1) / CT, batch);
+  if (up) hipLaunchKernelGGL(conv32_forward_kernel<true>, grid, dim3(256), 0, s, in, w, bias, out, H, W);
+  else hipLaunchKernelGGL(conv32_forward_kernel<false>, grid, dim3(256), 0, s, in, w, bias, out, H, W);
+  return hipGetLastError();
+}
+
+hipError_t launch_conv32_backward(bool up, bool bf16, const float* in, const uint4* frag, const float* w, float* out,
+                                  const float* omask, const int* wbad, int batch, int H, int W, hipStream_t s) {
+  if (batch < 1 || H < 1 || W < 1 || (up && ((H | W) & 1))) return hipErrorInvalidValue;
+  const Conv32Args a{in, frag, w, out, omask, wbad, H, W};
+  return up ? conv32_t<3>(bf16, a, batch, s) : conv32_t<2>(bf16, a, batch, s);
+}
+
+hipError_t launch_conv_first(int ci, const float* in, const float* w, const float* bias, float* out, int batch, int H,
+                             int W, hipStream_t s) {
+  if (batch < 1 || H < 1 || W < 1) return hipErrorInvalidValue;
+  const dim3 grid((W + 15) / 16, (H + 3) / 4, batch);
+#define CNN_FIRST(CI)                                                                                              \
+  if (ci == CI) {                                                                                                  \
+    hipLaunchKernelGGL((conv_thin_kernel<CI, false>), grid, dim3(256), 0, s, in, w, bias, out, nullptr, H, W);     \
+    return hipGetLastError();                                                                                      \
+  }
+  CNN_FIRST(1)
+  CNN_FIRST(3)
+  CNN_FIRST(4)
+#undef CNN_FIRST
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_conv_head(const float* in, const float* w, const float* bias, float* out, int batch, int H, int W,
+                            hipStream_t s) {
+  if (batch < 1 || H < 1 || W < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(conv_head_kernel, dim3((W + CT - 1) / CT, (H + CT - 1) / CT, batch), dim3(256), 0, s, in, w, bias,
+                     out, H, W);
+  return hipGetLastError();
+}
+
+hipError_t launch_conv_head_backward(const float* dy, const float* w, float* out, const float* omask, int batch,
+                                     int H, int W, hipStream_t s) {
+  if (batch < 1 || H < 1 || W < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((conv_thin_kernel<2, true>), dim3((W + 15) / 16, (H + 3) / 4, batch), dim3(256), 0, s, dy, w,
+                     nullptr, out, omask, H, W);
+  return hipGetLastError();
+}
+
+hipError_t launch_wgrad32(bool up, const float* in, const float* dout, float* part, float* grad, int batch, int H,
+                          int W, hipStream_t s) {
+  if (batch < 1 || H < 1 || W < 1 || (up && ((H | W) & 1))) return hipErrorInvalidValue;
+  const Tiling t = wgrad_tiling(batch, H, W);
+  const Wgrad32Args a{in, dout, part, H, W, t.tiles_x, t.per_sample, t.total, t.per_wg};
+  const void* k = up ? (const void*)wgrad32_kernel<true> : (const void*)wgrad32_kernel<false>;
+  const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SQ_LDS);
+  if (e != hipSuccess) return e;
+  if (up) hipLaunchKernelGGL(wgrad32_kernel<true>, dim3(t.wgs), dim3(256), SQ_LDS, s, a);
+  else hipLaunchKernelGGL(wgrad32_kernel<false>, dim3(t.wgs), dim3(256), SQ_LDS, s, a);
+  hipLaunchKernelGGL(rows_sum_kernel<0>, dim3((SQ_ROW + 63) / 64), dim3(1024), 0, s, (const float*)part, t.wgs, SQ_ROW,
+                     9 * C * C, C, grad);
+  return hipGetLastError();
+}
+
+hipError_t launch_wgrad_first(int ci, const float* in, const float* dout, float* part, float* grad, int batch, int H,
+                              int W, hipStream_t s) {
+  if (batch < 1 || H < 1 || W < 1) return hipErrorInvalidValue;
+  const Tiling t = wgrad_tiling(batch, H, W);
+  const WgradThinArgs a{dout, in, part, H, W, t.tiles_x, t.per_sample, t.total, t.per_wg};
+  const int row = thin_row(ci, false);
+#define CNN_WF(CI) \
+  if (ci == CI) hipLaunchKernelGGL((wgrad_thin_kernel<CI, false>), dim3(t.wgs), dim3(256), 0, s, a);
+  CNN_WF(1) else CNN_WF(3) else CNN_WF(4) else return hipErrorInvalidValue;
+#undef CNN_WF
+  hipLaunchKernelGGL(rows_sum_kernel<1>, dim3((row + 63) / 64), dim3(1024), 0, s, (const float*)part, t.wgs, row,
+                     row - C, ci, grad);
+  return hipGetLastError();
+}
+
+hipError_t launch_wgrad_head(const float* in, const float* dy, float* part, float* grad, int batch, int H, int W,
+                             hipStream_t s) {
+  if (batch < 1 || H < 1 || W < 1) return hipErrorInvalidValue;
+  const Tiling t = wgrad_tiling(batch, H, W);
+  const WgradThinArgs a{in, dy, part, H, W, t.tiles_x, t.per_sample, t.total, t.per_wg};
+  const int row = thin_row(2, true);
+  hipLaunchKernelGGL((wgrad_thin_kernel<2, true>), dim3(t.wgs), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(rows_sum_kernel<2>, dim3((row + 63) / 64), dim3(1024), 0, s, (const float*)part, t.wgs, row, row,
+                     2, grad);
+  // the bias: 16 x 16 tiles, behind the rows just used (at most 512 of 1024 floats)
+  const int tx = (W + CT - 1) / CT, per_sample = tx * ((H + CT - 1) / CT), total = batch * per_sample;
+  const int per = (total + WGRAD_MAX_WORKGROUPS - 1) / WGRAD_MAX_WORKGROUPS, wgs = (total + per - 1) / per;
+  float* const bp = part + (size_t)WGRAD_MAX_WORKGROUPS * row;
+  hipLaunchKernelGGL(head_bias_kernel, dim3(wgs), dim3(256), 0, s, dy, bp, H, W, tx, per_sample, total, per);
+  hipLaunchKernelGGL(head_bias_sum_kernel, dim3(1), dim3(64), 0, s, (const float*)bp, wgs, grad + 2 * C * 9);
+  return hipGetLastError();
+}
+
+}  // namespace cnn

@@ -37,8 +37,10 @@ struct magpie_cnn {
   int64_t off_w[N_LAYERS], off_b[N_LAYERS];
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
   int64_t t = 0;
-  void* wf[N_LAYERS] = {};
-  void* wt[N_LAYERS] = {};
+  float4* fwd = nullptr;     // compute copies of the weights (cnn::PrepArgs)
+  uint4* frag = nullptr;
+  float* wthin = nullptr;    // first, head, head_t
+  int* wbad = nullptr;
   float *x = nullptr, *a1 = nullptr, *a2 = nullptr, *a3 = nullptr, *a4 = nullptr, *y = nullptr, *dy = nullptr;
   float *f0 = nullptr, *f1 = nullptr, *l0 = nullptr, *l1 = nullptr;
   float* part = nullptr;
@@ -59,10 +61,15 @@ int cnn_dev(magpie_cnn* net) {
   return MAGPIE_OK;
 }
 
+// the thin layers' copies in wthin
+float* w_first(magpie_cnn* net) { return net->wthin; }
+float* w_head(magpie_cnn* net) { return net->wthin + (size_t)WIDTH * net->cin * 9; }
+float* w_head_t(magpie_cnn* net) { return w_head(net) + (size_t)2 * WIDTH * 9; }
+
 int prep_weights(magpie_cnn* net) {
-  for (int l = 0; l < N_LAYERS; ++l)
-    MG_HIP(cnn::launch_prep_weights(net->p + net->off_w[l], net->wf[l], net->wt[l], net->co[l], net->ci[l], net->bf16,
-                                    net->stream));
+  const cnn::PrepArgs a{net->p, {net->off_w[1], net->off_w[2], net->off_w[3]}, net->off_w[0], net->off_w[4], net->cin,
+                        net->bf16, net->fwd, net->frag, w_first(net), w_head(net), w_head_t(net), net->wbad};
+  MG_HIP(cnn::launch_prep(a, net->stream));
   return MAGPIE_OK;
 }
 
@@ -78,14 +85,15 @@ int copy_out(void* dst, const void* src, size_t bytes, int on_device, hipStream_
   return MAGPIE_OK;
 }
 
-// layer l: grad rows of the weight-gradient kernel summed into g
-int layer_wgrad(magpie_cnn* net, int l, bool up, const float* in, const float* dout, int nb, int H, int W) {
-  const int nwg = cnn::wgrad_workgroups(nb, H, W);
-  if (nwg > cnn::WGRAD_MAX_WORKGROUPS) return fail(MAGPIE_ERR_HIP, "weight-gradient partials exceed their buffer");
-  const int row = net->co[l] * net->ci[l] * 9 + net->co[l];
-  MG_HIP(cnn::launch_wgrad(up, in, dout, net->part, nb, net->ci[l], net->co[l], H, W, net->stream));
-  MG_HIP(cnn::launch_rows_sum(net->part, nwg, row, net->g + net->off_w[l], net->stream));
-  return MAGPIE_OK;
+// square layer l (1 .. 3), forward and backward-data
+hipError_t conv_forward(magpie_cnn* net, int l, bool up, const float* in, float* out, int nb, int side) {
+  return cnn::launch_conv32(up, in, net->fwd + (size_t)(l - 1) * cnn::FWD_VECS, net->p + net->off_b[l], out, nb, side,
+                            side, net->stream);
+}
+hipError_t conv_backward(magpie_cnn* net, int l, bool up, const float* dout, float* din, const float* omask, int nb,
+                         int side) {
+  return cnn::launch_conv32_backward(up, net->bf16, dout, net->frag + (size_t)(l - 1) * cnn::FRAG_VECS,
+                                     net->p + net->off_w[l], din, omask, net->wbad, nb, side, side, net->stream);
 }
 
 bool pow2(int f) { return f >= 1 && (f & (f - 1)) == 0; }
@@ -189,16 +197,14 @@ int magpie_cnn_create(magpie_cnn** out, int in_ch, int width, int side, int max_
   }
   const size_t B = (size_t)max_batch, S = side, S2 = 2 * (size_t)side;
   const size_t lo = B * WIDTH * S * S, hi = B * WIDTH * S2 * S2;
-  const size_t wsz = net->bf16 ? sizeof(uint16_t) : sizeof(float);
   rc = dev_alloc(&net->p, (size_t)net->n);
   if (!rc) rc = dev_alloc(&net->g, (size_t)net->n);
   if (!rc) rc = dev_alloc(&net->m, (size_t)net->n);
   if (!rc) rc = dev_alloc(&net->v, (size_t)net->n);
-  for (int l = 0; l < N_LAYERS && !rc; ++l) {
-    const size_t cnt = (size_t)net->co[l] * net->ci[l] * 9 * wsz;
-    rc = dev_alloc((char**)&net->wf[l], cnt);
-    if (!rc) rc = dev_alloc((char**)&net->wt[l], cnt);
-  }
+  if (!rc) rc = dev_alloc(&net->fwd, (size_t)3 * cnn::FWD_VECS);
+  if (!rc) rc = dev_alloc(&net->frag, (size_t)3 * cnn::FRAG_VECS);
+  if (!rc) rc = dev_alloc(&net->wthin, (size_t)(WIDTH * in_ch * 9 + 2 * 2 * WIDTH * 9));
+  if (!rc) rc = dev_alloc(&net->wbad, 1);
   if (!rc) rc = dev_alloc(&net->x, B * in_ch * S * S);
   if (!rc) rc = dev_alloc(&net->a1, lo);
   if (!rc) rc = dev_alloc(&net->a2, lo);
@@ -210,7 +216,7 @@ int magpie_cnn_create(magpie_cnn** out, int in_ch, int width, int side, int max_
   if (!rc) rc = dev_alloc(&net->f1, hi);
   if (!rc) rc = dev_alloc(&net->y, B * 2 * S2 * S2);
   if (!rc) rc = dev_alloc(&net->dy, B * 2 * S2 * S2);
-  if (!rc) rc = dev_alloc(&net->part, (size_t)cnn::WGRAD_MAX_WORKGROUPS * (WIDTH * WIDTH * 9 + WIDTH));
+  if (!rc) rc = dev_alloc(&net->part, (size_t)cnn::WGRAD_MAX_WORKGROUPS * cnn::SQ_ROW);
   if (!rc) rc = dev_alloc(&net->lpart, (size_t)cnn::cmse_blocks(max_batch, (int)(S2 * S2)));
   if (!rc) rc = dev_alloc(&net->lsum, 1);
   if (!rc) rc = dev_alloc(&net->tgt, B * S2 * S2);
@@ -246,10 +252,10 @@ int magpie_cnn_destroy(magpie_cnn* net) {
   dev_free(net->g);
   dev_free(net->m);
   dev_free(net->v);
-  for (int l = 0; l < N_LAYERS; ++l) {
-    dev_free(net->wf[l]);
-    dev_free(net->wt[l]);
-  }
+  dev_free(net->fwd);
+  dev_free(net->frag);
+  dev_free(net->wthin);
+  dev_free(net->wbad);
   dev_free(net->x);
   dev_free(net->a1);
   dev_free(net->a2);
@@ -318,17 +324,11 @@ int magpie_cnn_forward(magpie_cnn* net, const float* x, float* y, int nbatch, in
   hipStream_t s = net->stream;
   rc = copy_in(net->x, x, (size_t)nbatch * net->cin * S * S * sizeof(float), on_device, s);
   if (rc) return rc;
-  const bool bf = net->bf16;
-  MG_HIP(cnn::launch_conv(WIDTH, false, 0, bf, net->x, net->wf[0], net->p + net->off_b[0], net->a1, nullptr, nbatch,
-                          net->cin, S, S, s));
-  MG_HIP(cnn::launch_conv(WIDTH, false, 0, bf, net->a1, net->wf[1], net->p + net->off_b[1], net->a2, nullptr, nbatch,
-                          WIDTH, S, S, s));
-  MG_HIP(cnn::launch_conv(WIDTH, true, 0, bf, net->a2, net->wf[2], net->p + net->off_b[2], net->a3, nullptr, nbatch,
-                          WIDTH, S2, S2, s));
-  MG_HIP(cnn::launch_conv(WIDTH, false, 0, bf, net->a3, net->wf[3], net->p + net->off_b[3], net->a4, nullptr, nbatch,
-                          WIDTH, S2, S2, s));
-  MG_HIP(cnn::launch_conv(2, false, 1, bf, net->a4, net->wf[4], net->p + net->off_b[4], net->y, nullptr, nbatch,
-                          WIDTH, S2, S2, s));
+  MG_HIP(cnn::launch_conv_first(net->cin, net->x, w_first(net), net->p + net->off_b[0], net->a1, nbatch, S, S, s));
+  MG_HIP(conv_forward(net, 1, false, net->a1, net->a2, nbatch, S));
+  MG_HIP(conv_forward(net, 2, true, net->a2, net->a3, nbatch, S2));
+  MG_HIP(conv_forward(net, 3, false, net->a3, net->a4, nbatch, S2));
+  MG_HIP(cnn::launch_conv_head(net->a4, w_head(net), net->p + net->off_b[4], net->y, nbatch, S2, S2, s));
   net->last_batch = nbatch;
   net->have_dy = false;
   if (y) return copy_out(y, net->y, (size_t)nbatch * 2 * S2 * S2 * sizeof(float), on_device, s);
@@ -379,26 +379,20 @@ int magpie_cnn_backward(magpie_cnn* net, const float* dy, int nbatch, int on_dev
     rc = copy_in(net->dy, dy, (size_t)nb * 2 * S2 * S2 * sizeof(float), on_device, s);
     if (rc) return rc;
   }
-  const bool bf = net->bf16;
-  // layer 5: dy -> dW5, dp4 = (W5^T * dy) on a4 > 0
-  rc = layer_wgrad(net, 4, false, net->a4, net->dy, nb, S2, S2);
-  if (rc) return rc;
-  MG_HIP(cnn::launch_conv(WIDTH, false, 2, bf, net->dy, net->wt[4], nullptr, net->f0, net->a4, nb, 2, S2, S2, s));
-  // layer 4
-  rc = layer_wgrad(net, 3, false, net->a3, net->f0, nb, S2, S2);
-  if (rc) return rc;
-  MG_HIP(cnn::launch_conv(WIDTH, false, 2, bf, net->f0, net->wt[3], nullptr, net->f1, net->a3, nb, WIDTH, S2, S2, s));
-  // layer 3 (input read through the upsampling)
-  rc = layer_wgrad(net, 2, true, net->a2, net->f1, nb, S2, S2);
-  if (rc) return rc;
-  MG_HIP(cnn::launch_conv(WIDTH, false, 3, bf, net->f1, net->wt[2], nullptr, net->f0, nullptr, nb, WIDTH, S2, S2, s));
-  MG_HIP(cnn::launch_up_backward_mask(net->f0, net->a2, net->l0, nb, WIDTH, S, S, s));
-  // layer 2
-  rc = layer_wgrad(net, 1, false, net->a1, net->l0, nb, S, S);
-  if (rc) return rc;
-  MG_HIP(cnn::launch_conv(WIDTH, false, 2, bf, net->l0, net->wt[1], nullptr, net->l1, net->a1, nb, WIDTH, S, S, s));
-  // layer 1
-  return layer_wgrad(net, 0, false, net->x, net->l1, nb, S, S);
+  float* const part = net->part;
+  auto grad = [&](int l) { return net->g + net->off_w[l]; };
+  // head: dy -> its weights, then a4's gradient where a4 > 0
+  MG_HIP(cnn::launch_wgrad_head(net->a4, net->dy, part, grad(4), nb, S2, S2, s));
+  MG_HIP(cnn::launch_conv_head_backward(net->dy, w_head_t(net), net->f0, net->a4, nb, S2, S2, s));
+  MG_HIP(cnn::launch_wgrad32(false, net->a3, net->f0, part, grad(3), nb, S2, S2, s));
+  MG_HIP(conv_backward(net, 3, false, net->f0, net->f1, net->a3, nb, S2));
+  // the layer that reads its input through the upsampling
+  MG_HIP(cnn::launch_wgrad32(true, net->a2, net->f1, part, grad(2), nb, S2, S2, s));
+  MG_HIP(conv_backward(net, 2, true, net->f1, net->l0, net->a2, nb, S2));
+  MG_HIP(cnn::launch_wgrad32(false, net->a1, net->l0, part, grad(1), nb, S, S, s));
+  MG_HIP(conv_backward(net, 1, false, net->l0, net->l1, net->a1, nb, S));
+  MG_HIP(cnn::launch_wgrad_first(net->cin, net->x, net->l1, part, grad(0), nb, S, S, s));
+  return MAGPIE_OK;
 }
 
 int magpie_cnn_adam_step(magpie_cnn* net, float lr, float beta1, float beta2, float eps) {
