@@ -64,12 +64,21 @@ hipError_t launch_wgrad_head(const float* in, const float* dy, float* part, floa
 // partials go to part (n_blocks returned by cmse_blocks).  With rot non-null
 // each sample's prediction is first rotated by its best global phase
 // (rot[b] = ip / |ip|, ip = sum mask conj(pred) t, partials in ip_part
-// [B][cmse_ip_blocks(hw)]).
+// [B][cmse_ip_blocks(hw)]).  A mask that is not finite and >= 0 (out->bad) or all zero
+// (out->msum = 0) leaves dy alone.
+struct CmseHead {
+  double msum;   // the mask's sum, 0 where it is refused
+  int bad;
+};
+struct CmseResult {
+  double loss, msum;
+  int bad;
+};
 int cmse_blocks(int batch, int hw);
 int cmse_ip_blocks(int hw);
+// out: memory the host reads after the stream is synchronised
 hipError_t launch_cmse(const float* y, const float2* target, const float* mask, float2* rot, double2* ip_part,
-                       float* dy, double* part, int batch, int hw, float inv_norm, hipStream_t s);
-hipError_t launch_sum_f64(const double* x, int n, double* out, hipStream_t s);
+                       float* dy, double* part, int batch, int hw, CmseHead* head, CmseResult* out, hipStream_t s);
 
 // Adam with bias corrections c1 = 1/(1-b1^t), c2 = 1/(1-b2^t).
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr, float b1, float b2,

@@ -57,15 +57,27 @@ __global__ __launch_bounds__(CMSE_THREADS) void cmse_ip_kernel(const float* __re
   if (threadIdx.x == 0) part[(size_t)b * gridDim.x + blockIdx.x] = make_double2(rr[0], ri[0]);
 }
 
-// rot[b] = ip / |ip| (1 where ip = 0), ip = sum of the sample's partials in order
-__global__ __launch_bounds__(256) void cmse_rot_kernel(const double2* __restrict__ part, int nblk,
-                                                       float2* __restrict__ rot) {
+// Workgroup 0: the mask's sum, and whether all its values are finite and >= 0 (a mask
+// that is not, or whose sum is 0, gives head->msum = 0).  Workgroup b + 1: rot[b] = ip / |ip|
+// (1 where ip = 0), ip = sum of the sample's partials in order.
+__global__ __launch_bounds__(256) void cmse_head_kernel(const float* __restrict__ mask, int hw,
+                                                        const double2* __restrict__ part, int nblk,
+                                                        float2* __restrict__ rot, CmseHead* __restrict__ head) {
   __shared__ double rr[256], ri[256];
-  const int b = blockIdx.x;
   double a = 0.0, c = 0.0;
-  for (int i = threadIdx.x; i < nblk; i += 256) {
-    a += part[(size_t)b * nblk + i].x;
-    c += part[(size_t)b * nblk + i].y;
+  if (blockIdx.x == 0) {
+#pragma unroll 8
+    for (int i = threadIdx.x; i < hw; i += 256) {
+      const float v = mask[i];
+      a += (double)v;
+      c += (v >= 0.0f && v <= 3.402823466e38f) ? 0.0 : 1.0;
+    }
+  } else {
+    const size_t b = blockIdx.x - 1;
+    for (int i = threadIdx.x; i < nblk; i += 256) {
+      a += part[b * nblk + i].x;
+      c += part[b * nblk + i].y;
+    }
   }
   rr[threadIdx.x] = a;
   ri[threadIdx.x] = c;
@@ -77,22 +89,29 @@ __global__ __launch_bounds__(256) void cmse_rot_kernel(const double2* __restrict
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
+  if (threadIdx.x) return;
+  if (blockIdx.x == 0) {
+    head->bad = ri[0] > 0.0 ? 1 : 0;
+    head->msum = (ri[0] > 0.0 || !(rr[0] > 0.0)) ? 0.0 : rr[0];
+  } else {
     const double n = sqrt(rr[0] * rr[0] + ri[0] * ri[0]);
-    rot[b] = n > 0.0 ? make_float2((float)(rr[0] / n), (float)(ri[0] / n)) : make_float2(1.0f, 0.0f);
+    rot[blockIdx.x - 1] = n > 0.0 ? make_float2((float)(rr[0] / n), (float)(ri[0] / n)) : make_float2(1.0f, 0.0f);
   }
 }
 
+// dy is left as it was where the mask is refused (head->msum = 0)
 __global__ __launch_bounds__(CMSE_THREADS) void cmse_kernel(const float* __restrict__ y,
                                                             const float2* __restrict__ tgt,
                                                             const float* __restrict__ mask,
                                                             const float2* __restrict__ rot, float* __restrict__ dy,
                                                             double* __restrict__ part, int batch, int hw,
-                                                            float inv_norm) {
+                                                            const CmseHead* __restrict__ head) {
   __shared__ double red[CMSE_THREADS];
   const size_t i = (size_t)blockIdx.x * CMSE_THREADS + threadIdx.x;
+  const double msum = head->msum;
+  const float inv_norm = (float)(1.0 / ((double)batch * msum));
   double l = 0.0;
-  if (i < (size_t)batch * hw) {
+  if (i < (size_t)batch * hw && msum > 0.0) {
     const size_t b = i / hw;
     const int p = (int)(i - b * hw);
     float2 pv = pred_of(y, b, p, hw);
@@ -119,17 +138,25 @@ __global__ __launch_bounds__(CMSE_THREADS) void cmse_kernel(const float* __restr
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ __launch_bounds__(256) void sum_f64_kernel(const double* __restrict__ x, int n, double* __restrict__ out) {
-  __shared__ double red[256];
+// the loss, and what the host has to know of the mask, into host memory the GPU writes
+__global__ __launch_bounds__(1024) void cmse_loss_kernel(const double* __restrict__ x, int n,
+                                                         const CmseHead* __restrict__ head, int batch,
+                                                         CmseResult* __restrict__ out) {
+  __shared__ double red[1024];
   double a = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) a += x[i];
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += 1024) a += x[i];
   red[threadIdx.x] = a;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
+  for (int s = 512; s > 0; s >>= 1) {
     if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = red[0];
+  if (threadIdx.x == 0) {
+    out->loss = red[0] * (1.0 / ((double)batch * head->msum));
+    out->msum = head->msum;
+    out->bad = head->bad;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -446,21 +473,17 @@ int cmse_blocks(int batch, int hw) { return (int)(((size_t)batch * hw + CMSE_THR
 int cmse_ip_blocks(int hw) { return (hw + CMSE_THREADS - 1) / CMSE_THREADS; }
 
 hipError_t launch_cmse(const float* y, const float2* target, const float* mask, float2* rot, double2* ip_part,
-                       float* dy, double* part, int batch, int hw, float inv_norm, hipStream_t s) {
+                       float* dy, double* part, int batch, int hw, CmseHead* head, CmseResult* out, hipStream_t s) {
   const int nb = cmse_blocks(batch, hw);
   if (nb <= 0) return hipSuccess;
-  if (rot) {
-    const int nbi = cmse_ip_blocks(hw);
+  const int nbi = cmse_ip_blocks(hw);
+  if (rot)
     hipLaunchKernelGGL(cmse_ip_kernel, dim3(nbi, batch), dim3(CMSE_THREADS), 0, s, y, target, mask, ip_part, hw);
-    hipLaunchKernelGGL(cmse_rot_kernel, dim3(batch), dim3(256), 0, s, ip_part, nbi, rot);
-  }
+  hipLaunchKernelGGL(cmse_head_kernel, dim3(rot ? batch + 1 : 1), dim3(256), 0, s, mask, hw, ip_part, nbi, rot, head);
   hipLaunchKernelGGL(cmse_kernel, dim3(nb), dim3(CMSE_THREADS), 0, s, y, target, mask, (const float2*)rot, dy, part,
-                     batch, hw, inv_norm);
-  return hipGetLastError();
-}
-
-hipError_t launch_sum_f64(const double* x, int n, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(sum_f64_kernel, dim3(1), dim3(256), 0, s, x, n, out);
+                     batch, hw, (const CmseHead*)head);
+  hipLaunchKernelGGL(cmse_loss_kernel, dim3(1), dim3(1024), 0, s, (const double*)part, nb, (const CmseHead*)head, batch,
+                     out);
   return hipGetLastError();
 }
 

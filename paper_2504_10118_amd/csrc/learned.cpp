@@ -45,7 +45,8 @@ struct magpie_cnn {
   float *f0 = nullptr, *f1 = nullptr, *l0 = nullptr, *l1 = nullptr;
   float* part = nullptr;
   double* lpart = nullptr;
-  double* lsum = nullptr;
+  cnn::CmseHead* lhead = nullptr;
+  cnn::CmseResult* lres = nullptr;   // pinned host memory the loss kernel writes
   float2* tgt = nullptr;
   float* mask = nullptr;
   float2* rot = nullptr;
@@ -218,7 +219,11 @@ int magpie_cnn_create(magpie_cnn** out, int in_ch, int width, int side, int max_
   if (!rc) rc = dev_alloc(&net->dy, B * 2 * S2 * S2);
   if (!rc) rc = dev_alloc(&net->part, (size_t)cnn::WGRAD_MAX_WORKGROUPS * cnn::SQ_ROW);
   if (!rc) rc = dev_alloc(&net->lpart, (size_t)cnn::cmse_blocks(max_batch, (int)(S2 * S2)));
-  if (!rc) rc = dev_alloc(&net->lsum, 1);
+  if (!rc) rc = dev_alloc(&net->lhead, 1);
+  if (!rc && hipHostMalloc((void**)&net->lres, sizeof(*net->lres), hipHostMallocDefault) != hipSuccess) {
+    net->lres = nullptr;
+    rc = fail(MAGPIE_ERR_OOM, "pinned host allocation failed");
+  }
   if (!rc) rc = dev_alloc(&net->tgt, B * S2 * S2);
   if (!rc) rc = dev_alloc(&net->mask, S2 * S2);
   if (!rc) rc = dev_alloc(&net->rot, B);
@@ -269,7 +274,8 @@ int magpie_cnn_destroy(magpie_cnn* net) {
   dev_free(net->l1);
   dev_free(net->part);
   dev_free(net->lpart);
-  dev_free(net->lsum);
+  dev_free(net->lhead);
+  if (net->lres) hipHostFree(net->lres);
   dev_free(net->tgt);
   dev_free(net->mask);
   dev_free(net->rot);
@@ -346,23 +352,12 @@ int magpie_cnn_loss(magpie_cnn* net, const void* target, const float* mask, int 
   rc = copy_in(net->tgt, target, (size_t)nbatch * hw * sizeof(float2), on_device, s);
   if (!rc) rc = copy_in(net->mask, mask, (size_t)hw * sizeof(float), on_device, s);
   if (rc) return rc;
-  std::vector<float> hm(hw);
-  MG_HIP(hipMemcpyAsync(hm.data(), net->mask, hw * sizeof(float), hipMemcpyDeviceToHost, s));
-  MG_HIP(hipStreamSynchronize(s));
-  double msum = 0.0;
-  for (float v : hm) {
-    if (!(v >= 0.0f) || !std::isfinite(v)) return fail(MAGPIE_ERR_INVALID_ARG, "mask must be finite and >= 0");
-    msum += v;
-  }
-  if (!(msum > 0.0)) return fail(MAGPIE_ERR_INVALID_ARG, "mask is all zero");
-  const double inv = 1.0 / ((double)nbatch * msum);
   MG_HIP(cnn::launch_cmse(net->y, net->tgt, net->mask, align_phase ? net->rot : nullptr, net->ip_part, net->dy,
-                          net->lpart, nbatch, hw, (float)inv, s));
-  MG_HIP(cnn::launch_sum_f64(net->lpart, cnn::cmse_blocks(nbatch, hw), net->lsum, s));
-  double h = 0.0;
-  MG_HIP(hipMemcpyAsync(&h, net->lsum, sizeof(double), hipMemcpyDeviceToHost, s));
+                          net->lpart, nbatch, hw, net->lhead, net->lres, s));
   MG_HIP(hipStreamSynchronize(s));
-  *loss = h * inv;
+  if (net->lres->bad) return fail(MAGPIE_ERR_INVALID_ARG, "mask must be finite and >= 0");
+  if (!(net->lres->msum > 0.0)) return fail(MAGPIE_ERR_INVALID_ARG, "mask is all zero");
+  *loss = net->lres->loss;
   net->have_dy = true;
   return std::isfinite(*loss) ? MAGPIE_OK : fail(MAGPIE_ERR_NUMERIC, "non-finite loss");
 }

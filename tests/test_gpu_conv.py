@@ -122,3 +122,27 @@ def test_infinite_output_gradient(bf16):
     fin = np.isfinite(want)
     assert 0 < fin.sum() < want.size and np.array_equal(np.sign(g[np.isinf(want)]), np.sign(want[np.isinf(want)]))
     assert np.linalg.norm(g[fin] - want[fin]) <= 2e-5 * np.linalg.norm(want[fin])
+
+
+def test_refused_mask_keeps_the_output_gradient():
+    """A loss with a refused mask fails and leaves the last valid loss's output gradient in place."""
+    from paper_2504_10118_amd import MagpieError
+    cin, side, nb = 1, 6, 2
+    p, x, rng = _problem(900, cin, side, nb)
+    t = np.exp(1j * rng.uniform(-1, 1, (nb, 2 * side, 2 * side))).astype(np.complex64)
+    mask = rng.uniform(0.5, 1.0, (2 * side, 2 * side)).astype(np.float32)
+    net = _net(cin, side, nb, 0, p)
+    net.forward(x)
+    net.loss(t, mask, align_phase=True)
+    net.backward(nbatch=nb)
+    g = net.get_grads()
+    for bad in (-1.0, np.nan, np.inf):
+        m2 = mask.copy()
+        m2[3, 4] = bad
+        with pytest.raises(MagpieError, match="finite"):
+            net.loss(t, m2, align_phase=False)
+    with pytest.raises(MagpieError, match="all zero"):
+        net.loss(t, 0 * mask)
+    net.backward(nbatch=nb)
+    assert np.array_equal(net.get_grads().view(np.uint32), g.view(np.uint32))
+    net.close()
