@@ -295,7 +295,6 @@ int magpie_destroy(magpie_ctx* c) {
   dev_free(c->epoch_ctr);
   dev_free(c->stage);
   dev_free(c->pnum);
-  dev_free(c->pden);
   dev_free(c->pmax);
   dev_free(c->pacc);
   dev_free(c->posrec);
@@ -507,8 +506,7 @@ static int ensure_epoch_buffers(magpie_ctx* c, int n_epochs, int batch, size_t r
     dev_free(c->stage);
     // the probe-step partials are sized with the staging: reallocated on next use
     dev_free(c->pnum);
-    dev_free(c->pden);
-    dev_free(c->pmax);
+      dev_free(c->pmax);
     dev_free(c->pacc);
     c->pcap = 0;
     rc = dev_alloc(&c->stage, need_stage);
@@ -523,11 +521,9 @@ static int ensure_epoch_buffers(magpie_ctx* c, int n_epochs, int batch, size_t r
     MG_HIP(hipStreamSynchronize(c->stream));
     drop_graph(c);
     dev_free(c->pnum);
-    dev_free(c->pden);
-    dev_free(c->pmax);
+      dev_free(c->pmax);
     dev_free(c->pacc);
     rc = dev_alloc(&c->pnum, need_stage);
-    if (!rc) rc = dev_alloc(&c->pden, need_stage);
     if (!rc) rc = dev_alloc(&c->pmax, (size_t)B * mg::MAX_WAVES);
     if (!rc) rc = dev_alloc(&c->pacc, mg::probe_scratch_doubles(m, B));
     if (rc) {
@@ -726,7 +722,6 @@ int mgrt::launch_epochs(magpie_ctx* c, int n_epochs, int B, int batches_per_epoc
   sa.stage_wt = (B <= c->n_cu) ? 1 : 0;
   if (probe_step) {
     sa.probe_num = c->pnum;
-    sa.probe_den = c->pden;
     sa.probe_max = c->pmax;
   }
   // Alternating probe step: after the minibatch's object update a second pass of
@@ -737,24 +732,26 @@ int mgrt::launch_epochs(magpie_ctx* c, int n_epochs, int B, int batches_per_epoc
   mg::StepArgs sp = sa;
   if (alternate) {
     sa.probe_num = nullptr;
-    sa.probe_den = nullptr;
     sa.probe_max = nullptr;
     sp.phi_part = nullptr;
     sp.phase = nullptr;
   }
+  const int nw = mg::step_waves(m, c->rb);
   auto probe_pass = [&]() -> hipError_t {
     sp.pos = sa.pos;
     sp.posx = sa.posx;
     sp.count = sa.count;
     sp.epoch = sa.epoch;
     sp.epoch_stride = sa.epoch_stride;
-    return mg::launch_step(m, c->rb, mg::MODE_STEP, sp, c->stream);
+    const hipError_t e = mg::launch_step(m, c->rb, mg::MODE_STEP, sp, c->stream);
+    return e != hipSuccess ? e : mg::launch_probe_partial(m, sp, nw, c->pacc, c->stream);
   };
-  const int nw = mg::step_waves(m, c->rb);
+  // the simultaneous step's partial sums, before the accumulation changes the object
+  const bool simultaneous = probe_step && !alternate;
+  auto probe_sums = [&]() { return mg::launch_probe_partial(m, sa, nw, c->pacc, c->stream); };
   // probe step after a minibatch's accumulation: apply, then rebuild the hierarchy
   auto probe_tail = [&](int count) -> hipError_t {
-    hipError_t e =
-        mg::launch_probe_apply(m, count, nw, c->pnum, c->pden, c->pmax, c->beta, c->q64, c->pacc, c->stream);
+    hipError_t e = mg::launch_probe_apply(m, count, c->beta, c->q64, c->pacc, c->stream);
     if (e == hipSuccess)
       e = mg::launch_level_constants(c->m, c->L, c->alpha, c->u_given ? 1 : 0, c->q64, c->u0, c->w0, c->w0f,
                                      c->u0f, c->qf, c->lvl, c->lvl_a_off, c->scr_q, c->scr_u, c->rb, c->qtab,
@@ -798,6 +795,7 @@ int mgrt::launch_epochs(magpie_ctx* c, int n_epochs, int B, int batches_per_epoc
         sa.pos = buf.posrec + (size_t)t * B;
         sa.count = std::min(B, N - t * B);
         ce = mg::launch_step(m, c->rb, mg::MODE_STEP, sa, c->stream);
+        if (ce == hipSuccess && simultaneous) ce = probe_sums();
         aa.batch_index = t;
         aa.pos = scan ? sa.pos : nullptr;
         aa.count = sa.count;
@@ -835,6 +833,7 @@ int mgrt::launch_epochs(magpie_ctx* c, int n_epochs, int B, int batches_per_epoc
       int ti = timed_slot(c, 0, sa.count);
       MG_HIP(mg::launch_step(m, c->rb, mg::MODE_STEP, sa, c->stream, ti >= 0 ? c->timed[ti].a : nullptr,
                              ti >= 0 ? c->timed[ti].b : nullptr));
+      if (simultaneous) MG_HIP(probe_sums());
       aa.inv = buf.inv + (size_t)e * N;
       aa.batch_index = t;
       aa.pos = scan ? sa.pos : nullptr;

@@ -129,8 +129,7 @@ struct magpie_ctx {
   size_t stage_cap = 0;  // in float2
   float2* phase = nullptr;  // eq. (3.2) phase store [n_pos][m][m], natural order (flag MAGPIE_PHASE_RECYCLE)
   size_t phase_cap = 0;     // in float2
-  float2* pnum = nullptr;   // probe step partials (allocated with the staging when the flag is on)
-  float* pden = nullptr;
+  float2* pnum = nullptr;   // probe step differences (allocated with the staging when the flag is on)
   float* pmax = nullptr;
   double* pacc = nullptr;   // probe step: per-chunk partial sums (mg::probe_scratch_doubles)
   size_t pcap = 0;

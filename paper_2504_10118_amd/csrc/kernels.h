@@ -54,8 +54,7 @@ struct StepArgs {
   double* phi_part;       // per-wave partials of Phi_k [N][MAX_WAVES] (nullable)
   double* gn_part;        // MODE_OBJECTIVE: per-wave partials of ||grad_k||^2 [N][MAX_WAVES]
   float* d_out;           // MODE_FORWARD: |F(Q z_k)|^2 natural order [N][m][m]
-  float2* probe_num;      // probe step: conj(z_k)(R_k - Q z_k) per position [count][m][m] (nullable)
-  float* probe_den;       // probe step: |z_k|^2 per position [count][m][m]
+  float2* probe_num;      // probe step: Q z_k - R_k per position [count][m][m] (nullable)
   float* probe_max;       // probe step: per-wave max |z_k|^2 [count][MAX_WAVES]
   float2* phase;          // MODE_STEP, nullable: eq. (3.2) phase store [N][m][m] natural order
   int stage_wt;           // MODE_STEP: store the staged updates with device scope (written through
@@ -168,8 +167,10 @@ inline size_t probe_scratch_doubles(int m, int max_count) {
   const size_t chunks = (size_t)(max_count + PROBE_CHUNK - 1) / PROBE_CHUNK;
   return chunks * ((size_t)3 * m * m + 1);
 }
-hipError_t launch_probe_apply(int m, int count, int nwaves, const float2* num, const float* den,
-                              const float* pmax, double beta, double2* q64, double* scratch, hipStream_t s);
+// Pass 1 reads the object a.z at the windows of a's records (a: the arguments of the
+// step launch that stored the differences), so the object must be the one that launch read.
+hipError_t launch_probe_partial(int m, const StepArgs& a, int nwaves, double* scratch, hipStream_t s);
+hipError_t launch_probe_apply(int m, int count, double beta, double2* q64, const double* scratch, hipStream_t s);
 hipError_t launch_convert_c64_c128(const float2* src, double2* dst, size_t n, hipStream_t s);
 hipError_t launch_convert_c128_c64(const double2* src, float2* dst, size_t n, hipStream_t s);
 hipError_t launch_check_finite_c64(const float2* src, size_t n, int* bad_flag, hipStream_t s);

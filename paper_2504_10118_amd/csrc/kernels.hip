@@ -164,7 +164,6 @@ __device__ __forceinline__ StepArgs load_step_args(const StepArgs* p) {
   a.gn_part = d->gn_part;
   a.d_out = d->d_out;
   a.probe_num = d->probe_num;
-  a.probe_den = d->probe_den;
   a.probe_max = d->probe_max;
   a.phase = nullptr;   // multi-context runs do not recycle phases
   a.stage_wt = 0;      // ... and stage through L2 (their launches are large)
@@ -560,11 +559,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
 
   // ---- gather z_k, exit wave Q * z_k: thread (x = col, g) holds rows y = RB*n1 + g
   float2 v[RA];
-  // patch rows y = RB*n1 + g: per-lane byte offset (g, col), per-row scalar offset n1
   const float2* zbase = a.z + (size_t)off.x * a.n_cols + off.y;
   const rsrc_t zr = make_rsrc(zbase, (unsigned)(((size_t)(a.n_rows - off.x) * a.n_cols - off.y) * sizeof(float2)));
-  const int zvo = (g * a.n_cols + col) * (int)sizeof(float2);
-  const int zso = RB * a.n_cols * (int)sizeof(float2);
   constexpr int ZPOL = COH ? kPolicyDeviceScope : 0;
   constexpr int qso = RB * M * (int)sizeof(float2);
   const float4* qt = a.qtab + tid;   // [n1][tid]: each load reads one contiguous block
@@ -676,6 +672,19 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
     if constexpr (KEEP) {
       qk[n1] = qv;
       u0k[n1] = uv;
+    }
+  }
+  if constexpr (STEPM) {
+    if (a.probe_num) {
+      // probe step: this position's largest |z_k|^2, taken while the patch is in the tile
+      float pmx = 0.0f;
+#pragma unroll
+      for (int n1 = 0; n1 < RA; ++n1) {
+        const float2 zz = T[(RB * n1 + g) * P + col];
+        pmx = fmaxf(pmx, zz.x * zz.x + zz.y * zz.y);
+      }
+      const float wm = wave_max<LANES, XV>(pmx);
+      if ((tid & 63) == 0) a.probe_max[(size_t)slot * MAX_WAVES + wave] = wm;
     }
   }
   wave_sync();   // the column pass below reuses this wave's own column slice of the tile
@@ -862,7 +871,6 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
 
     // ---- gradient g0 = conj(Q) (Q z_k - R_k) (eq. 2.2): v / M^2 is Q z_k - R_k
     constexpr float inv_m2 = 1.0f / (float)(M * M);
-    float pmx = 0.0f;
 #pragma unroll
     for (int n1 = 0; n1 < RA; ++n1) {
       float2 qq;
@@ -870,25 +878,10 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
       else qq = qt2[n1 * TPB];
       const float2 dk = cscale(v[n1], inv_m2);
       if constexpr (STEPM) {
-        if (a.probe_num) {
-          // probe step partials: conj(z_k)(R_k - Q z_k) and |z_k|^2 (the patch
-          // is read again for them, at the column stride)
-          const float2 zz = bload2p<ZPOL>(zr, zvo, n1 * zso);
-          const float2 pn = cmulc(zz, make_float2(-dk.x, -dk.y));
-          const float pd = zz.x * zz.x + zz.y * zz.y;
-          const size_t e = (size_t)slot * M * M + (size_t)(RB * n1 + g) * M + col;
-          a.probe_num[e] = pn;
-          a.probe_den[e] = pd;
-          pmx = fmaxf(pmx, pd);
-        }
+        // probe step: Q z_k - R_k; probe_partial_kernel forms its products with the window
+        if (a.probe_num) a.probe_num[(size_t)slot * M * M + (size_t)(RB * n1 + g) * M + col] = dk;
       }
       v[n1] = cmulc(qq, dk);
-    }
-    if constexpr (STEPM) {
-      if (a.probe_num) {
-        const float wm = wave_max<LANES, XV>(pmx);
-        if ((tid & 63) == 0) a.probe_max[(size_t)slot * MAX_WAVES + wave] = wm;
-      }
     }
 
     if constexpr (MODE == MODE_OBJECTIVE) {
@@ -1507,66 +1500,159 @@ hipError_t launch_accumulate(const AccumArgs& a, int th, int n_tiles, hipStream_
 }
 
 // ---------------------------------------------------------------------------
-// Probe hierarchy in FP64 (eq. 4.4, Alg 3 coarse-level preparation).  One
-// workgroup.  Level 0: u0 (u^rPIE unless given), w0 = u0 + |Q|^2, FP32 copies.
-// Level l >= 1 from level l-1 on 2x2 bins: Q_l = I Q, S = I |Q|^2,
-// u^ = I u, w^ = I w, V = |Q_l|^2 / S (0 where S = 0), u_l = V u^;
-// rho = u^ / w^, r = 1 / w^ where V > 0 and w^ > 0, else rho = 1, r = 0.
+// Probe hierarchy in FP64 (eq. 4.4, Alg 3 coarse-level preparation), the plan's probe
+// table, and the rows of the probe's spectrum, in one launch.  Level 0: u0 (u^rPIE
+// unless given), w0 = u0 + |Q|^2, FP32 copies.  Level l >= 1 from level l-1 on 2x2
+// bins: Q_l = I Q, S = I |Q|^2, u^ = I u, w^ = I w, V = |Q_l|^2 / S (0 where S = 0),
+// u_l = V u^; rho = u^ / w^, r = 1 / w^ where V > 0 and w^ > 0, else rho = 1, r = 0.
 // Output per level: V [Ml^2], rho [Ml^2], r [Ml^2].
+//
+// Only max |Q|^2 couples the pixels beyond their coarsest bin, so the probe is cut into
+// regions of side `region` (a multiple of the coarsest bin, at least 16), one workgroup
+// each, which take the maximum themselves and then go through their levels alone; every
+// level has its own part of the scratch.  (One workgroup over the whole probe: 11.0 us at
+// m = 64 with three grids, and a launch of its own for the table, 4.7 us.)
+// The remaining m workgroups transform one probe row each (see below).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void level_constants_kernel(int m, int levels, double alpha, int u_given,
-                                                               const double2* q64, double* u0, double* w0,
-                                                               float* w0f, float* u0f, float2* qf, double* lvl,
-                                                               int a_off, double2* scr_q, double* scr_u) {
-  __shared__ double red[1024];
-  const int tid = threadIdx.x;
-  const int n0 = m * m;
+struct LevelArgs {
+  int m, levels, region, n_regions;
+  double alpha;
+  int u_given;
+  const double2* q64;
+  double *u0, *w0;
+  float *w0f, *u0f;
+  float2* qf;
+  double* lvl;
+  int a_off;
+  double2* scr_q;
+  double* scr_u;
+  int rb, keep;       // FFT plan: threads per transform; keep: table of (Re Q, Im Q, u0, 0) entries
+  float4* qtab;
+  double2* spec_tmp;
+};
+
+// The probe table entry of pixel (y, x) in the thread order of plan (m, rb): entry
+// [n1][tid] belongs to thread tid = g + rb*col at pixel (rb*n1 + g, col), so each of the
+// step kernel's loads of this table reads one contiguous block.
+__device__ __forceinline__ void store_qtab(const LevelArgs& a, int y, int x, float2 q, float u) {
+  const int g = y & (a.rb - 1), n1 = y / a.rb, e = n1 * (a.m * a.rb) + g + a.rb * x;
+  if (a.keep) {
+    a.qtab[e] = make_float4(q.x, q.y, u, 0.0f);
+  } else {
+    float2* q2 = reinterpret_cast<float2*>(a.qtab);
+    q2[e] = q;
+    reinterpret_cast<float*>(q2 + a.m * a.m)[e] = u;
+  }
+}
+
+// exp(-2 pi i j / m) for j < m (exact arguments) into LDS
+__device__ __forceinline__ void spectrum_twiddles(double2* W, int m) {
+  for (int j = threadIdx.x; j < m; j += blockDim.x) {
+    double sn, cs;
+    sincospi(-2.0 * (double)j / (double)m, &sn, &cs);
+    W[j] = make_double2(cs, sn);
+  }
+}
+
+// Probe spectrum F(Q) of the FP32 probe in FP64 (a direct DFT along each axis, exact
+// twiddles from sincospi of the reduced exponent), rounded to FP32 once.
+// Values within the DFT's own rounding bound, 2 m eps sum |Q| (doubled here), are
+// set to exactly zero: a symmetric probe's spectrum vanishes exactly on whole
+// lines, where the modulus replacement takes theta(0), and the sums leave there
+// only rounding (below 1e-16 sum |Q|, against 1e-8 sum |Q| for the smallest value
+// that does not vanish, with the 128 x 128 test probe).
+// Row y: A[y][kx] = sum_x Q[y][x] W^(kx x), twiddles from a table of m (evaluating them
+// per term made the two passes 19 and 16 us at m = 64); the row's sum |Q[y][x]| goes to
+// tmp[m * m + y].x.
+__device__ void spectrum_row(const LevelArgs& a, int y) {
+  __shared__ double2 W[128], v[128];
+  __shared__ double l1[128];
+  const int m = a.m, t = threadIdx.x;
+  spectrum_twiddles(W, m);
+  if (t < m) {
+    const double2 q = a.q64[y * m + t];
+    const float2 f = make_float2((float)q.x, (float)q.y);
+    v[t] = make_double2((double)f.x, (double)f.y);
+    l1[t] = hypot(v[t].x, v[t].y);
+  }
+  __syncthreads();
+  for (int s = m >> 1; s > 0; s >>= 1) {
+    if (t < s) l1[t] += l1[t + s];
+    __syncthreads();
+  }
+  if (t == 0) a.spec_tmp[m * m + y] = make_double2(l1[0], 0.0);
+  if (t >= m) return;
+  double re = 0.0, im = 0.0;
+  int k = 0;
+#pragma unroll 4
+  for (int x = 0; x < m; ++x) {
+    const double2 w = W[k], q = v[x];
+    re += q.x * w.x - q.y * w.y;
+    im += q.x * w.y + q.y * w.x;
+    k = (k + t) & (m - 1);
+  }
+  a.spec_tmp[y * m + t] = make_double2(re, im);
+}
+
+__global__ __launch_bounds__(256) void level_constants_kernel(LevelArgs a) {
+  __shared__ double red[256];
+  const int tid = threadIdx.x, m = a.m, levels = a.levels;
+  if ((int)blockIdx.x >= a.n_regions) {
+    spectrum_row(a, blockIdx.x - a.n_regions);
+    return;
+  }
   double mx = 0.0;
-  for (int e = tid; e < n0; e += blockDim.x) {
-    const double2 q = q64[e];
+#pragma unroll 8
+  for (int e = tid; e < m * m; e += 256) {
+    const double2 q = a.q64[e];
     mx = fmax(mx, q.x * q.x + q.y * q.y);
   }
   red[tid] = mx;
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
+  for (int s = 128; s > 0; s >>= 1) {
     if (tid < s) red[tid] = fmax(red[tid], red[tid + s]);
     __syncthreads();
   }
   const double amax = red[0];
-  for (int e = tid; e < n0; e += blockDim.x) {
-    const double2 q = q64[e];
+  const int R = a.region, per = m / R, ry = (blockIdx.x / per) * R, rx = (blockIdx.x % per) * R;
+  for (int i = tid; i < R * R; i += 256) {
+    const int y = ry + i / R, x = rx + i % R, e = y * m + x;
+    const double2 q = a.q64[e];
     const double a2 = q.x * q.x + q.y * q.y;
-    const double uu = u_given ? u0[e] : alpha * (amax - a2);
-    u0[e] = uu;
-    w0[e] = uu + a2;
-    w0f[e] = (float)(uu + a2);
-    u0f[e] = (float)uu;
-    qf[e] = make_float2((float)q.x, (float)q.y);
+    const double uu = a.u_given ? a.u0[e] : a.alpha * (amax - a2);
+    a.u0[e] = uu;
+    a.w0[e] = uu + a2;
+    a.w0f[e] = (float)(uu + a2);
+    a.u0f[e] = (float)uu;
+    const float2 qf = make_float2((float)q.x, (float)q.y);
+    a.qf[e] = qf;
+    store_qtab(a, y, x, qf, (float)uu);
   }
   __syncthreads();
-  const double2* Qp = q64;
-  const double* Up = u0;
-  double2* Qn = scr_q;
-  double* Un = scr_u;
-  int Mp = m;
-  int lv = 0;
+  const double2* Qp = a.q64;
+  const double* Up = a.u0;
+  double2* Qn = a.scr_q;
+  double* Un = a.scr_u;
+  int Mp = m, lv = 0;
   for (int l = 1; l < levels; ++l) {
-    const int Ml = Mp >> 1;
-    double* V = lvl + lv;
+    const int Ml = Mp >> 1, Rl = R >> l, Y0 = ry >> l, X0 = rx >> l;
+    double* V = a.lvl + lv;
     double* rho = V + Ml * Ml;
     double* r = V + 2 * Ml * Ml;
-    for (int e = tid; e < Ml * Ml; e += blockDim.x) {
-      const int Y = e / Ml, X = e % Ml;
+    for (int i = tid; i < Rl * Rl; i += 256) {
+      const int Y = Y0 + i / Rl, X = X0 + i % Rl, e = Y * Ml + X;
       double2 qs = make_double2(0.0, 0.0);
       double S = 0.0, U = 0.0;
+#pragma unroll
       for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
         for (int dx = 0; dx < 2; ++dx) {
-          const int i = (2 * Y + dy) * Mp + 2 * X + dx;
-          const double2 q = Qp[i];
+          const int j = (2 * Y + dy) * Mp + 2 * X + dx;
+          const double2 q = Qp[j];
           qs.x += q.x;
           qs.y += q.y;
           S += q.x * q.x + q.y * q.y;
-          U += Up[i];
+          U += Up[j];
         }
       qs.x *= 0.25;
       qs.y *= 0.25;
@@ -1583,11 +1669,10 @@ __global__ __launch_bounds__(1024) void level_constants_kernel(int m, int levels
       Un[e] = Vv * U;
     }
     __syncthreads();
-    // next level reads Qn/Un; ping-pong between the two halves of the scratch
     Qp = Qn;
     Up = Un;
-    Qn = (Qn == scr_q) ? scr_q + (m / 2) * (m / 2) : scr_q;
-    Un = (Un == scr_u) ? scr_u + (m / 2) * (m / 2) : scr_u;
+    Qn += Ml * Ml;
+    Un += Ml * Ml;
     lv += 3 * Ml * Ml;
     Mp = Ml;
   }
@@ -1596,12 +1681,13 @@ __global__ __launch_bounds__(1024) void level_constants_kernel(int m, int levels
   // in-wave V-cycle's block: A_1..A_{L-1}, then copies of V_1..V_{L-2}, every
   // grid row padded to side + CST_PAD doubles (pads zero), all stored times 1/4
   // (the in-wave V-cycle multiplies them with the sums of 2 x 2 bins, not the means).
-  __syncthreads();
+  // The pads of a row belong to its last region.
   if (levels > 1) {
-    const int M1 = m / 2, S1 = M1 + CST_PAD;
-    double* A = lvl + a_off;
-    for (int e = tid; e < M1 * S1; e += blockDim.x) {
-      const int Y1 = e / S1, X1 = e % S1;
+    const int M1 = m / 2, S1 = M1 + CST_PAD, R1 = R / 2;
+    const int wide = R1 + (rx + R == m ? CST_PAD : 0);
+    double* A = a.lvl + a.a_off;
+    for (int i = tid; i < R1 * wide; i += 256) {
+      const int Y1 = ry / 2 + i / wide, X1 = rx / 2 + i % wide, e = Y1 * S1 + X1;
       double prod = 1.0;
       int off = 0;
       for (int l = 1; l < levels; ++l) {
@@ -1609,8 +1695,8 @@ __global__ __launch_bounds__(1024) void level_constants_kernel(int m, int levels
         double val = 0.0;
         if (X1 < M1) {
           const int idx = (Y1 >> (l - 1)) * Ml + (X1 >> (l - 1));
-          const double rho = lvl[off + Ml * Ml + idx];
-          const double r = lvl[off + 2 * Ml * Ml + idx];
+          const double rho = a.lvl[off + Ml * Ml + idx];
+          const double r = a.lvl[off + 2 * Ml * Ml + idx];
           val = -r * prod;
           prod *= rho;
         }
@@ -1618,13 +1704,13 @@ __global__ __launch_bounds__(1024) void level_constants_kernel(int m, int levels
         off += 3 * Ml * Ml;
       }
     }
-    double* Vc = lvl + a_off + cst_v_off(m, levels, 1);
+    double* Vc = a.lvl + a.a_off + cst_v_off(m, levels, 1);
     int off = 0;
     for (int l = 1; l <= levels - 2; ++l) {
-      const int Ml = m >> l, Sl = Ml + CST_PAD;
-      for (int e = tid; e < Ml * Sl; e += blockDim.x) {
-        const int Y = e / Sl, X = e % Sl;
-        Vc[e] = X < Ml ? 0.25 * lvl[off + Y * Ml + X] : 0.0;
+      const int Ml = m >> l, Sl = Ml + CST_PAD, Rl = R >> l, wl = Rl + (rx + R == m ? CST_PAD : 0);
+      for (int i = tid; i < Rl * wl; i += 256) {
+        const int Y = (ry >> l) + i / wl, X = (rx >> l) + i % wl;
+        Vc[Y * Sl + X] = X < Ml ? 0.25 * a.lvl[off + Y * Ml + X] : 0.0;
       }
       Vc += Ml * Sl;
       off += 3 * Ml * Ml;
@@ -1632,66 +1718,31 @@ __global__ __launch_bounds__(1024) void level_constants_kernel(int m, int levels
   }
 }
 
-// (Re Q, Im Q, u0, 0) per pixel in the thread order of plan (M, RB): entry
-// [n1][tid] belongs to thread tid = g + RB*col at pixel (RB*n1 + g, col), so
-// each of the step kernel's loads of this table reads one contiguous block.
+// Columns of the spectrum, written in the plan's spectral thread order: entry
+// e = j * TPB + tid holds F[ky][kx] with ky = tid / RB, kx = (tid % RB) * CB + j / RB +
+// RA * (j % RB).
 template <int M, int RB>
-__global__ void qtab_kernel(const float2* qf, const float* u0f, float4* qtab) {
-  constexpr int TPB = M * RB;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= M * M) return;
-  const int n1 = e / TPB, tid = e - n1 * TPB, g = tid & (RB - 1), col = tid / RB;
-  const int i = (RB * n1 + g) * M + col;
-  const float2 q = qf[i];
-  if constexpr (keeps_table(M)) {
-    qtab[e] = make_float4(q.x, q.y, u0f[i], 0.0f);
-  } else {
-    float2* q2 = reinterpret_cast<float2*>(qtab);
-    q2[e] = q;
-    reinterpret_cast<float*>(q2 + M * M)[e] = u0f[i];
-  }
-}
-
-// Probe spectrum F(Q) of the FP32 probe in FP64 (a direct DFT along each axis,
-// exact twiddles from sincospi of the reduced exponent), rounded to FP32 once.
-// Values within the DFT's own rounding bound, 2 m eps sum |Q| (doubled here), are
-// set to exactly zero: a symmetric probe's spectrum vanishes exactly on whole
-// lines, where the modulus replacement takes theta(0), and the sums leave there
-// only rounding (below 1e-16 sum |Q|, against 1e-8 sum |Q| for the smallest value
-// that does not vanish, with the 128 x 128 test probe).
-// Rows: one workgroup per row y, thread kx: A[y][kx] = sum_x Q[y][x] W^(kx x);
-// the row's sum |Q[y][x]| goes to tmp[m * m + y].x.
-__global__ void probe_spectrum_rows_kernel(int m, const float2* __restrict__ qf, double2* __restrict__ tmp) {
-  const int y = blockIdx.x, kx = threadIdx.x;
-  double re = 0.0, im = 0.0, l1 = 0.0;
-  for (int x = 0; x < m; ++x) {
-    double sn, cs;
-    sincospi(-2.0 * (double)((kx * x) % m) / (double)m, &sn, &cs);
-    const float2 q = qf[y * m + x];
-    re += (double)q.x * cs - (double)q.y * sn;
-    im += (double)q.x * sn + (double)q.y * cs;
-    l1 += hypot((double)q.x, (double)q.y);
-  }
-  tmp[y * m + kx] = make_double2(re, im);
-  if (kx == 0) tmp[m * m + y] = make_double2(l1, 0.0);
-}
-// Columns, written in the plan's spectral thread order: entry e = j * TPB + tid
-// holds F[ky][kx] with ky = tid / RB, kx = (tid % RB) * CB + j / RB + RA * (j % RB).
-template <int M, int RB>
-__global__ void probe_spectrum_cols_kernel(const double2* __restrict__ tmp, float2* __restrict__ qspec) {
+__global__ __launch_bounds__(256) void probe_spectrum_cols_kernel(const double2* __restrict__ tmp,
+                                                                  float2* __restrict__ qspec) {
   constexpr int TPB = M * RB, RA = M / RB, CB = RA / RB;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  __shared__ double2 W[M];
+  __shared__ double l1s[M];
+  spectrum_twiddles(W, M);
+  if ((int)threadIdx.x < M) l1s[threadIdx.x] = tmp[M * M + threadIdx.x].x;
+  __syncthreads();
+  const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= M * M) return;
   const int j = e / TPB, tid = e - j * TPB;
   const int ky = tid / RB, kx = (tid % RB) * CB + j / RB + RA * (j % RB);
   double re = 0.0, im = 0.0, l1 = 0.0;
+  int k = 0;
+#pragma unroll 8
   for (int y = 0; y < M; ++y) {
-    double sn, cs;
-    sincospi(-2.0 * (double)((ky * y) % M) / (double)M, &sn, &cs);
-    const double2 t = tmp[y * M + kx];
-    re += t.x * cs - t.y * sn;
-    im += t.x * sn + t.y * cs;
-    l1 += tmp[M * M + y].x;
+    const double2 w = W[k], t = tmp[y * M + kx];
+    re += t.x * w.x - t.y * w.y;
+    im += t.x * w.y + t.y * w.x;
+    l1 += l1s[y];
+    k = (k + ky) & (M - 1);
   }
   const double bound = 4.0 * M * 0x1p-52 * l1;
   qspec[e] = hypot(re, im) <= bound ? make_float2(0.0f, 0.0f) : make_float2((float)re, (float)im);
@@ -1701,21 +1752,18 @@ hipError_t launch_level_constants(int m, int levels, double alpha, int u_given, 
                                   double* u0, double* w0, float* w0f, float* u0f, float2* qf, double* lvl,
                                   int lvl_a_off, double2* scr_q, double* scr_u, int rb, float4* qtab,
                                   float2* qspec, double2* spec_tmp, hipStream_t s) {
-  hipLaunchKernelGGL(level_constants_kernel, dim3(1), dim3(1024), 0, s, m, levels, alpha, u_given, q64, u0,
-                     w0, w0f, u0f, qf, lvl, lvl_a_off, scr_q, scr_u);
+  if (!plan_valid(m, rb) || levels < 1 || (1 << (levels - 1)) > m) return hipErrorInvalidValue;
+  const int region = std::min(m, std::max(16, 1 << (levels - 1)));
+  const LevelArgs a{m,  levels, region, (m / region) * (m / region), alpha, u_given, q64, u0,   w0,      w0f, u0f,
+                    qf, lvl,    lvl_a_off, scr_q, scr_u, rb, keeps_table(m) ? 1 : 0, qtab, spec_tmp};
+  hipLaunchKernelGGL(level_constants_kernel, dim3(a.n_regions + m), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(probe_spectrum_rows_kernel, dim3(m), dim3(m), 0, s, m, (const float2*)qf, spec_tmp);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-#define MG_QT(MM, RR)                                                                                     \
-  if (m == MM && rb == RR) {                                                                              \
-    hipLaunchKernelGGL((qtab_kernel<MM, RR>), dim3((MM * MM + 255) / 256), dim3(256), 0, s, qf, u0f, qtab); \
-    e = hipGetLastError();                                                                                \
-    if (e != hipSuccess) return e;                                                                        \
+#define MG_QT(MM, RR)                                                                                      \
+  if (m == MM && rb == RR) {                                                                               \
     hipLaunchKernelGGL((probe_spectrum_cols_kernel<MM, RR>), dim3((MM * MM + 255) / 256), dim3(256), 0, s, \
-                       (const double2*)spec_tmp, qspec);                                                  \
-    return hipGetLastError();                                                                             \
+                       (const double2*)spec_tmp, qspec);                                                   \
+    return hipGetLastError();                                                                              \
   }
   MG_FOR_EACH_PLAN(MG_QT)
 #undef MG_QT
@@ -1838,47 +1886,69 @@ hipError_t launch_reduce_sum(const double* x, int n, double* out, hipStream_t s)
   return hipGetLastError();
 }
 
-// Probe step (beyond the paper; simultaneous with the object step): per pixel,
-// FP64 sums over the minibatch's slots in order.
-// Pass 1: chunk c of PROBE_CHUNK slots; per pixel the FP64 sums of the probe
-// numerator and denominator in slot order, and per chunk (one thread) the sum
-// of the slots' largest |z_k|^2.  part: [chunk][3][mm], then [chunk] maxima.
-__global__ __launch_bounds__(256) void probe_partial_kernel(int mm, int count, int nwaves, const float2* num,
-                                                            const float* den, const float* pmax, double* part) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  const int c = blockIdx.y;
-  const int s0 = c * PROBE_CHUNK, s1 = min(count, s0 + PROBE_CHUNK);
+// Probe step (beyond the paper), per pixel FP64 sums over the minibatch's slots in order.
+// Pass 1: chunk c of PROBE_CHUNK slots; per pixel the sums of conj(z_k)(R_k - Q z_k)
+// and |z_k|^2 in slot order, from the stored differences Q z_k - R_k and the object
+// itself (it runs before the accumulation changes it, or, for the alternating step,
+// after), and per chunk the sum of the slots' largest |z_k|^2.  All of a chunk's loads
+// are in flight together.  part: [chunk][3][mm], then [chunk] maxima.
+__global__ __launch_bounds__(256) void probe_partial_kernel(const float2* __restrict__ z, int n_cols, int m, int lm,
+                                                            const int4* __restrict__ pos, const int* epoch,
+                                                            int epoch_stride, int count, int nwaves,
+                                                            const float2* __restrict__ diff,
+                                                            const float* __restrict__ pmax,
+                                                            double* __restrict__ part) {
+  __shared__ float smax[PROBE_CHUNK];
+  const int mm = m * m, p = blockIdx.x * 256 + threadIdx.x, c = blockIdx.y;
+  const int s0 = c * PROBE_CHUNK, n = min(count - s0, PROBE_CHUNK);
   const int chunks = (count + PROBE_CHUNK - 1) / PROBE_CHUNK;
+  const int4* rec = pos + (epoch ? (size_t)(*epoch) * epoch_stride : 0) + s0;
   if (p < mm) {
-    double nr = 0.0, ni = 0.0, dd = 0.0;
-    for (int s = s0; s < s1; ++s) {
-      const float2 v = num[(size_t)s * mm + p];
-      nr += (double)v.x;
-      ni += (double)v.y;
-      dd += (double)den[(size_t)s * mm + p];
+    const size_t at = (size_t)(p >> lm) * n_cols + (p & (m - 1));
+    float2 d[PROBE_CHUNK], zz[PROBE_CHUNK];
+#pragma unroll
+    for (int s = 0; s < PROBE_CHUNK; ++s) {
+      const int t = s < n ? s : n - 1;
+      const int4 r = rec[t];
+      d[s] = diff[(size_t)(s0 + t) * mm + p];
+      zz[s] = z[(size_t)r.y * n_cols + r.z + at];
     }
+    double nr = 0.0, ni = 0.0, dd = 0.0;
+#pragma unroll
+    for (int s = 0; s < PROBE_CHUNK; ++s)
+      if (s < n) {
+        const float2 v = cmulc(zz[s], make_float2(-d[s].x, -d[s].y));
+        nr += (double)v.x;
+        ni += (double)v.y;
+        dd += (double)(zz[s].x * zz[s].x + zz[s].y * zz[s].y);
+      }
     double* q = part + (size_t)c * 3 * mm;
     q[p] = nr;
     q[mm + p] = ni;
     q[2 * mm + p] = dd;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    double mx = 0.0;
-    for (int s = s0; s < s1; ++s) {
+  if (blockIdx.x == 0) {
+    if ((int)threadIdx.x < n) {
       float w = 0.0f;
-      for (int j = 0; j < nwaves; ++j) w = fmaxf(w, pmax[(size_t)s * MAX_WAVES + j]);
-      mx += (double)w;
+      for (int j = 0; j < nwaves; ++j) w = fmaxf(w, pmax[(size_t)(s0 + threadIdx.x) * MAX_WAVES + j]);
+      smax[threadIdx.x] = w;
     }
-    part[(size_t)chunks * 3 * mm + c] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double mx = 0.0;
+      for (int s = 0; s < n; ++s) mx += (double)smax[s];
+      part[(size_t)chunks * 3 * mm + c] = mx;
+    }
   }
 }
 
 // Pass 2: the chunks in order, then the probe step where the denominator is positive.
-__global__ __launch_bounds__(256) void probe_apply_kernel(int mm, int chunks, double beta, const double* part,
-                                                          double2* q64) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(64) void probe_apply_kernel(int mm, int chunks, double beta,
+                                                         const double* __restrict__ part, double2* __restrict__ q64) {
+  const int p = blockIdx.x * 64 + threadIdx.x;
   if (p >= mm) return;
   double nr = 0.0, ni = 0.0, dd = 0.0, mx = 0.0;
+#pragma unroll 8
   for (int c = 0; c < chunks; ++c) {
     const double* q = part + (size_t)c * 3 * mm;
     nr += q[p];
@@ -1895,16 +1965,21 @@ __global__ __launch_bounds__(256) void probe_apply_kernel(int mm, int chunks, do
   }
 }
 
-hipError_t launch_probe_apply(int m, int count, int nwaves, const float2* num, const float* den, const float* pmax,
-                              double beta, double2* q64, double* scratch, hipStream_t s) {
+hipError_t launch_probe_partial(int m, const StepArgs& a, int nwaves, double* scratch, hipStream_t s) {
+  if (a.count <= 0) return hipSuccess;
+  int lm = 0;
+  while ((1 << lm) < m) ++lm;
+  const int mm = m * m, chunks = (a.count + PROBE_CHUNK - 1) / PROBE_CHUNK;
+  hipLaunchKernelGGL(probe_partial_kernel, dim3((mm + 255) / 256, chunks), dim3(256), 0, s, a.z, a.n_cols, m, lm, a.pos,
+                     a.epoch, a.epoch_stride, a.count, nwaves, (const float2*)a.probe_num, (const float*)a.probe_max,
+                     scratch);
+  return hipGetLastError();
+}
+
+hipError_t launch_probe_apply(int m, int count, double beta, double2* q64, const double* scratch, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  const int mm = m * m;
-  const int chunks = (count + PROBE_CHUNK - 1) / PROBE_CHUNK;
-  hipLaunchKernelGGL(probe_partial_kernel, dim3((mm + 255) / 256, chunks), dim3(256), 0, s, mm, count, nwaves, num,
-                     den, pmax, scratch);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(probe_apply_kernel, dim3((mm + 255) / 256), dim3(256), 0, s, mm, chunks, beta, scratch, q64);
+  const int mm = m * m, chunks = (count + PROBE_CHUNK - 1) / PROBE_CHUNK;
+  hipLaunchKernelGGL(probe_apply_kernel, dim3((mm + 63) / 64), dim3(64), 0, s, mm, chunks, beta, scratch, q64);
   return hipGetLastError();
 }
 
