@@ -82,6 +82,17 @@ struct AccumArgs {
   const float* w0f;       // u + |Q|^2 [m][m], FP32 copy
 };
 
+// Consecutive minibatches of `batch` positions (the last of an epoch may be short) in one
+// launch of one workgroup: step.pos holds the records of whole epochs of n_pos positions,
+// n_minibatches counts over them; step's object is read and z (the same array) updated.
+struct ChainArgs {
+  StepArgs step;
+  float2* z;
+  const float* w0f;
+  int n_pos, batch, n_minibatches;
+  int spare;   // set by the launch: groups without a position only help with the sums
+};
+
 constexpr int ACC_TILE_W = 32;   // accumulation tile width (two rows per wave)
 // one pixel per thread: a 32 x TH tile takes 32 TH threads (TH / 2 waves)
 constexpr int acc_threads(int th) { return ACC_TILE_W * th; }
@@ -104,6 +115,9 @@ hipError_t launch_step(int m, int rb, int mode, const StepArgs& a, hipStream_t s
                        hipEvent_t ev1 = nullptr);
 hipError_t launch_accumulate(const AccumArgs& a, int th, int n_tiles, hipStream_t s, hipEvent_t ev0 = nullptr,
                              hipEvent_t ev1 = nullptr);
+// Largest minibatch the chained launch takes with plan (m, rb) and that many grids (0: none).
+int chain_limit(int m, int rb, int levels);
+hipError_t launch_chain(int m, int rb, const ChainArgs& q, hipStream_t s);
 // One launch over several contexts: descriptor j describes context j for this
 // round; prefix (device, n_ctx + 1 ints) holds the running totals of the
 // contexts' positions (step) or tiles (accumulation), prefix[0] = 0 and

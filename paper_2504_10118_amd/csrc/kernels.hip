@@ -275,9 +275,10 @@ __device__ __forceinline__ bool modulus_diff(float2 t, float s, float2& out, flo
 // levels 2.. unpadded.  Each level's constants (V, rho, r: they do not depend on
 // the data) are loaded before the barrier that precedes the level, so their
 // latency overlaps the wait.
-template <int M, int TPB, int P, int RB, int RA>
-__device__ void magps_lds(const StepArgs& a, const float2* T, double2* C, const float2* v, const float* u0v,
-                          int col, int g, float2* stage_k, const int tid) {
+// CHAIN: the result goes to the tile in natural order instead of the staging.
+template <int M, int TPB, int P, int RB, int RA, bool CHAIN = false>
+__device__ void magps_lds(const StepArgs& a, float2* T, double2* C, float2* v, const float* u0v, int col, int g,
+                          float2* stage_k, const int tid) {
   const int L = a.levels;
   constexpr int M1 = M / 2, S1 = M1 + 1;
   constexpr int E1 = (M1 * M1 + TPB - 1) / TPB;               // level-1 bins per thread
@@ -474,6 +475,18 @@ __device__ void magps_lds(const StepArgs& a, const float2* T, double2* C, const 
     }
   }
   __syncthreads();
+  if constexpr (CHAIN) {
+#pragma unroll
+    for (int n1 = 0; n1 < RA; ++n1) {
+      const double2 e1 = C[((RB * n1 + g) >> 1) * S1 + (col >> 1)];
+      const double uu = (double)u0v[n1];
+      v[n1] = make_float2((float)(uu * e1.x - (double)v[n1].x), (float)(uu * e1.y - (double)v[n1].y));
+    }
+    __syncthreads();   // every thread has read its e_1, which overlays the tile
+#pragma unroll
+    for (int n1 = 0; n1 < RA; ++n1) T[(RB * n1 + g) * P + col] = v[n1];
+    return;
+  }
   // stage_k (this position's staged update) is uniform, so the resource stays scalar
   const rsrc_t outr = make_rsrc(stage_k, (unsigned)(M * M * sizeof(float2)));
 #pragma unroll
@@ -495,8 +508,21 @@ __device__ void magps_lds(const StepArgs& a, const float2* T, double2* C, const 
 // transposes (forward and back) synchronise the workgroup.
 // COH: the object is read at device scope (the work-queue launch, where other
 // workgroups of the same launch update it).
-template <int M, int RBv, int MODE, bool COH = false>
-__device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
+// CHAIN: the body is run by one group of TPB threads of a larger workgroup, on its own
+// part of LDS (the chained launch: the record comes from the caller, the in-wave V-cycle's
+// constants are parked already, and the update c_k is left in the tile, natural order with
+// the tile's pitch, instead of the staging).
+struct ChainGroup {
+  float2* tile;
+  const double* cst;
+  float2* zc;
+  int tid, k;
+  int2 off;
+  bool active;   // false: the group repeats another group's position and records nothing
+};
+
+template <int M, int RBv, int MODE, bool COH = false, bool CHAIN = false>
+__device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const ChainGroup* cg = nullptr) {
   constexpr int RB = Plan<M, RBv>::RB, RA = Plan<M, RBv>::RA;
   constexpr int TPB = M * RB, CB = RA / RB, P = M + Plan<M, RBv>::PAD;
   constexpr int LANES = TPB < 64 ? TPB : 64;
@@ -511,12 +537,14 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
   constexpr int XV = TPB <= 512 ? XOR_ALL_VALU : 32;
   extern __shared__ double2 smem_d2[];
   float2* T = reinterpret_cast<float2*>(smem_d2);
+  if constexpr (CHAIN) T = cg->tile;
 
-  // In the work-queue launch the body runs in a loop: an opaque copy of the
+  // In the work-queue and chained launches the body runs in a loop: an opaque copy of the
   // thread index keeps the compiler from hoisting the index arithmetic out of
   // the loop and holding it in registers across both item kinds.
   int tid = threadIdx.x;
-  if constexpr (COH) asm volatile("" : "+v"(tid));
+  if constexpr (CHAIN) tid = cg->tid;
+  if constexpr (COH || CHAIN) asm volatile("" : "+v"(tid));
   const int g = tid & (RB - 1);
   const int col = tid / RB;
   const int cl = col & (CPW - 1);
@@ -525,7 +553,10 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
   const size_t eoff = a.epoch ? (size_t)(*a.epoch) * a.epoch_stride : 0;
   int k, slot = wg;   // slot: where this position's staged update (and probe partials) go
   int2 off;
-  if (a.posx) {
+  if constexpr (CHAIN) {
+    k = cg->k;
+    off = cg->off;
+  } else if (a.posx) {
     const int4 pr = a.posx[eoff + wg];
     k = pr.x;
     off = make_int2(pr.y, pr.z);
@@ -576,6 +607,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
   // in-wave V-cycle constants parked in LDS beside the tile (M <= 64; larger M
   // takes the V-cycle through LDS, which reads its constants from memory)
   constexpr bool CST = STEPM && (M <= 64) && (LWI > 0);
+  constexpr bool PARK = CST && !CHAIN;   // the chained launch has parked them already
   // The twiddle table reads go first (small, needed by the first FFT stage).
   float2 qk[KEEP ? RA : 1];
   float u0k[KEEP ? RA : 1];
@@ -607,11 +639,12 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
   constexpr int M1c = M / 2;
   constexpr int CST_MAX = CST ? cst_count_max(M, LWI) : 2;
   constexpr int CST_PER = ((CST_MAX + 1) / 2 + TPB - 1) / TPB;   // double2 per thread
-  double* const Cst = reinterpret_cast<double*>(T + M * P);
-  const int nCst = (CST && a.levels >= 2 && a.levels - 1 <= LWI) ? cst_count(M, a.levels) : 0;
-  double2 cst[CST_PER];
+  const double* Cst = reinterpret_cast<const double*>(T + M * P);
+  if constexpr (CHAIN) Cst = cg->cst;
+  [[maybe_unused]] const int nCst = (CST && a.levels >= 2 && a.levels - 1 <= LWI) ? cst_count(M, a.levels) : 0;
+  double2 cst[PARK ? CST_PER : 1];
   auto load_cst = [&]() {
-    if constexpr (CST) {
+    if constexpr (PARK) {
       const double2* src = reinterpret_cast<const double2*>(a.lvl + a.lvl_a_off);
 #pragma unroll
       for (int i = 0; i < CST_PER; ++i) {
@@ -653,9 +686,11 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
   // reference value of the window: its centre pixel (see the spectrum term after
   // the forward transform, which reads it back from s_zc past the next barrier
   // rather than holding it in registers through the column pass)
-  __shared__ float2 s_zc;
+  __shared__ float2 s_zc_;
+  float2* s_zc = &s_zc_;
+  if constexpr (CHAIN) s_zc = cg->zc;
   const float2 zc = T[(M / 2) * P + M / 2];
-  if (tid == 0) s_zc = zc;
+  if (tid == 0) *s_zc = zc;
 #pragma unroll
   for (int n1 = 0; n1 < RA; ++n1) {
     float2 qv;
@@ -708,10 +743,11 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
   for (int c = 0; c < CB; ++c)
 #pragma unroll
     for (int k2 = 0; k2 < RB; ++k2) T[((g * CB + c) + RA * k2) * P + col] = v[c * RB + k2];
-  if constexpr (CST) {
+  if constexpr (PARK) {
+    double2* const dst = reinterpret_cast<double2*>(T + M * P);
 #pragma unroll
     for (int i = 0; i < CST_PER; ++i)
-      if (2 * (tid + i * TPB) < nCst) reinterpret_cast<double2*>(Cst)[tid + i * TPB] = cst[i];
+      if (2 * (tid + i * TPB) < nCst) dst[tid + i * TPB] = cst[i];
   }
   __syncthreads();
 
@@ -742,7 +778,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
   // so that only RB of its values are live at a time.
   // Buffer loads: one per-lane offset and a constant per-load offset (a plain
   // pointer per load costs an address pair each and spilled at 128 x 128).
-  const float2 zcs = s_zc;
+  const float2 zcs = *s_zc;
   const rsrc_t qsr = make_rsrc(a.qspec, (unsigned)(M * M * sizeof(float2)));
 #pragma unroll
   for (int c = 0; c < CB; ++c) {
@@ -807,7 +843,9 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
       }
     }
     }
-    if (a.phi_part) {
+    bool active = true;
+    if constexpr (CHAIN) active = cg->active;
+    if (a.phi_part && active) {
       const double tot = wave_sum<LANES, XV>((double)phis);
       if ((tid & 63) == 0) a.phi_part[(size_t)k * MAX_WAVES + wave] = tot * (0.5 / ((double)M * (double)M));
     }
@@ -894,11 +932,17 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
     } else {
       const rsrc_t outr = make_rsrc(a.stage + (size_t)slot * M * M, (unsigned)(M * M * sizeof(float2)));
       const int ovo = (g * M + col) * (int)sizeof(float2);
+      // the update of row RB*n1 + g.  (Chained: into the tile, whose columns of this wave
+      // only this wave has used since the last barrier.)
+      auto emit = [&](int n1, float2 c) {
+        if constexpr (CHAIN) T[(RB * n1 + g) * P + col] = c;
+        else bstore2_stage(outr, c, ovo, n1 * qso, a.stage_wt != 0);
+      };
       const int L = a.levels;
       if (L <= 1) {
+        if constexpr (CHAIN) wave_sync();
 #pragma unroll
-        for (int n1 = 0; n1 < RA; ++n1)
-          bstore2_stage(outr, make_float2(-v[n1].x, -v[n1].y), ovo, n1 * qso, a.stage_wt != 0);
+        for (int n1 = 0; n1 < RA; ++n1) emit(n1, make_float2(-v[n1].x, -v[n1].y));
         return;
       }
       if (L - 1 <= LWI) {
@@ -914,6 +958,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
         constexpr int NCP = (LW > LRB) ? (1 << (LW - LRB)) : 1;
         constexpr int NC0 = NCP > NCB ? NCP : NCB;
         constexpr int NC = NC0 < RA ? NC0 : RA;
+        if constexpr (CHAIN) wave_sync();
 #pragma unroll
         for (int n0 = 0; n0 < RA; n0 += NC) {
           double2 cur[NC], e1[NC];
@@ -955,8 +1000,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
               // stored times 1/4: gh is the bin's sum, 4 g^_l, and the products with the
               // scaled constants are the same numbers as those of the mean (scaling by a
               // power of two is exact)
-              const double* A = (const double*)Cst + (size_t)(l - 1) * M1c * (M1c + CST_PAD);
-              const double* V = (const double*)Cst + cst_v_off(M, L, l);
+              const double* A = Cst + (size_t)(l - 1) * M1c * (M1c + CST_PAD);
+              const double* V = Cst + cst_v_off(M, L, l);
               const bool more = (l + 1 < L);
 #pragma unroll
               for (int i = 0; i < NC; ++i) {
@@ -979,10 +1024,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
             double uu;
             if constexpr (KEEP) uu = (double)u0k[n0 + i];
             else uu = (double)ut[(n0 + i) * TPB];
-            bstore2_stage(outr,
-                          make_float2((float)(uu * e1[i].x - (double)v[n0 + i].x),
-                                      (float)(uu * e1[i].y - (double)v[n0 + i].y)),
-                          ovo, (n0 + i) * qso, a.stage_wt != 0);
+            emit(n0 + i, make_float2((float)(uu * e1[i].x - (double)v[n0 + i].x),
+                                     (float)(uu * e1[i].y - (double)v[n0 + i].y)));
           }
         }
         return;
@@ -1000,7 +1043,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg) {
 #pragma unroll
       for (int n1 = 0; n1 < RA; ++n1) T[(RB * n1 + g) * P + col] = v[n1];
       __syncthreads();
-      magps_lds<M, TPB, P, RB, RA>(a, T, smem_d2, v, u0v, col, g, a.stage + (size_t)slot * M * M, tid);
+      magps_lds<M, TPB, P, RB, RA, CHAIN>(a, T, reinterpret_cast<double2*>(T), v, u0v, col, g,
+                                          a.stage + (size_t)slot * M * M, tid);
     }
   }
 }
@@ -1047,6 +1091,142 @@ template <int M, int RB>
 static size_t lds_bytes_m() {
   static_assert(lds_bytes_c<M, RB>() <= (size_t)LDS_MAX_BYTES, "step kernel LDS exceeds the CU's LDS");
   return lds_bytes_c<M, RB>();
+}
+
+// ---------------------------------------------------------------------------
+// Chained launch: consecutive minibatches of few positions on one workgroup.  The
+// workgroup holds one group of the plan's threads per position (up to 1024 threads); each
+// minibatch is the groups' steps, which leave their updates in their tiles, then the sums
+// of the updates over the windows' pixels and the object's update, with workgroup
+// barriers in between: data stays on one CU, so nothing has to be written back between
+// minibatches.  With one grid or the in-wave V-cycle the workgroup has all its groups even
+// if the minibatch has fewer positions: the spare ones share the sums (q.spare).  A pixel is handled for the first window that covers it, and its sums run over
+// the covering windows in processing order, so the results are those of the step and
+// accumulation launches bit for bit.
+// ---------------------------------------------------------------------------
+constexpr int CHAIN_MAX = 16;   // groups of a workgroup
+// Workgroup barriers of step_body with one grid or the in-wave V-cycle (after the gather and
+// before each transpose's reads): what a spare group waits at meanwhile.
+constexpr int STEP_BARRIERS = 3;
+
+template <int M, int RB>
+constexpr bool chain_ok() {
+  // a group is whole waves; plans of more points per thread spill at the 128 registers
+  // of a 1024-thread workgroup
+  return M <= 64 && (M * RB) % 64 == 0 && RB == (M >= 64 ? 8 : 4);
+}
+template <int M, int RB>
+constexpr size_t chain_tile_bytes() {
+  return (size_t)M * (M + Plan<M, RB>::PAD) * sizeof(float2);
+}
+template <int M, int RB>
+constexpr size_t chain_shared_bytes() {   // V-cycle constants, then w0
+  return (size_t)((cst_count_max(M, inwave_depth<M, RB>()) + 1) & ~1) * sizeof(double) + (size_t)M * M * sizeof(float);
+}
+template <int M, int RB>
+constexpr int chain_groups_c() {
+  if (!chain_ok<M, RB>()) return 0;
+  return std::min(CHAIN_MAX, 1024 / (M * RB));
+}
+
+template <int M, int RBv>
+__global__ __launch_bounds__((chain_groups_c<M, RBv>() * M * RBv)) void chain_kernel(ChainArgs q) {
+  constexpr int TPB = M * RBv, MM = M * M, P = M + Plan<M, RBv>::PAD, TILE = M * P;
+  static_assert(chain_groups_c<M, RBv>() * chain_tile_bytes<M, RBv>() + chain_shared_bytes<M, RBv>() + 1024 <=
+                    (size_t)LDS_MAX_BYTES, "chained kernel LDS exceeds the CU's LDS");
+  extern __shared__ double2 smem_d2[];
+  __shared__ int4 srec[2][CHAIN_MAX];
+  __shared__ float2 szc[CHAIN_MAX];
+  const StepArgs& a = q.step;
+  const int group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / TPB);
+  float2* const tiles = reinterpret_cast<float2*>(smem_d2);
+  double* const cst = reinterpret_cast<double*>(tiles + (size_t)q.batch * TILE);
+  float* const w0 = reinterpret_cast<float*>(cst + ((cst_count_max(M, inwave_depth<M, RBv>()) + 1) & ~1));
+  if (a.levels >= 2 && a.levels - 1 <= inwave_depth<M, RBv>()) {
+    const int n = cst_count(M, a.levels);
+    const double2* src = reinterpret_cast<const double2*>(a.lvl + a.lvl_a_off);
+    for (int e = threadIdx.x; 2 * e < n; e += blockDim.x) reinterpret_cast<double2*>(cst)[e] = src[e];
+  }
+  for (int e = threadIdx.x; e < MM; e += blockDim.x) w0[e] = q.w0f[e];
+  ChainGroup cg;
+  cg.tile = tiles + (size_t)group * TILE;
+  cg.cst = cst;
+  cg.zc = &szc[group];
+  cg.tid = (int)threadIdx.x - group * TPB;
+  // records of a minibatch, loaded a minibatch ahead
+  int base = 0, left = q.n_pos;   // first record of the minibatch after the loaded one; positions left in its epoch
+  auto fetch = [&](int buf) {
+    const int n = min(q.batch, left);
+    if ((int)threadIdx.x < n) srec[buf][threadIdx.x] = a.pos[base + threadIdx.x];
+    base += n;
+    left -= n;
+    if (left == 0) left = q.n_pos;
+    return n;
+  };
+  int next = fetch(0);
+  __syncthreads();
+#pragma unroll 1
+  for (int i = 0; i < q.n_minibatches; ++i) {
+    const int count = next;
+    const int4* rec = srec[i & 1];
+    cg.active = group < count;
+    const int4 r = rec[cg.active ? group : 0];
+    cg.k = __builtin_amdgcn_readfirstlane(r.x);
+    cg.off = make_int2(__builtin_amdgcn_readfirstlane(r.y), __builtin_amdgcn_readfirstlane(r.z));
+    if (i + 1 < q.n_minibatches) next = fetch((i + 1) & 1);
+    if (cg.active || !q.spare) {
+      step_body<M, RBv, MODE_STEP, false, true>(a, 0, &cg);
+    } else {
+#pragma unroll
+      for (int k = 0; k < STEP_BARRIERS; ++k) __syncthreads();
+    }
+    __syncthreads();   // the updates are in the tiles
+    // U pixels per thread at a time: their object values are loaded together, and each
+    // window's offset is read once for all of them
+    constexpr int U = 4;
+    int t0 = threadIdx.x;
+    asm volatile("" : "+v"(t0));
+#pragma unroll 1
+    for (int e0 = t0; e0 < count * MM; e0 += U * (int)blockDim.x) {
+      int Y[U], X[U], s[U];
+      float2 zo[U];
+      double nr[U], ni[U], dd[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = e0 + u * (int)blockDim.x;
+        const bool in = e < count * MM;
+        s[u] = in ? e / MM : -1;
+        const int4 o = rec[in ? s[u] : 0];
+        Y[u] = in ? o.y + e % MM / M : -2 * M;
+        X[u] = o.z + e % M;
+        zo[u] = in ? q.z[(size_t)Y[u] * a.n_cols + X[u]] : make_float2(0.0f, 0.0f);
+        nr[u] = ni[u] = dd[u] = 0.0;
+      }
+      for (int j = 0; j < count; ++j) {
+        const int4 o = rec[j];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int yy = Y[u] - o.y, xx = X[u] - o.z;
+          if ((unsigned)yy < (unsigned)M && (unsigned)xx < (unsigned)M) {
+            if (j < s[u]) {
+              Y[u] = -2 * M;   // an earlier window has this pixel
+            } else {
+              const float2 c = tiles[(size_t)j * TILE + yy * P + xx];
+              nr[u] += (double)c.x;
+              ni[u] += (double)c.y;
+              dd[u] += (double)w0[yy * M + xx];
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (dd[u] > 0.0)
+          q.z[(size_t)Y[u] * a.n_cols + X[u]] =
+              make_float2((float)((double)zo[u].x + nr[u] / dd[u]), (float)((double)zo[u].y + ni[u] / dd[u]));
+    }
+    __syncthreads();   // the object is updated, the tiles are free
+  }
 }
 
 template <int M, int RB, int MODE>
@@ -1109,6 +1289,55 @@ hipError_t launch_step(int m, int rb, int mode, const StepArgs& a, hipStream_t s
 #define MG_LS(MM, RR) if (m == MM && rb == RR) return launch_step_p<MM, RR>(mode, a, s, ev0, ev1);
   MG_FOR_EACH_PLAN(MG_LS)
 #undef MG_LS
+  return hipErrorInvalidValue;
+}
+
+// The line between the chained launch and two launches per minibatch: the positions'
+// groups fill at most half of a 1024-thread workgroup.  Beyond that the one CU's VALU is
+// what a minibatch waits for.  Per minibatch, three grids, a pass waited for (and, in
+// parentheses, per minibatch of passes over three contexts in turn, where the host's two
+// launches bound the other form), two launches -> chained: 16 x 16 windows, 1: 8.7 -> 4.0
+// (8.5 -> 2.8), 8: 13.1 -> 11.6 (12.8 -> 5.2), 16: 17.6 -> 19.8; 32 x 32, 1: 11.1 -> 7.2
+// (9.2 -> 4.9), 4: 13.8 -> 14.0 (10.0 -> 4.9), 8: 16.1 -> 24.9; 64 x 64, 1: 13.7 -> 11.3
+// (10.1 -> 7.7), 2: 14.3 -> 19.9 us.  Hierarchies whose V-cycle runs through LDS have no
+// spare groups and are chained for single positions only: 32 x 32 with six grids, 1: 12.8 ->
+// 11.6, 4: 14.8 -> 19.4; 64 x 64 with seven, 1: 16.9 -> 16.0 us.
+template <int M, int RB>
+static int chain_limit_p(int levels) {
+  if (!chain_groups_c<M, RB>()) return 0;
+  return levels - 1 <= inwave_depth<M, RB>() ? 512 / (M * RB) : 1;
+}
+
+int chain_limit(int m, int rb, int levels) {
+#define MG_CG(MM, RR) if (m == MM && rb == RR) return chain_limit_p<MM, RR>(levels);
+  MG_FOR_EACH_PLAN(MG_CG)
+#undef MG_CG
+  return 0;
+}
+
+template <int M, int RB>
+static hipError_t launch_chain_p(const ChainArgs& q, hipStream_t s) {
+  if constexpr (chain_groups_c<M, RB>() < 1) {
+    return hipErrorInvalidValue;
+  } else {
+    ChainArgs a = q;
+    a.spare = (q.step.levels <= 1 || q.step.levels - 1 <= inwave_depth<M, RB>()) ? 1 : 0;
+    const int groups = a.spare ? chain_groups_c<M, RB>() : q.batch;
+    const size_t lds = q.batch * chain_tile_bytes<M, RB>() + chain_shared_bytes<M, RB>();
+    const hipError_t e = hipFuncSetAttribute((const void*)chain_kernel<M, RB>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((chain_kernel<M, RB>), dim3(1), dim3(groups * M * RB), lds, s, a);
+    return hipGetLastError();
+  }
+}
+
+hipError_t launch_chain(int m, int rb, const ChainArgs& q, hipStream_t s) {
+  if (q.n_minibatches <= 0) return hipSuccess;
+  if (q.batch < 1 || q.batch > chain_limit(m, rb, q.step.levels)) return hipErrorInvalidValue;
+#define MG_CH(MM, RR) if (m == MM && rb == RR) return launch_chain_p<MM, RR>(q, s);
+  MG_FOR_EACH_PLAN(MG_CH)
+#undef MG_CH
   return hipErrorInvalidValue;
 }
 
