@@ -243,8 +243,11 @@ int magpie_create(magpie_ctx** out, int n_rows, int n_cols, int m, int n_levels,
   if (!rc) rc = dev_alloc(&c->lvl, std::max<size_t>(nlvl, 1));
   if (!rc) rc = dev_alloc(&c->scr_q, 2 * half);
   if (!rc) rc = dev_alloc(&c->scr_u, 2 * half);
-  if (!rc) rc = dev_alloc(&c->flag, 1);
-  if (!rc) rc = dev_alloc(&c->red, 4);
+  if (!rc && hipHostMalloc((void**)&c->red, 2 * sizeof(double) + sizeof(int), hipHostMallocDefault) != hipSuccess) {
+    c->red = nullptr;
+    rc = fail(MAGPIE_ERR_OOM, "pinned host allocation failed");
+  }
+  if (!rc) c->flag = reinterpret_cast<int*>(c->red + 2);
   if (!rc) rc = dev_alloc(&c->epoch_ctr, 1);
   if (!rc && (hipEventCreateWithFlags(&c->pin_done[0], hipEventDisableTiming) != hipSuccess ||
               hipEventCreateWithFlags(&c->pin_done[1], hipEventDisableTiming) != hipSuccess ||
@@ -290,8 +293,7 @@ int magpie_destroy(magpie_ctx* c) {
   dev_free(c->lvl);
   dev_free(c->scr_q);
   dev_free(c->scr_u);
-  dev_free(c->flag);
-  dev_free(c->red);
+  if (c->red) hipHostFree(c->red);
   dev_free(c->epoch_ctr);
   dev_free(c->stage);
   dev_free(c->pnum);
@@ -440,7 +442,7 @@ int magpie_load_intensities(magpie_ctx* c, const float* d, int is_sqrt, int on_d
     }
     src = tmp;
   }
-  MG_HIP(hipMemsetAsync(c->flag, 0, sizeof(int), c->stream));
+  *c->flag = 0;
   hipError_t e = mg::launch_permute_sqrt(c->m, c->rb, c->n_pos, src, is_sqrt ? 1 : 0, c->sqrtd, c->flag, c->stream);
   int bad = 0;
   rc = (e == hipSuccess) ? read_flag(c, &bad) : fail(MAGPIE_ERR_HIP, "permute kernel launch failed");
@@ -460,26 +462,25 @@ int magpie_set_object(magpie_ctx* c, const void* z, int dtype, int on_device) {
   int rc = set_dev(c);
   if (rc) return rc;
   const size_t n = (size_t)c->nr * c->nc;
-  if (on_device) {
-    if (dtype == MAGPIE_C64) {
-      MG_HIP(hipMemcpyAsync(c->z, z, n * sizeof(float2), hipMemcpyDeviceToDevice, c->stream));
-    } else {
-      MG_HIP(mg::launch_convert_c128_c64((const double2*)z, c->z, n, c->stream));
-    }
-  } else {
-    if (dtype == MAGPIE_C64) {
-      MG_HIP(hipMemcpyAsync(c->z, z, n * sizeof(float2), hipMemcpyHostToDevice, c->stream));
-      MG_HIP(hipStreamSynchronize(c->stream));
-    } else {
-      std::vector<float2> t(n);
+  *c->flag = 0;
+  std::vector<float2> t;
+  const void* src = z;
+  if (!on_device) {
+    const float2* h = (const float2*)z;
+    if (dtype == MAGPIE_C128) {
+      t.resize(n);
       const double2* p = (const double2*)z;
       for (size_t i = 0; i < n; ++i) t[i] = make_float2((float)p[i].x, (float)p[i].y);
-      MG_HIP(hipMemcpyAsync(c->z, t.data(), n * sizeof(float2), hipMemcpyHostToDevice, c->stream));
-      MG_HIP(hipStreamSynchronize(c->stream));
+      h = t.data();
     }
+    MG_HIP(hipMemcpyAsync(c->z, h, n * sizeof(float2), hipMemcpyHostToDevice, c->stream));
+    src = c->z;
   }
-  MG_HIP(hipMemsetAsync(c->flag, 0, sizeof(int), c->stream));
-  MG_HIP(mg::launch_check_finite_c64(c->z, n, c->flag, c->stream));
+  const hipError_t e = mg::launch_take_object(src, on_device && dtype == MAGPIE_C128, c->z, n, c->flag, c->stream);
+  if (e != hipSuccess) {
+    (void)hipStreamSynchronize(c->stream);   // the upload reads t or the caller's array
+    return fail(MAGPIE_ERR_HIP, std::string("object check: ") + hipGetErrorString(e));
+  }
   int bad = 0;
   rc = read_flag(c, &bad);
   if (rc) return rc;
@@ -629,10 +630,12 @@ static void workgroup_order(const int32_t* rec, int bt, int cs, int32_t* out, st
 // epochs e0 .. e0+ne-1 (permutations from `order`, already checked, or the
 // library's seeded ones for epoch counter c->epoch_index + e), built in pinned
 // slot `slot` (slot_epochs epochs wide) and uploaded to the device records from
-// epoch offset dev_epoch; the slot's event marks the end of its upload.  With
-// batch > 0 the records of its minibatches in workgroup order go to c->posx too.
+// epoch offset dev_epoch; the slot's event marks the end of its upload.  Minibatches of
+// B positions: the inverse permutations are left out where the accumulation screens the
+// records instead.  With batch > 0 the records of its minibatches in workgroup order go
+// to c->posx too.
 static int fill_records(magpie_ctx* c, int e0, int ne, uint64_t seed, const int32_t* order, int slot,
-                        size_t slot_epochs, size_t dev_epoch, hipStream_t s, int batch = 0) {
+                        size_t slot_epochs, size_t dev_epoch, hipStream_t s, int B, int batch = 0) {
   const int N = c->n_pos;
   // a slot's region moves with its width: then both slots' uploads must be done
   for (int s = 0; s < 2; ++s)
@@ -671,7 +674,8 @@ static int fill_records(magpie_ctx* c, int e0, int ne, uint64_t seed, const int3
                         c->h_sorted);
   }
   const size_t n = (size_t)ne * N;
-  MG_HIP(hipMemcpyAsync(c->inv + dev_epoch * N, hi, n * sizeof(int32_t), hipMemcpyHostToDevice, s));
+  if (B > mg::ACC_SCAN_MAX)
+    MG_HIP(hipMemcpyAsync(c->inv + dev_epoch * N, hi, n * sizeof(int32_t), hipMemcpyHostToDevice, s));
   MG_HIP(hipMemcpyAsync(c->posrec + dev_epoch * N, hr, n * sizeof(int4), hipMemcpyHostToDevice, s));
   if (batch > 0) MG_HIP(hipMemcpyAsync(c->posx + dev_epoch * N, hx, n * sizeof(int4), hipMemcpyHostToDevice, s));
   MG_HIP(hipEventRecord(c->pin_done[slot], s));
@@ -685,7 +689,7 @@ static int prepare_epochs(magpie_ctx* c, int n_epochs, int batch, uint64_t seed,
   int rc = ensure_epoch_buffers(c, n_epochs, batch, (size_t)n_epochs);
   if (!rc && order) rc = check_orders(c, n_epochs, order);
   if (!rc) rc = ensure_pinned(c, (size_t)n_epochs);
-  if (!rc) rc = fill_records(c, 0, n_epochs, seed, order, 0, (size_t)n_epochs, 0, c->stream);
+  if (!rc) rc = fill_records(c, 0, n_epochs, seed, order, 0, (size_t)n_epochs, 0, c->stream, std::min(batch, c->n_pos));
   return rc;
 }
 
@@ -906,7 +910,7 @@ int magpie_run_epochs(magpie_ctx* c, int n_epochs, int batch, uint64_t seed, con
   for (int e0 = 0; e0 < n_epochs; ++chunk) {
     const int ne = chunk == 0 ? 1 : std::min(CH, n_epochs - e0);
     const int slot = chunk & 1;
-    rc = fill_records(c, e0, ne, seed, order, slot, ch, (size_t)slot * ch, c->stream, xorder ? B : 0);
+    rc = fill_records(c, e0, ne, seed, order, slot, ch, (size_t)slot * ch, c->stream, B, xorder ? B : 0);
     if (rc) return rc;
     const size_t off = (size_t)slot * ch * N;
     rc = launch_epochs(c, ne, B, (N + B - 1) / B, false,
@@ -968,11 +972,9 @@ int magpie_objective(magpie_ctx* c, double* phi, double* grad_stat) {
   sa.gn_part = c->gn_part;
   const int nw = mg::step_waves(c->m, c->rb);
   MG_HIP(mg::launch_step(c->m, c->rb, mg::MODE_OBJECTIVE, sa, c->stream));
-  MG_HIP(mg::launch_reduce_parts(c->obj_part, c->n_pos, nw, 0, c->phi_obj, c->red, c->stream));
-  MG_HIP(mg::launch_reduce_parts(c->gn_part, c->n_pos, nw, 1, c->gnorm, c->red + 1, c->stream));
-  double h[2];
-  MG_HIP(hipMemcpyAsync(h, c->red, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  MG_HIP(mg::launch_reduce_objective(c->obj_part, c->gn_part, c->n_pos, nw, c->phi_obj, c->gnorm, c->red, c->stream));
   MG_HIP(hipStreamSynchronize(c->stream));
+  const double h[2] = {((volatile double*)c->red)[0], ((volatile double*)c->red)[1]};
   if (!std::isfinite(h[0]) || !std::isfinite(h[1])) return fail(MAGPIE_ERR_NUMERIC, "non-finite objective");
   *phi = h[0];
   if (grad_stat) *grad_stat = h[1] / ((double)c->n_pos * c->m);
@@ -984,7 +986,7 @@ int magpie_get_step_phi(magpie_ctx* c, double* phi_k) {
   if (!c->has_pos) return fail(MAGPIE_ERR_BAD_STATE, "no positions");
   int rc = set_dev(c);
   if (rc) return rc;
-  MG_HIP(mg::launch_reduce_parts(c->step_part, c->n_pos, mg::step_waves(c->m, c->rb), 0, c->phi_step, nullptr, c->stream));
+  MG_HIP(mg::launch_reduce_phi(c->step_part, c->n_pos, mg::step_waves(c->m, c->rb), c->phi_step, c->stream));
   MG_HIP(hipMemcpyAsync(phi_k, c->phi_step, (size_t)c->n_pos * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   MG_HIP(hipStreamSynchronize(c->stream));
   return MAGPIE_OK;
@@ -1205,7 +1207,6 @@ int magpie_set_tuning(magpie_ctx* c, int threads_per_transform, int tile_rows) {
       rc = dev_alloc(&nat, cnt);
       if (rc) return rc;
       hipError_t e = mg::launch_unpermute_sqrt(c->m, c->rb, c->n_pos, c->sqrtd, nat, c->stream);
-      if (e == hipSuccess) e = hipMemsetAsync(c->flag, 0, sizeof(int), c->stream);
       if (e == hipSuccess) e = mg::launch_permute_sqrt(c->m, rb, c->n_pos, nat, 1, c->sqrtd, c->flag, c->stream);
       if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
       dev_free(nat);
@@ -1548,7 +1549,7 @@ int magpie_run_epochs_multi(magpie_ctx* const* ctxs, int count, int n_epochs, co
     const int slot = chunk & 1;
     // records of every member for these epochs, uploaded on st into its device slot
     for (int i = 0; i < count && !rc; ++i)
-      rc = fill_records(ctxs[i], e0, ne, seed, nullptr, slot, CH, (size_t)slot * CH, st);
+      rc = fill_records(ctxs[i], e0, ne, seed, nullptr, slot, CH, (size_t)slot * CH, st, B[i]);
     if (rc) break;
     // round descriptors of the chunk: per partition and round its members' step
     // descriptors, then their accumulation descriptors by tile height; running

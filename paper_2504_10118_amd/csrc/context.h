@@ -106,6 +106,8 @@ struct magpie_ctx {
   double* lvl = nullptr;
   double2* scr_q = nullptr;
   double* scr_u = nullptr;
+  // pinned host memory kernels write: a check's result and the objective's two sums (every
+  // call that launches such a kernel synchronises the stream before it returns)
   int* flag = nullptr;
   double* red = nullptr;
 
@@ -212,11 +214,10 @@ int noalloc_init_device(int device);
 int launch_epochs(magpie_ctx* c, int n_epochs, int B, int batches_per_epoch, bool allow_graph,
                   const EpochBuffers& buf);
 
+// Waits for the stream and returns what the checks launched since *c->flag was cleared found.
 inline int read_flag(magpie_ctx* c, int* out) {
-  int h = 0;
-  MG_HIP(hipMemcpyAsync(&h, c->flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   MG_HIP(hipStreamSynchronize(c->stream));
-  *out = h;
+  *out = *(volatile int*)c->flag;
   return MAGPIE_OK;
 }
 

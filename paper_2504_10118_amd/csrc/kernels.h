@@ -163,13 +163,16 @@ hipError_t launch_level_constants(int m, int levels, double alpha, int u_given,
                                   const double2* q64, double* u0, double* w0, float* w0f, float* u0f,
                                   float2* qf, double* lvl, int lvl_a_off, double2* scr_q, double* scr_u, int rb,
                                   float4* qtab, float2* qspec, double2* spec_tmp, hipStream_t s);
-hipError_t launch_permute_sqrt(int m, int rb, int n_pos, const float* src, int is_sqrt, float* dst,
-                               int* bad_flag, hipStream_t s);
+// bad: memory the host reads once the stream is synchronised; set to 1 at invalid input
+hipError_t launch_permute_sqrt(int m, int rb, int n_pos, const float* src, int is_sqrt, float* dst, int* bad,
+                               hipStream_t s);
 hipError_t launch_unpermute_sqrt(int m, int rb, int n_pos, const float* src, float* dst, hipStream_t s);
-hipError_t launch_reduce_sum(const double* x, int n, double* out, hipStream_t s);
-// per position: sum of nw partials (optionally sqrt), then a fixed-order total
-hipError_t launch_reduce_parts(const double* parts, int n, int nw, int take_sqrt, double* per_pos,
-                               double* total, hipStream_t s);
+// per position: the sum of its nw per-wave partials
+hipError_t launch_reduce_phi(const double* parts, int n, int nw, double* per_pos, hipStream_t s);
+// the same of the objective's and (square roots) of the gradients' partials, and their
+// sums over the positions into totals[0], totals[1]
+hipError_t launch_reduce_objective(const double* phi, const double* gn, int n, int nw, double* phi_k, double* gnorm_k,
+                                   double* totals, hipStream_t s);
 hipError_t launch_set_counter(int* counter, int value, hipStream_t s);
 hipError_t launch_advance_counter(int* counter, hipStream_t s);
 // Q += sum_s num_s / (sum_s den_s + beta sum_s max_s) where the denominator is
@@ -186,8 +189,8 @@ inline size_t probe_scratch_doubles(int m, int max_count) {
 hipError_t launch_probe_partial(int m, const StepArgs& a, int nwaves, double* scratch, hipStream_t s);
 hipError_t launch_probe_apply(int m, int count, double beta, double2* q64, const double* scratch, hipStream_t s);
 hipError_t launch_convert_c64_c128(const float2* src, double2* dst, size_t n, hipStream_t s);
-hipError_t launch_convert_c128_c64(const double2* src, float2* dst, size_t n, hipStream_t s);
-hipError_t launch_check_finite_c64(const float2* src, size_t n, int* bad_flag, hipStream_t s);
+// dst = src (complex64 or complex128; src may be dst), *bad = 1 at a value that is not finite
+hipError_t launch_take_object(const void* src, int is_c128, float2* dst, size_t n, int* bad, hipStream_t s);
 hipError_t launch_fill_c64(float2* dst, size_t n, float re, float im, hipStream_t s);
 
 }  // namespace mg

@@ -2002,39 +2002,63 @@ hipError_t launch_level_constants(int m, int levels, double alpha, int u_given, 
 // ---------------------------------------------------------------------------
 // sqrt(d) between natural order [k][ky][kx] and the kernel order of plan
 // (M, RB): thread tid = g + RB*ky of position k holds kx = g*CB + c + RA*k2 at
-// j = c*RB + k2, i.e. element [k][tid*RA + j].  Natural -> kernel flags
-// negative or non-finite input.
+// j = c*RB + k2, i.e. element [k][tid*RA + j]: within a row of M values in either order.
+// Natural -> kernel sets *bad (memory the host reads) at negative or non-finite input.
 // ---------------------------------------------------------------------------
-template <int M, int RB, int TO_KERNEL>
-__global__ void permute_sqrt_kernel(int n_pos, const float* src, int is_sqrt, float* dst, int* bad) {
-  constexpr int RA = M / RB, CB = RA / RB;
-  const int k = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int g = tid & (RB - 1), ky = tid / RB;
-  const size_t nat = (size_t)k * M * M + (size_t)ky * M;     // natural row ky
-  const size_t ker = (size_t)k * M * M + (size_t)tid * RA;   // this thread's kernel-order run
-  int badl = 0;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // callers' data: 4-byte alignment
+
+// Rows are staged in LDS, so that both sides move 16 bytes per lane: read and written in
+// place, one side 4 bytes at a stride of RA, 1600 positions of 64 x 64 took 23.6 us; this
+// form 10.8 (52 MB in all: 4.9 TB/s).  Pitch M + 8: the four rows a wave gathers from (M = 64)
+// start eight banks apart.
+template <int M, int RB>
+__global__ __launch_bounds__(M * M / 4 < 256 ? M * M / 4 : 256) void permute_sqrt_kernel(const float* __restrict__ src,
+                                                                                      int is_sqrt,
+                                                                                      float* __restrict__ dst,
+                                                                                      int* bad) {
+  constexpr int RA = M / RB, CB = RA / RB, MM = M * M, NT = MM / 4 < 256 ? MM / 4 : 256, P = M + 8;
+  constexpr int ROWS = 4 * NT / M;   // rows per round
+  __shared__ __attribute__((aligned(16))) float T[ROWS * P];
+  const float* s = src + (size_t)blockIdx.x * MM;
+  float* d = dst + (size_t)blockIdx.x * MM;
+  const int i = 4 * threadIdx.x, row = i / M, col = i % M;
+  bool badl = false;
+#pragma unroll 4
+  for (int e0 = 0; e0 < MM; e0 += 4 * NT) {
+    const f32x4u x = *reinterpret_cast<const f32x4u*>(s + e0 + i);
+    if (e0) __syncthreads();
 #pragma unroll
-  for (int c = 0; c < CB; ++c)
-#pragma unroll
-    for (int k2 = 0; k2 < RB; ++k2) {
-      const int kx = g * CB + c + RA * k2;
-      if (TO_KERNEL) {
-        const float x = src[nat + kx];
-        if (!(x >= 0.0f) || !isfinite(x)) badl = 1;
-        dst[ker + c * RB + k2] = is_sqrt ? x : sqrtf(x);
-      } else {
-        dst[nat + kx] = src[ker + c * RB + k2];
-      }
+    for (int q = 0; q < 4; ++q) {
+      badl = badl || !(x[q] >= 0.0f) || !isfinite(x[q]);
+      T[row * P + col + q] = is_sqrt ? x[q] : sqrtf(x[q]);
     }
-  if (badl) atomicOr(bad, 1);
+    __syncthreads();
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = col + q, g = e / RA, c = e % RA / RB, k2 = e % RB;
+      v[q] = T[row * P + g * CB + c + RA * k2];
+    }
+    *reinterpret_cast<float4*>(d + e0 + i) = make_float4(v[0], v[1], v[2], v[3]);
+  }
+  if (badl) *bad = 1;
+}
+
+template <int M, int RB>
+__global__ void unpermute_sqrt_kernel(const float* src, float* dst) {
+  constexpr int RA = M / RB, CB = RA / RB;
+  const int tid = threadIdx.x, g = tid & (RB - 1), ky = tid / RB;
+  const size_t nat = ((size_t)blockIdx.x * M + ky) * M, ker = (size_t)blockIdx.x * M * M + (size_t)tid * RA;
+#pragma unroll
+  for (int j = 0; j < RA; ++j) dst[nat + g * CB + j / RB + RA * (j % RB)] = src[ker + j];
 }
 
 hipError_t launch_permute_sqrt(int m, int rb, int n_pos, const float* src, int is_sqrt, float* dst, int* bad,
                                hipStream_t s) {
 #define MG_PS(MM, RR) \
   if (m == MM && rb == RR) { \
-    hipLaunchKernelGGL((permute_sqrt_kernel<MM, RR, 1>), dim3(n_pos), dim3(MM * RR), 0, s, n_pos, src, is_sqrt, dst, bad); \
+    hipLaunchKernelGGL((permute_sqrt_kernel<MM, RR>), dim3(n_pos), dim3(std::min(MM * MM / 4, 256)), 0, s, src, is_sqrt, \
+                       dst, bad);                                                                                        \
     return hipGetLastError(); \
   }
   MG_FOR_EACH_PLAN(MG_PS)
@@ -2045,7 +2069,7 @@ hipError_t launch_permute_sqrt(int m, int rb, int n_pos, const float* src, int i
 hipError_t launch_unpermute_sqrt(int m, int rb, int n_pos, const float* src, float* dst, hipStream_t s) {
 #define MG_US(MM, RR) \
   if (m == MM && rb == RR) { \
-    hipLaunchKernelGGL((permute_sqrt_kernel<MM, RR, 0>), dim3(n_pos), dim3(MM * RR), 0, s, n_pos, src, 1, dst, nullptr); \
+    hipLaunchKernelGGL((unpermute_sqrt_kernel<MM, RR>), dim3(n_pos), dim3(MM * RR), 0, s, src, dst); \
     return hipGetLastError(); \
   }
   MG_FOR_EACH_PLAN(MG_US)
@@ -2054,48 +2078,64 @@ hipError_t launch_unpermute_sqrt(int m, int rb, int n_pos, const float* src, flo
 }
 
 // ---------------------------------------------------------------------------
-// Fixed-order FP64 sum of n values (one workgroup): thread t sums t, t+256, ...
-// in order, then a fixed tree.
+// Per position the sum of its nw per-wave partials (and its square root), then the fixed-
+// order FP64 sum over the positions (thread t: t, t + 1024, ... in order, then a fixed
+// tree); workgroup b takes the b-th set.  total may be host memory.  (256 threads with a
+// dependent load per partial, one launch per set: 11.5 us each for 1600 positions.)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void reduce_sum_kernel(const double* x, int n, double* out) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) s += x[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = red[0];
-}
+struct ReduceSets {
+  const double* parts[2];
+  double* per_pos[2];
+  double* total[2];
+  int take_sqrt[2];
+};
 
-__global__ __launch_bounds__(256) void reduce_parts_kernel(const double* parts, int n, int nw, int take_sqrt,
-                                                           double* per_pos, double* total) {
-  __shared__ double red[256];
+template <int NW>
+__global__ __launch_bounds__(1024) void reduce_parts_kernel(ReduceSets r, int n) {
+  __shared__ double red[1024];
+  const int b = blockIdx.x;
+  const double* parts = r.parts[b];
   double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    double p = 0.0;
-    for (int w = 0; w < nw; ++w) p += parts[(size_t)i * MAX_WAVES + w];
-    if (take_sqrt) p = sqrt(p);
-    if (per_pos) per_pos[i] = p;
+#pragma unroll 2
+  for (int i = threadIdx.x; i < n; i += 1024) {
+    double v[NW], p = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) v[w] = parts[(size_t)i * MAX_WAVES + w];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) p += v[w];
+    if (r.take_sqrt[b]) p = sqrt(p);
+    if (r.per_pos[b]) r.per_pos[b][i] = p;
     s += p;
   }
   red[threadIdx.x] = s;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
+  for (int w = 512; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0 && total) *total = red[0];
+  if (threadIdx.x == 0 && r.total[b]) *r.total[b] = red[0];
 }
 
-hipError_t launch_reduce_parts(const double* parts, int n, int nw, int take_sqrt, double* per_pos, double* total,
-                               hipStream_t s) {
-  hipLaunchKernelGGL(reduce_parts_kernel, dim3(1), dim3(256), 0, s, parts, n, nw, take_sqrt, per_pos, total);
+static hipError_t launch_reduce(const ReduceSets& r, int sets, int n, int nw, hipStream_t s) {
+  switch (nw) {
+    case 1: hipLaunchKernelGGL(reduce_parts_kernel<1>, dim3(sets), dim3(1024), 0, s, r, n); break;
+    case 2: hipLaunchKernelGGL(reduce_parts_kernel<2>, dim3(sets), dim3(1024), 0, s, r, n); break;
+    case 4: hipLaunchKernelGGL(reduce_parts_kernel<4>, dim3(sets), dim3(1024), 0, s, r, n); break;
+    case 8: hipLaunchKernelGGL(reduce_parts_kernel<8>, dim3(sets), dim3(1024), 0, s, r, n); break;
+    case 16: hipLaunchKernelGGL(reduce_parts_kernel<16>, dim3(sets), dim3(1024), 0, s, r, n); break;
+    default: return hipErrorInvalidValue;   // waves of a plan: m rb / 64, at least 1
+  }
   return hipGetLastError();
 }
 
+hipError_t launch_reduce_phi(const double* parts, int n, int nw, double* per_pos, hipStream_t s) {
+  return launch_reduce(ReduceSets{{parts, nullptr}, {per_pos, nullptr}, {nullptr, nullptr}, {0, 0}}, 1, n, nw, s);
+}
+
+hipError_t launch_reduce_objective(const double* phi, const double* gn, int n, int nw, double* phi_k, double* gnorm_k,
+                                   double* totals, hipStream_t s) {
+  return launch_reduce(ReduceSets{{phi, gn}, {phi_k, gnorm_k}, {totals, totals + 1}, {0, 1}}, 2, n, nw, s);
+}
 
 // Epoch counter for graph replays (kernels, so that a captured graph holds no memset node).
 __global__ void set_counter_kernel(int* c, int v) { *c = v; }
@@ -2107,11 +2147,6 @@ hipError_t launch_set_counter(int* counter, int value, hipStream_t s) {
 }
 hipError_t launch_advance_counter(int* counter, hipStream_t s) {
   hipLaunchKernelGGL(advance_counter_kernel, dim3(1), dim3(1), 0, s, counter);
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_sum(const double* x, int n, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_sum_kernel, dim3(1), dim3(256), 0, s, x, n, out);
   return hipGetLastError();
 }
 
@@ -2216,13 +2251,16 @@ __global__ void convert_c64_c128_kernel(const float2* src, double2* dst, size_t 
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = make_double2(src[i].x, src[i].y);
 }
-__global__ void convert_c128_c64_kernel(const double2* src, float2* dst, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = make_float2((float)src[i].x, (float)src[i].y);
-}
-__global__ void check_finite_c64_kernel(const float2* src, size_t n, int* bad) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && (!isfinite(src[i].x) || !isfinite(src[i].y))) atomicOr(bad, 1);
+// dst = src (nothing where dst == src), and *bad (memory the host reads) set at a value that is not finite
+template <typename T>
+__global__ __launch_bounds__(256) void take_object_kernel(const T* __restrict__ src, float2* dst, size_t n, int* bad) {
+  float probe = 0.0f;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+    const float2 v = make_float2((float)src[i].x, (float)src[i].y);
+    probe = fmaf(v.x, 0.0f, fmaf(v.y, 0.0f, probe));   // NaN once a value is not finite
+    if ((const void*)src != (const void*)dst) dst[i] = v;
+  }
+  if (!(probe == 0.0f)) *bad = 1;
 }
 
 hipError_t launch_convert_c64_c128(const float2* src, double2* dst, size_t n, hipStream_t s) {
@@ -2230,14 +2268,11 @@ hipError_t launch_convert_c64_c128(const float2* src, double2* dst, size_t n, hi
   hipLaunchKernelGGL(convert_c64_c128_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, dst, n);
   return hipGetLastError();
 }
-hipError_t launch_convert_c128_c64(const double2* src, float2* dst, size_t n, hipStream_t s) {
+hipError_t launch_take_object(const void* src, int is_c128, float2* dst, size_t n, int* bad, hipStream_t s) {
   if (!n) return hipSuccess;
-  hipLaunchKernelGGL(convert_c128_c64_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, dst, n);
-  return hipGetLastError();
-}
-hipError_t launch_check_finite_c64(const float2* src, size_t n, int* bad, hipStream_t s) {
-  if (!n) return hipSuccess;
-  hipLaunchKernelGGL(check_finite_c64_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, n, bad);
+  const unsigned blocks = (unsigned)std::min<size_t>((n + 255) / 256, 2048);
+  if (is_c128) hipLaunchKernelGGL(take_object_kernel<double2>, dim3(blocks), dim3(256), 0, s, (const double2*)src, dst, n, bad);
+  else hipLaunchKernelGGL(take_object_kernel<float2>, dim3(blocks), dim3(256), 0, s, (const float2*)src, dst, n, bad);
   return hipGetLastError();
 }
 

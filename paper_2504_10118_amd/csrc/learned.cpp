@@ -139,8 +139,8 @@ int prolong_into_object(magpie_ctx* c, const void* coarse_dev, int side, int for
 }
 
 int check_object_finite(magpie_ctx* c) {
-  MG_HIP(hipMemsetAsync(c->flag, 0, sizeof(int), c->stream));
-  MG_HIP(mg::launch_check_finite_c64(c->z, (size_t)c->nr * c->nc, c->flag, c->stream));
+  *c->flag = 0;
+  MG_HIP(mg::launch_take_object(c->z, 0, c->z, (size_t)c->nr * c->nc, c->flag, c->stream));
   int bad = 0;
   int rc = read_flag(c, &bad);
   if (rc) return rc;
