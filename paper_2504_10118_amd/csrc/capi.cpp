@@ -150,6 +150,8 @@ int build_tiles(magpie_ctx* c) {
   }
   c->scan_r0 = r0;
   c->scan_r1 = r1;
+  c->scan_c0 = c0;
+  c->scan_c1 = c1;
   c->box_x0 = c0 / mg::ACC_TILE_W;
   c->box_y0 = r0 / c->th;
   c->box_nx = c1 / mg::ACC_TILE_W - c->box_x0 + 1;
@@ -296,6 +298,8 @@ int magpie_destroy(magpie_ctx* c) {
   if (c->red) hipHostFree(c->red);
   dev_free(c->epoch_ctr);
   dev_free(c->stage);
+  dev_free(c->z2);
+  dev_free(c->stage2);
   dev_free(c->pnum);
   dev_free(c->pmax);
   dev_free(c->pacc);
@@ -695,6 +699,39 @@ static int prepare_epochs(magpie_ctx* c, int n_epochs, int batch, uint64_t seed,
 
 }  // extern "C"
 
+// Whether this context's epochs of minibatch size B take merged launches, and their buffers.
+static int prepare_merged(magpie_ctx* c, int B, bool* merged) {
+  *merged = false;
+  if (c->timing || (c->flags & (MAGPIE_UPDATE_PROBE | MAGPIE_PHASE_RECYCLE)) || B > mg::ACC_SCAN_MAX ||
+      !mg::merged_valid(c->m, c->rb) || B <= mg::chain_limit(c->m, c->rb, c->L))
+    return MAGPIE_OK;
+  // windows of the previous minibatch that overlap a window, on average: what a merged step
+  // repeats.  Per minibatch, a pass waited for (in parentheses, of passes over three contexts
+  // in turn, where the launches' host time counts), two launches -> merged: 16 x 16 windows,
+  // 64 of them, 0.2: 11.1 -> 9.3 (10.5 -> 7.0); 64, 2.9: 18.8 -> 17.2 (17.4 -> 14.7); 128, 5.7: 27.1
+  // -> 26.5 us (25.6 -> 16.3); 32 x 32, 32, 0.3: 13.7 -> 12.0 (10.6 -> 8.2); 8, 2.4: 12.5 -> 12.5 (10.4 ->
+  // 8.3); 128, 1.2: 17.3 -> 16.8; 256, 2.4: 21.6 -> 23.0; 64, 4.7: 18.7 -> 19.9; 64 x 64 (eight
+  // staged rows per thread, tiles in the steps' LDS footprint), 16, 1.3: 16.2 -> 18.1 us.
+  const double span_r = c->scan_r1 - c->scan_r0 + 1, span_c = c->scan_c1 - c->scan_c0 + 1;
+  const double overlap = (double)B * 4.0 * c->m * c->m / (span_r * span_c);
+  if (c->m <= 16 ? overlap > 6.0 : (overlap > 2.5 || B > 128)) return MAGPIE_OK;
+  const size_t need = (size_t)B * c->m * c->m;
+  if (need > c->stage2_cap) {
+    MG_HIP(hipStreamSynchronize(c->stream));
+    dev_free(c->stage2);
+    c->stage2_cap = 0;
+    int rc = dev_alloc(&c->stage2, need);
+    if (rc) return rc;
+    c->stage2_cap = need;
+  }
+  if (!c->z2) {
+    int rc = dev_alloc(&c->z2, (size_t)c->nr * c->nc);
+    if (rc) return rc;
+  }
+  *merged = true;
+  return MAGPIE_OK;
+}
+
 // Launches n_epochs prepared epochs of minibatch size B (the first
 // batches_per_epoch minibatches of each; the rest are not run) on the buffers
 // `buf` (the context's own, or the caller-free scratch of the no-allocation entry
@@ -843,6 +880,55 @@ int mgrt::launch_epochs(magpie_ctx* c, int n_epochs, int B, int batches_per_epoc
     MG_HIP(mg::launch_chain(m, c->rb, q, c->stream));
     return MAGPIE_OK;
   }
+  if (buf.stage2) {
+    // merged launches (the caller has found that they pay): each but the first writes the
+    // object with the minibatch's before it to the other buffer; the last update ends in c->z
+    const int th = mg::qtile_rows(m, c->rb);
+    aa.box_y0 = c->scan_r0 / th;
+    const int tiles = c->box_nx * (c->scan_r1 / th - aa.box_y0 + 1);
+    float2* zb[2] = {c->z, c->z2};
+    float2* sb[2] = {buf.stage, buf.stage2};
+    int cur = 0;      // buffer that holds the object before the pending update
+    bool pending = false;
+    int i = 0;
+    auto update_to = [&](float2* out) {
+      aa.z = zb[cur];
+      aa.z_out = out;
+      aa.n_tiles = tiles;
+    };
+    for (int e = 0; e < n_epochs; ++e)
+      for (int t = 0; t < nbatch; ++t, ++i) {
+        sa.pos = buf.posrec + (size_t)e * N + (size_t)t * B;
+        sa.count = std::min(B, N - t * B);
+        sa.stage = sb[i & 1];
+        sa.z = zb[cur];
+        if (pending) {
+          update_to(zb[1 - cur]);
+        } else {
+          aa.count = 0;
+          aa.n_tiles = 0;
+          aa.pos = sa.pos;
+        }
+        MG_HIP(mg::launch_merged(m, c->rb, sa, aa, c->stream));
+        if (pending) cur = 1 - cur;
+        pending = true;
+        aa.pos = sa.pos;
+        aa.count = sa.count;
+        aa.stage = sa.stage;
+      }
+    if (pending) {
+      if (cur == 0) {   // in place: the plain accumulation
+        aa.z = c->z;
+        aa.box_y0 = c->box_y0;
+        MG_HIP(mg::launch_accumulate(aa, c->th, n_tiles, c->stream));
+      } else {
+        update_to(c->z);
+        sa.count = 0;
+        MG_HIP(mg::launch_merged(m, c->rb, sa, aa, c->stream));
+      }
+    }
+    return MAGPIE_OK;
+  }
   for (int e = 0; e < n_epochs; ++e) {
     for (int t = 0; t < nbatch; ++t) {
       sa.pos = buf.posrec + (size_t)e * N + (size_t)t * B;
@@ -903,6 +989,9 @@ int magpie_run_epochs(magpie_ctx* c, int n_epochs, int batch, uint64_t seed, con
   if (rc) return rc;
   const int N = c->n_pos;
   const int B = std::min(batch, N);
+  bool merged = false;
+  rc = prepare_merged(c, B, &merged);
+  if (rc) return rc;
   // workgroup order for the 128-point plans, whose gathers are bound by the patches'
   // L2 misses (measured no faster at m = 64)
   const bool xorder = c->m >= 128;
@@ -914,7 +1003,8 @@ int magpie_run_epochs(magpie_ctx* c, int n_epochs, int batch, uint64_t seed, con
     if (rc) return rc;
     const size_t off = (size_t)slot * ch * N;
     rc = launch_epochs(c, ne, B, (N + B - 1) / B, false,
-                       EpochBuffers{c->stage, c->posrec + off, c->inv + off, xorder ? c->posx + off : nullptr});
+                       EpochBuffers{c->stage, c->posrec + off, c->inv + off, xorder ? c->posx + off : nullptr,
+                                    merged ? c->stage2 : nullptr});
     if (rc) return rc;
     e0 += ne;
   }

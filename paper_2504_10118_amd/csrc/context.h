@@ -124,11 +124,14 @@ struct magpie_ctx {
   int4* tile_ent = nullptr;
   int tiles_x = 0, tiles_y = 0;
   int box_x0 = 0, box_y0 = 0, box_nx = 0, box_ny = 0;   // tiles some window reaches
-  int scan_r0 = 0, scan_r1 = 0;  // first and last object row some window covers
+  int scan_r0 = 0, scan_r1 = 0, scan_c0 = 0, scan_c1 = 0;  // first and last object row and column some window covers
   std::vector<int32_t> h_offs;
 
   float2* stage = nullptr;
   size_t stage_cap = 0;  // in float2
+  float2* z2 = nullptr;      // merged launches: the object's other buffer and the other
+  float2* stage2 = nullptr;  // staging (allocated on first use)
+  size_t stage2_cap = 0;
   float2* phase = nullptr;  // eq. (3.2) phase store [n_pos][m][m], natural order (flag MAGPIE_PHASE_RECYCLE)
   size_t phase_cap = 0;     // in float2
   float2* pnum = nullptr;   // probe step differences (allocated with the staging when the flag is on)
@@ -204,6 +207,7 @@ struct EpochBuffers {
   const int4* posrec;
   const int* inv;
   const int4* posx;   // nullable: records in workgroup order (step launches read them if given)
+  float2* stage2 = nullptr;   // given: merged launches, with this as the other staging
 };
 
 // noalloc.hip: resolves the device address of the no-allocation entry point's

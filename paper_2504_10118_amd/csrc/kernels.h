@@ -62,7 +62,8 @@ struct StepArgs {
 };
 
 struct AccumArgs {
-  float2* z;              // object, updated in place
+  float2* z;              // object, updated in place (merged launches: read)
+  float2* z_out;          // merged launches: the updated object
   int n_rows, n_cols, m;
   int tiles_x;            // number of tile columns of the object (ACC_TILE_W wide)
   int box_x0, box_y0;     // first tile column / row of the box of tiles any window reaches
@@ -115,6 +116,11 @@ hipError_t launch_step(int m, int rb, int mode, const StepArgs& a, hipStream_t s
                        hipEvent_t ev1 = nullptr);
 hipError_t launch_accumulate(const AccumArgs& a, int th, int n_tiles, hipStream_t s, hipEvent_t ev0 = nullptr,
                              hipEvent_t ev1 = nullptr);
+// Merged launch: a's steps, reading the object before the previous minibatch's update, and b:
+// that update (records b.pos, b.count of them, staged in b.stage) from b.z to b.z_out over
+// n_tiles tiles of qtile_rows(m, rb) rows.  a.count = 0: the update alone; b.count = 0: no update.
+bool merged_valid(int m, int rb);
+hipError_t launch_merged(int m, int rb, const StepArgs& a, const AccumArgs& b, hipStream_t s);
 // Largest minibatch the chained launch takes with plan (m, rb) and that many grids (0: none).
 int chain_limit(int m, int rb, int levels);
 hipError_t launch_chain(int m, int rb, const ChainArgs& q, hipStream_t s);

@@ -521,8 +521,13 @@ struct ChainGroup {
   bool active;   // false: the group repeats another group's position and records nothing
 };
 
-template <int M, int RBv, int MODE, bool COH = false, bool CHAIN = false>
-__device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const ChainGroup* cg = nullptr) {
+// PREV: the object read is the one before the previous minibatch's update, which the gather
+// applies to its window itself (the merged launch: see merged_kernel).
+constexpr int PREV_MAX = 256;   // positions of a minibatch in merged launches
+
+template <int M, int RBv, int MODE, bool COH = false, bool CHAIN = false, bool PREV = false>
+__device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const ChainGroup* cg = nullptr,
+                                          const AccumArgs* pv = nullptr) {
   constexpr int RB = Plan<M, RBv>::RB, RA = Plan<M, RBv>::RA;
   constexpr int TPB = M * RB, CB = RA / RB, P = M + Plan<M, RBv>::PAD;
   constexpr int LANES = TPB < 64 ? TPB : 64;
@@ -669,7 +674,74 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const
 #pragma unroll
     for (int j = 0; j < RA; ++j) dst[j * GR * P] = bload2p<ZPOL>(zr, gvo, j * gso);
   };
-  row_gather();
+  // The same with the previous minibatch's update: every wave finds its windows that
+  // overlap this one, 64 records at a time (one per lane), and adds their staged updates
+  // and weights at its pixels in processing order, two windows' loads in flight, as the
+  // accumulation does (the same sums and the same rounding).
+  auto row_gather_prev = [&]() {
+    const int r0 = tid / M, x = tid & (M - 1), lane = tid & 63;
+    const int gvo = (r0 * a.n_cols + x) * (int)sizeof(float2);
+    const int gso = GR * a.n_cols * (int)sizeof(float2);
+    float2 zz[RA];
+#pragma unroll
+    for (int j = 0; j < RA; ++j) zz[j] = bload2p<ZPOL>(zr, gvo, j * gso);
+    double nr[RA], ni[RA], dd[RA];
+#pragma unroll
+    for (int j = 0; j < RA; ++j) nr[j] = ni[j] = dd[j] = 0.0;
+    bool any = false;
+    for (int base = 0; base < pv->count; base += 64) {
+      int ry = -2 * M, rz = 0;
+      if (base + lane < pv->count) {
+        const int4 r = pv->pos[base + lane];
+        ry = r.y;
+        rz = r.z;
+      }
+      unsigned long long mask = __ballot(ry > off.x - M && ry < off.x + M && rz > off.y - M && rz < off.y + M);
+      any = any || mask != 0;
+      while (mask) {
+        float2 cv[2][RA];
+        float wv[2][RA];
+        bool ok[2][RA];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const bool have = mask != 0;
+          const int l = have ? __builtin_ctzll(mask) : 0;
+          mask &= mask - 1;
+          const int oy = off.x - __builtin_amdgcn_readlane(ry, l), ox = off.y - __builtin_amdgcn_readlane(rz, l);
+          const float2* st = pv->stage + (size_t)(base + l) * M * M;
+          const bool okx = have && (unsigned)(x + ox) < (unsigned)M;
+#pragma unroll
+          for (int j = 0; j < RA; ++j) {
+            const int yy = r0 + j * GR + oy;
+            ok[h][j] = okx && (unsigned)yy < (unsigned)M;
+            const int i = ok[h][j] ? yy * M + x + ox : 0;
+            cv[h][j] = st[i];
+            wv[h][j] = pv->w0f[i];
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int j = 0; j < RA; ++j)
+            if (ok[h][j]) {
+              nr[j] += (double)cv[h][j].x;
+              ni[j] += (double)cv[h][j].y;
+              dd[j] += (double)wv[h][j];
+            }
+      }
+    }
+    if (any) {
+#pragma unroll
+      for (int j = 0; j < RA; ++j)
+        if (dd[j] > 0.0)
+          zz[j] = make_float2((float)((double)zz[j].x + nr[j] / dd[j]), (float)((double)zz[j].y + ni[j] / dd[j]));
+    }
+    float2* const dst = T + r0 * P + x;
+#pragma unroll
+    for (int j = 0; j < RA; ++j) dst[j * GR * P] = zz[j];
+  };
+  if constexpr (PREV) row_gather_prev();
+  else row_gather();
   // The probe table (needed with the patch), the constants (parked in LDS
   // before the first transpose) and sqrt(d) (needed at the modulus) are issued
   // after the patch, in the order they are needed: loads return in issue
@@ -1367,7 +1439,8 @@ size_t step_lds_bytes(int m, int rb) {
 // COH: the staged updates and the object are read, and the object written, at
 // device scope (the work-queue launch, where workgroups on other XCDs produce
 // and consume them within the launch).
-template <int TH, bool COH = false>
+// OUT: the tile's new values go to a.z_out, its other pixels are copied there.
+template <int TH, bool COH = false, bool OUT = false>
 __device__ __forceinline__ void accumulate_body(const AccumArgs& a, const int b) {
   constexpr int NT = acc_threads(TH);
   constexpr int NW = NT / 64;
@@ -1494,13 +1567,16 @@ __device__ __forceinline__ void accumulate_body(const AccumArgs& a, const int b)
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
       const int Y = Y0 + 2 * NW * i;
+      if constexpr (OUT) {
+        if (Y < a.n_rows && !(dd[i] > 0.0)) a.z_out[(size_t)Y * a.n_cols + X] = zo[i];
+      }
       if (Y < a.n_rows && dd[i] > 0.0) {
         const float2 zn =
             make_float2((float)((double)zo[i].x + nr[i] / dd[i]), (float)((double)zo[i].y + ni[i] / dd[i]));
         if constexpr (COH)
           bstore2_device(zrs, zn, (int)((unsigned)(Y * a.n_cols + X) * (unsigned)sizeof(float2)), 0);
         else
-          a.z[(size_t)Y * a.n_cols + X] = zn;
+          (OUT ? a.z_out : a.z)[(size_t)Y * a.n_cols + X] = zn;
       }
     }
   }
@@ -1518,6 +1594,29 @@ __global__ __launch_bounds__(acc_threads(TH)) void accumulate_multi_kernel(const
   const int j = owner_of(prefix, n_ctx, b);
   const AccumArgs a = load_accum_args(descs + j);
   accumulate_body<TH>(a, b - prefix[j]);
+}
+
+// ---------------------------------------------------------------------------
+// Merged launch: the steps of a minibatch and the previous minibatch's update of the object
+// in one launch.  The object alternates between two buffers: the tile workgroups write the
+// updated object to the other one, and the step workgroups read the old one and apply the
+// previous minibatch's update to their own window (redundantly, with the same sums).  So
+// neither waits for the other, and a minibatch is one launch instead of two.  The work
+// repeated per window grows with the previous minibatch's windows that overlap it, so this
+// is for sparse minibatches of small windows (the host's rule states the measured line).
+// Steps first: they are the longer ones.
+// ---------------------------------------------------------------------------
+template <int M, int RBv>
+__global__ __launch_bounds__(M * RBv) void merged_kernel(StepArgs a, AccumArgs b) {
+  constexpr int TH = M * RBv / ACC_TILE_W;
+  if ((int)blockIdx.x < a.count) step_body<M, RBv, MODE_STEP, false, false, true>(a, (int)blockIdx.x, nullptr, &b);
+  else accumulate_body<TH, false, true>(b, (int)blockIdx.x - a.count);
+}
+
+// the last minibatch's update, out of place
+template <int TH>
+__global__ __launch_bounds__(acc_threads(TH)) void accumulate_out_kernel(AccumArgs a) {
+  accumulate_body<TH, false, true>(a, (int)blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1626,6 +1725,45 @@ static void launch_accumulate_t(const AccumArgs& a, int n_tiles, hipStream_t s, 
     hipExtLaunchKernelGGL(accumulate_kernel<TH>, dim3(n_tiles), dim3(acc_threads(TH)), 0, s, ev0, ev1, 0, a);
   else
     hipLaunchKernelGGL(accumulate_kernel<TH>, dim3(n_tiles), dim3(acc_threads(TH)), 0, s, a);
+}
+
+template <int M, int RB>
+constexpr bool merged_ok() {
+  return M <= 32 && M * RB >= 64 && M / RB <= 8;
+}
+
+template <int M, int RB>
+static hipError_t launch_merged_p(const StepArgs& a, const AccumArgs& b, hipStream_t s) {
+  if constexpr (!merged_ok<M, RB>()) {
+    return hipErrorInvalidValue;
+  } else {
+    if (a.count <= 0) {
+      if (b.n_tiles > 0)
+        hipLaunchKernelGGL(accumulate_out_kernel<M * RB / ACC_TILE_W>, dim3(b.n_tiles), dim3(M * RB), 0, s, b);
+      return hipGetLastError();
+    }
+    const size_t lds = lds_bytes_m<M, RB>();
+    const hipError_t e = hipFuncSetAttribute((const void*)merged_kernel<M, RB>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((merged_kernel<M, RB>), dim3(a.count + b.n_tiles), dim3(M * RB), lds, s, a, b);
+    return hipGetLastError();
+  }
+}
+
+hipError_t launch_merged(int m, int rb, const StepArgs& a, const AccumArgs& b, hipStream_t s) {
+  if (a.count > PREV_MAX || b.count > PREV_MAX || a.count < 0 || b.n_tiles < 0) return hipErrorInvalidValue;
+#define MG_LG(MM, RR) if (m == MM && rb == RR) return launch_merged_p<MM, RR>(a, b, s);
+  MG_FOR_EACH_PLAN(MG_LG)
+#undef MG_LG
+  return hipErrorInvalidValue;
+}
+
+bool merged_valid(int m, int rb) {
+#define MG_MV(MM, RR) if (m == MM && rb == RR) return merged_ok<MM, RR>();
+  MG_FOR_EACH_PLAN(MG_MV)
+#undef MG_MV
+  return false;
 }
 
 bool tile_valid(int th) { return th == 8 || th == 16 || th == 32; }
