@@ -16,7 +16,7 @@ namespace cnn {
 // ([chunk of four input channels][tap][co]), and frag, FRAG_VECS vectors of bf16 parts each
 // for backward-data; the first layer keeps its order (first[32][cin][9]); the head becomes
 // head[32][9][2] and, transposed and flipped, head_t[32][2][9].  With bf16 the
-// copies hold the weights rounded to bf16.  *wbad: nonzero if a square layer's weight is not finite.
+// copies hold the weights rounded to bf16.  *wbad: set where a square layer's weight is not finite (zero before the launch).
 constexpr int FWD_VECS = 8 * 9 * 32, FRAG_VECS = 18 * 3 * 64;
 struct PrepArgs {
   const float* p;               // parameter vector
@@ -80,9 +80,11 @@ int cmse_ip_blocks(int hw);
 hipError_t launch_cmse(const float* y, const float2* target, const float* mask, float2* rot, double2* ip_part,
                        float* dy, double* part, int batch, int hw, CmseHead* head, CmseResult* out, hipStream_t s);
 
-// Adam with bias corrections c1 = 1/(1-b1^t), c2 = 1/(1-b2^t).
+// Adam with bias corrections c1 = 1/(1-b1^t), c2 = 1/(1-b2^t); reset: moments to zero.  Both
+// clear *wbad (see PrepArgs) for the weight preparation that follows.
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr, float b1, float b2,
-                       float eps, float c1, float c2, hipStream_t s);
+                       float eps, float c1, float c2, int* wbad, hipStream_t s);
+hipError_t launch_adam_reset(float* m, float* v, int64_t n, int* wbad, hipStream_t s);
 
 // Network input map.  a2[i] = |Q_i|^2, out = ||Q||_2.
 hipError_t launch_probe_norm(const double2* q, int m, double* out, double* a2, hipStream_t s);

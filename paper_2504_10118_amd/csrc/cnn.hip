@@ -164,8 +164,9 @@ __global__ __launch_bounds__(1024) void cmse_loss_kernel(const double* __restric
 // ---------------------------------------------------------------------------
 __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
                             float* __restrict__ v, int64_t n, float lr, float b1, float b2, float eps, float c1,
-                            float c2) {
+                            float c2, int* __restrict__ wbad) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) *wbad = 0;
   if (i >= n) return;
   const float gi = g[i];
   const float mi = b1 * m[i] + (1.0f - b1) * gi;
@@ -487,11 +488,22 @@ hipError_t launch_cmse(const float* y, const float2* target, const float* mask, 
   return hipGetLastError();
 }
 
+__global__ void adam_reset_kernel(float* __restrict__ m, float* __restrict__ v, int64_t n, int* __restrict__ wbad) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) *wbad = 0;
+  if (i < n) m[i] = v[i] = 0.0f;
+}
+
+hipError_t launch_adam_reset(float* m, float* v, int64_t n, int* wbad, hipStream_t s) {
+  hipLaunchKernelGGL(adam_reset_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, m, v, n, wbad);
+  return hipGetLastError();
+}
+
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr, float b1, float b2,
-                       float eps, float c1, float c2, hipStream_t s) {
+                       float eps, float c1, float c2, int* wbad, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, g, m, v, n, lr, b1, b2, eps,
-                     c1, c2);
+                     c1, c2, wbad);
   return hipGetLastError();
 }
 

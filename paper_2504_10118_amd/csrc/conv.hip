@@ -257,9 +257,14 @@ __global__ __launch_bounds__(256, 2) void conv32_kernel(Conv32Args a) {
     st[k][0] = lo.x; st[k][1] = lo.y; st[k][2] = lo.z; st[k][3] = lo.w;
     st[k][4] = hi.x; st[k][5] = hi.y; st[k][6] = hi.z; st[k][7] = hi.w;
   }
-  uint4 wf[2][WS];   // the next step's fragments are loaded while the current one multiplies
+  // fragments are loaded PF steps ahead of their products: they come from L2 (54 KB per
+  // tile and wave, more than L1 holds)
+  constexpr int PF = 3;
+  uint4 wf[PF + 1][WS];
 #pragma unroll
-  for (int s = 0; s < WS; ++s) wf[0][s] = fr[s * 64];
+  for (int k = 0; k < PF; ++k)
+#pragma unroll
+    for (int s = 0; s < WS; ++s) wf[k][s] = fr[(k * WS + s) * 64];
   float probe = 0.0f;
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
@@ -284,25 +289,34 @@ __global__ __launch_bounds__(256, 2) void conv32_kernel(Conv32Args a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[k][r] = 0.0f;
   const int p0 = (4 * wave + (n >> 4)) * HALO + (n & 15);
-#pragma unroll
-  for (int step = 0; step < 18; ++step) {
+  // software pipeline, held by scheduling barriers: step i issues the weights of step i +
+  // PF and the LDS reads of step i + 1 before its own twelve products
+  uint4 x[2][2][3];
+  auto read = [&](int step, uint4 (&xs)[2][3]) {
     const int t = step >> 1, kh = step & 1;
-    if (step + 1 < 18) {
-#pragma unroll
-      for (int s = 0; s < WS; ++s) wf[(step + 1) & 1][s] = fr[((step + 1) * WS + s) * 64];
-    }
-    uint4 x[2][3];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const int p = p0 + (2 * k + t / 3) * HALO + t % 3;
       const int at = 4 * p + ((2 * kh + h) ^ ((p >> 2) & 3));
 #pragma unroll
-      for (int q = 0; q < 3; ++q) x[k][q] = T[q][at];
+      for (int q = 0; q < 3; ++q) xs[k][q] = T[q][at];
     }
+  };
+  read(0, x[0]);
+#pragma unroll
+  for (int step = 0; step < 18; ++step) {
+    if (step + PF < 18) {
+#pragma unroll
+      for (int s = 0; s < WS; ++s) wf[(step + PF) % (PF + 1)][s] = fr[((step + PF) * WS + s) * 64];
+    }
+    if (step + 1 < 18) read(step + 1, x[(step + 1) & 1]);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < Pairs<WS>::N; ++j)
 #pragma unroll
-      for (int k = 0; k < 2; ++k) acc[k] = mfma(wf[step & 1][Pairs<WS>::w[j]], x[k][Pairs<WS>::x[j]], acc[k]);
+      for (int k = 0; k < 2; ++k)
+        acc[k] = mfma(wf[step % (PF + 1)][Pairs<WS>::w[j]], x[step & 1][k][Pairs<WS>::x[j]], acc[k]);
+    __builtin_amdgcn_sched_barrier(0);
   }
 
   // lane (h, n) holds channels 8 q + 4 h + (0..3) of pixel n of each block
@@ -448,7 +462,7 @@ constexpr int GH = 8;                                  // tile rows
 constexpr int A_PITCH = GH * 32 + 16;                  // bytes per channel of a staged tile without halo
 constexpr int B_ROW = 48;                              // bytes per row of the halo tile (24 pixels, 18 used)
 constexpr int B_PITCH = (GH + 2) * B_ROW + 16;         // odd multiples of 16 bytes: no bank conflicts
-constexpr int SQ_LDS = 3 * C * (A_PITCH + B_PITCH);    // 74 KB: two workgroups per CU
+constexpr int SQ_LDS = 3 * C * (A_PITCH + B_PITCH);    // 74 KB: twice per CU
 
 struct Wgrad32Args {
   const float* in;      // [B][Hi][Wi][32]
@@ -457,10 +471,25 @@ struct Wgrad32Args {
   int H, W, tiles_x, tiles_per_sample, total_tiles, tiles_per_wg;
 };
 
-// dout of 8 pixels (channel c, row y, from x): FP32 values, 0 outside
+// n of 8 pixels (channel c, row y, from x): FP32 values, 0 outside
 template <bool UP>
 __device__ __forceinline__ void load8(const float* base, int H, int W, int y, int x, int c, int n, float* v) {
   const int Wi = UP ? W >> 1 : W;
+  if (n == 8 && y >= 0 && y < H && x >= 0 && x + 8 <= W) {   // inside: one address, constant offsets
+    const float* p = base + ((size_t)(UP ? y >> 1 : y) * Wi + (UP ? x >> 1 : x)) * C + c;
+    if (UP) {   // pixels x .. x + 7 of the doubled row: the low-resolution columns x / 2 .. (x + 7) / 2
+      const int odd = x & 1;
+      float q[5];
+#pragma unroll
+      for (int j = 0; j < 5; ++j) q[j] = (j < 4 || odd) ? p[j * C] : 0.0f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = odd ? q[(j + 1) >> 1] : q[j >> 1];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = p[j * C];
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int gx = x + j;
@@ -470,12 +499,14 @@ __device__ __forceinline__ void load8(const float* base, int H, int W, int y, in
   }
 }
 
+constexpr int SQ_THREADS = 768;
+
 // The scalar form of a run of tiles: element e of its part row, summed pixel by pixel.
 template <bool UP>
 __device__ __noinline__ void wgrad32_scalar(const Wgrad32Args& a, int t_begin, int t_end) {
   const int Hi = UP ? a.H >> 1 : a.H, Wi = UP ? a.W >> 1 : a.W;
   float* pr = a.part + (size_t)blockIdx.x * SQ_ROW;
-  for (int e = threadIdx.x; e < SQ_ROW; e += 256) {
+  for (int e = threadIdx.x; e < SQ_ROW; e += SQ_THREADS) {
     const int t = e >> 10, r = (e >> 6) & 15, lane = e & 63;
     const bool isb = e >= 9 * C * C;
     const int co = isb ? e - 9 * C * C : 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), ci = lane & 31;
@@ -500,116 +531,124 @@ __device__ __noinline__ void wgrad32_scalar(const Wgrad32Args& a, int t_begin, i
   }
 }
 
-// 32 x 32 channels: all nine taps of a K step from three row reads of the halo tile, the
-// horizontal shifts formed in registers (a wave holds the nine 32 x 32 sums, 144
-// registers).  Each wave takes two rows of the tile; the four waves' sums are added in
-// order through LDS at the end of the run.
+// 32 x 32 channels.  A workgroup of twelve waves per CU: wave (rg, dy) takes rows 2 rg and
+// 2 rg + 1 of the tile and the three taps of row dy, their horizontal shifts formed in
+// registers from one row read (three 32 x 32 sums, 48 registers).  Tiles are staged into
+// two LDS buffers in turn, the next tile's values loaded to registers before the current
+// one's products and split and stored after them, so that neither memory latency nor
+// the staging's arithmetic stands between the products.  (Four waves with all nine taps
+// each, 144 registers of sums, two workgroups per CU and one buffer each: 85 us at 32 samples
+// of 128 x 128, 110 through the upsampling; the products alone 23.)  The row groups' sums
+// are added in order through LDS at the end of the run.
+
 template <bool UP>
-__global__ __launch_bounds__(256, 2) void wgrad32_kernel(Wgrad32Args a) {
+__global__ __launch_bounds__(SQ_THREADS, 3) void wgrad32_kernel(Wgrad32Args a) {
   extern __shared__ uint4 smem[];
-  unsigned char* const As = reinterpret_cast<unsigned char*>(smem);         // dout
-  unsigned char* const Bs = As + 3 * C * A_PITCH;                           // in, with halo
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, n = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rg = wave / 3, dy = wave - 3 * rg;
   const int Hi = UP ? a.H >> 1 : a.H, Wi = UP ? a.W >> 1 : a.W;
-  f32x16 acc[9];
+  f32x16 acc[3];
 #pragma unroll
-  for (int t = 0; t < 9; ++t)
+  for (int t = 0; t < 3; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
   float bsum = 0.0f, probe = 0.0f;   // this thread's share of channel tid & 31's bias gradient
   const int t_begin = blockIdx.x * a.tiles_per_wg, t_end = min(a.total_tiles, t_begin + a.tiles_per_wg);
   const int sc = tid & 31, sg = tid >> 5;
-  for (int tile = t_begin; tile < t_end; ++tile) {
+  // Staging: thread tid takes channel sc of pixel groups sg (0 .. 23) and sg + 24: groups
+  // 0 .. 15 are the 8 x 2 of dout, 16 .. 45 the 10 x 3 of in (the third of 2 pixels).
+  float v[2][8];
+  auto load = [&](int tile) {
     const int b = tile / a.tiles_per_sample, tr = tile - b * a.tiles_per_sample;
     const int y0 = (tr / a.tiles_x) * GH, x0 = (tr % a.tiles_x) * 16;
     const float* inb = a.in + (size_t)b * Hi * Wi * C;
     const float* dob = a.dout + (size_t)b * a.H * a.W * C;
-    float va[2][8], vb[4][8];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {   // 16 groups of 8 pixels, 8 rows x 2
-      const int i = sg + 8 * k;
-      load8<false>(dob, a.H, a.W, y0 + (i >> 1), x0 + 8 * (i & 1), sc, 8, va[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {   // 30 groups, 10 rows x 3 (the third of 2 pixels)
-      const int i = sg + 8 * k, row = i / 3, gx = i - 3 * row;
-      load8<UP>(inb, a.H, a.W, i < 30 ? y0 + row - 1 : -1, x0 + 8 * gx - 1, sc, gx == 2 ? 2 : 8, vb[k]);
-    }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const int i = sg + 8 * k;
-      uint4 s[3];
-      split8(va[k], s, probe);
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-        *reinterpret_cast<uint4*>(As + (q * C + sc) * A_PITCH + 16 * i) = s[q];
-      bsum += ((va[k][0] + va[k][1]) + (va[k][2] + va[k][3])) + ((va[k][4] + va[k][5]) + (va[k][6] + va[k][7]));
+      const int i = sg + 24 * k, q = i - 16, row = q / 3, gx = q - 3 * row;
+      if (k == 0 && i < 16)
+        load8<false>(dob, a.H, a.W, y0 + (i >> 1), x0 + 8 * (i & 1), sc, 8, v[k]);
+      else
+        load8<UP>(inb, a.H, a.W, i < 46 ? y0 + row - 1 : -1, x0 + 8 * gx - 1, sc, gx == 2 ? 2 : 8, v[k]);
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = sg + 8 * k;
-      uint4 s[3];
-      split8(vb[k], s, probe);
-      if (i < 30)
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-          *reinterpret_cast<uint4*>(Bs + (q * C + sc) * B_PITCH + 16 * i) = s[q];
-    }
-    __syncthreads();
+  };
+  auto store = [&](int buf) {
+    unsigned char* const As = reinterpret_cast<unsigned char*>(smem) + buf * SQ_LDS;   // dout
+    unsigned char* const Bs = As + 3 * C * A_PITCH;                                    // in, with halo
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const int row = 2 * wave + k;
-      uint4 g[3];
+      const int i = sg + 24 * k;
+      uint4 s[3];
+      split8(v[k], s, probe);
+      if (k == 0 && i < 16) {
 #pragma unroll
-      for (int q = 0; q < 3; ++q)
-        g[q] = *reinterpret_cast<const uint4*>(As + (q * C + n) * A_PITCH + row * 32 + h * 16);
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(As + (q * C + sc) * A_PITCH + 16 * i) = s[q];
+        bsum += ((v[k][0] + v[k][1]) + (v[k][2] + v[k][3])) + ((v[k][4] + v[k][5]) + (v[k][6] + v[k][7]));
+      } else if (i < 46) {
 #pragma unroll
-      for (int dy = 0; dy < 3; ++dy) {
-        uint4 x[3][3];   // [dx][part]
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-          const unsigned char* src = Bs + (q * C + n) * B_PITCH + (row + dy) * B_ROW + h * 16;
-          const uint4 d = *reinterpret_cast<const uint4*>(src);
-          const uint32_t d4 = *reinterpret_cast<const uint32_t*>(src + 16);
-          x[0][q] = d;
-          x[1][q] = make_uint4(__builtin_amdgcn_alignbit(d.y, d.x, 16), __builtin_amdgcn_alignbit(d.z, d.y, 16),
-                               __builtin_amdgcn_alignbit(d.w, d.z, 16), __builtin_amdgcn_alignbit(d4, d.w, 16));
-          x[2][q] = make_uint4(d.y, d.z, d.w, d4);
-        }
-#pragma unroll
-        for (int j = 0; j < 6; ++j)
-#pragma unroll
-          for (int dx = 0; dx < 3; ++dx)
-            acc[3 * dy + dx] = mfma(g[Pairs<3>::w[j]], x[dx][Pairs<3>::x[j]], acc[3 * dy + dx]);
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(Bs + (q * C + sc) * B_PITCH + 16 * (i - 16)) = s[q];
       }
     }
+  };
+  if (t_begin < t_end) {
+    load(t_begin);
+    store(0);
+  }
+  __syncthreads();
+  for (int tile = t_begin; tile < t_end; ++tile) {
+    const int buf = (tile - t_begin) & 1;
+    const unsigned char* const As = reinterpret_cast<const unsigned char*>(smem) + buf * SQ_LDS;
+    const unsigned char* const Bs = As + 3 * C * A_PITCH;
+    const bool more = tile + 1 < t_end;
+    if (more) load(tile + 1);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int row = 2 * rg + k;
+      uint4 g[3], x[3][3];   // x: [dx][part]
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        g[q] = *reinterpret_cast<const uint4*>(As + (q * C + n) * A_PITCH + row * 32 + h * 16);
+        const unsigned char* src = Bs + (q * C + n) * B_PITCH + (row + dy) * B_ROW + h * 16;
+        const uint4 d = *reinterpret_cast<const uint4*>(src);
+        const uint32_t d4 = *reinterpret_cast<const uint32_t*>(src + 16);
+        x[0][q] = d;
+        x[1][q] = make_uint4(__builtin_amdgcn_alignbit(d.y, d.x, 16), __builtin_amdgcn_alignbit(d.z, d.y, 16),
+                             __builtin_amdgcn_alignbit(d.w, d.z, 16), __builtin_amdgcn_alignbit(d4, d.w, 16));
+        x[2][q] = make_uint4(d.y, d.z, d.w, d4);
+      }
+#pragma unroll
+      for (int j = 0; j < 6; ++j)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) acc[dx] = mfma(g[Pairs<3>::w[j]], x[dx][Pairs<3>::x[j]], acc[dx]);
+    }
+    if (more) store(buf ^ 1);
     __syncthreads();
   }
   if (__syncthreads_or(!(probe == 0.0f))) {
     wgrad32_scalar<UP>(a, t_begin, t_end);
     return;
   }
-  // the waves' sums in order, then the row: fragment order [t][r][lane], then the bias
+  // the row groups' sums in order, then the row: fragment order [t][r][lane], then the bias
   float* const red = reinterpret_cast<float*>(smem);
   for (int w = 0; w < 4; ++w) {
-    if (wave == w)
+    if (rg == w)
 #pragma unroll
-      for (int t = 0; t < 9; ++t)
+      for (int t = 0; t < 3; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          float* d = red + (t * 16 + r) * 64 + lane;
+          float* d = red + ((3 * dy + t) * 16 + r) * 64 + lane;
           *d = w ? *d + acc[t][r] : acc[t][r];
         }
     __syncthreads();
   }
   float* pr = a.part + (size_t)blockIdx.x * SQ_ROW;
-  for (int e = tid; e < 9 * C * C; e += 256) pr[e] = red[e];
+  for (int e = tid; e < 9 * C * C; e += SQ_THREADS) pr[e] = red[e];
   __syncthreads();
-  red[tid] = bsum;
+  red[tid] = bsum;   // zero in the threads that staged no dout
   __syncthreads();
   if (tid < C) {
     float s = red[tid];
-    for (int k = 1; k < 8; ++k) s += red[tid + 32 * k];
+    for (int k = 1; k < 16; ++k) s += red[tid + 32 * k];
     pr[9 * C * C + tid] = s;
   }
 }
@@ -656,13 +695,53 @@ __device__ __noinline__ void wgrad_thin_scalar(const WgradThinArgs& a, int t_beg
   }
 }
 
+// Bias gradient of the head: its phase channel's sum is zero but for rounding (see the
+// top of this file), so the order is fixed for good: runs of 16 x 16 tiles pixel by pixel,
+// the runs in four strided sets.  A workgroup stages a tile's two planes and two lanes add
+// them up (256 dependent additions per tile); these workgroups come behind the weight
+// gradient's own, whose memory traffic hides the chains.
+struct HeadBias {
+  float* part;   // [workgroups][2]
+  int first, tiles_x, tiles_per_sample, total_tiles, tiles_per_wg;   // first: of these workgroups
+};
+__device__ void head_bias(const float* __restrict__ dy, const HeadBias& hb, int H, int W, float4 (*v)[CT * CT / 4]) {
+  const int wg = blockIdx.x - hb.first;
+  const int t_begin = wg * hb.tiles_per_wg, t_end = min(hb.total_tiles, t_begin + hb.tiles_per_wg);
+  float acc = 0.0f;
+  for (int tile = t_begin; tile < t_end; ++tile) {
+    const int b = tile / hb.tiles_per_sample, tr = tile - b * hb.tiles_per_sample;
+    const int y = (tr / hb.tiles_x) * CT + threadIdx.x / CT, x = (tr % hb.tiles_x) * CT + threadIdx.x % CT;
+    const bool in = y < H && x < W;
+    const float* src = dy + ((size_t)b * 2 * H + y) * W + x;
+    const float d0 = in ? src[0] : 0.0f, d1 = in ? src[(size_t)H * W] : 0.0f;
+    __syncthreads();
+    reinterpret_cast<float*>(v[0])[threadIdx.x] = d0;
+    reinterpret_cast<float*>(v[1])[threadIdx.x] = d1;
+    __syncthreads();
+    if (threadIdx.x < 2)
+#pragma unroll 8
+      for (int i = 0; i < CT * CT / 4; ++i) {
+        const float4 q = v[threadIdx.x][i];
+        acc += q.x;
+        acc += q.y;
+        acc += q.z;
+        acc += q.w;
+      }
+  }
+  if (threadIdx.x < 2) hb.part[2 * wg + threadIdx.x] = acc;
+}
+
 template <int CN, bool FLIP>
-__global__ __launch_bounds__(256) void wgrad_thin_kernel(WgradThinArgs a) {
+__global__ __launch_bounds__(256) void wgrad_thin_kernel(WgradThinArgs a, HeadBias hb) {
   constexpr int NB = (9 * CN + 31) / 32, ROW = thin_row(CN, FLIP);
   constexpr int COPY = (GH + 2) * 32;                            // one shifted copy: 10 rows of 16 pixels
   __shared__ uint4 As4[3 * C * A_PITCH / 16];
   __shared__ uint4 Ts4[3 * CN * 3 * COPY / 16];
   __shared__ float red[NB * C * C > 256 ? NB * C * C : 256];
+  if (FLIP && (int)blockIdx.x >= hb.first) {
+    head_bias(a.thin, hb, a.H, a.W, reinterpret_cast<float4 (*)[CT * CT / 4]>(As4));
+    return;
+  }
   unsigned char* const As = reinterpret_cast<unsigned char*>(As4);
   unsigned char* const Ts = reinterpret_cast<unsigned char*>(Ts4);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
@@ -770,61 +849,27 @@ __global__ __launch_bounds__(256) void wgrad_thin_kernel(WgradThinArgs a) {
   }
 }
 
-// Bias gradient of the head: its phase channel's sum is zero but for rounding (see the
-// top of this file), so the order is fixed for good: runs of 16 x 16 tiles pixel by pixel,
-// the runs in four strided sets.  One workgroup per run stages a tile's two planes and
-// two lanes add them up (256 dependent additions per tile).
-__global__ __launch_bounds__(256) void head_bias_kernel(const float* __restrict__ dy, float* __restrict__ part, int H,
-                                                        int W, int tiles_x, int tiles_per_sample, int total_tiles,
-                                                        int tiles_per_wg) {
-  __shared__ float4 v[2][CT * CT / 4];
-  const int t_begin = blockIdx.x * tiles_per_wg, t_end = min(total_tiles, t_begin + tiles_per_wg);
-  float acc = 0.0f;
-  for (int tile = t_begin; tile < t_end; ++tile) {
-    const int b = tile / tiles_per_sample, tr = tile - b * tiles_per_sample;
-    const int y = (tr / tiles_x) * CT + threadIdx.x / CT, x = (tr % tiles_x) * CT + threadIdx.x % CT;
-    const bool in = y < H && x < W;
-    const float* src = dy + ((size_t)b * 2 * H + y) * W + x;
-    const float d0 = in ? src[0] : 0.0f, d1 = in ? src[(size_t)H * W] : 0.0f;
-    __syncthreads();
-    reinterpret_cast<float*>(v[0])[threadIdx.x] = d0;
-    reinterpret_cast<float*>(v[1])[threadIdx.x] = d1;
-    __syncthreads();
-    if (threadIdx.x < 2)
-#pragma unroll 8
-      for (int i = 0; i < CT * CT / 4; ++i) {
-        const float4 q = v[threadIdx.x][i];
-        acc += q.x;
-        acc += q.y;
-        acc += q.z;
-        acc += q.w;
-      }
-  }
-  if (threadIdx.x < 2) part[2 * blockIdx.x + threadIdx.x] = acc;
-}
-
-__global__ __launch_bounds__(64) void head_bias_sum_kernel(const float* __restrict__ part, int n_rows,
-                                                           float* __restrict__ grad) {
-  __shared__ float red[4][2];
-  const int j = threadIdx.x & 1, s = threadIdx.x >> 1;
-  if (s < 4) {
-    float acc = 0.0f;
-#pragma unroll 8
-    for (int r = s; r < n_rows; r += 4) acc += part[2 * r + j];
-    red[s][j] = acc;
-  }
-  __syncthreads();
-  if (s == 0) grad[j] = ((red[0][j] + red[1][j]) + red[2][j]) + red[3][j];
-}
-
 // grad = sum of the part rows, from fragment order to the layer's parameter order:
 // column e of a row is (t, r, lane) of a square layer, (block, r, lane) of a thin one,
 // then (not the head) the bias.  64 columns per workgroup, 16 strided row sets combined in order.
 // KIND 0: square; 1: first layer (CN input channels); 2: head (CN output channels).
 template <int KIND>
 __global__ __launch_bounds__(1024) void rows_sum_kernel(const float* __restrict__ part, int n_rows, int row_len,
-                                                        int n_w, int cn, float* __restrict__ grad) {
+                                                        int n_w, int cn, float* __restrict__ grad,
+                                                        const float* __restrict__ bias_part, int bias_rows) {
   __shared__ float red[16][64];
+  if (KIND == 2 && blockIdx.x == gridDim.x - 1) {   // the head's bias, see head_bias
+    const int j = threadIdx.x & 1, q = threadIdx.x >> 1;
+    if (q < 4) {
+      float acc = 0.0f;
+#pragma unroll 16
+      for (int r = q; r < bias_rows; r += 4) acc += bias_part[2 * r + j];
+      red[q][j] = acc;
+    }
+    __syncthreads();
+    if (q == 0) grad[2 * C * 9 + j] = ((red[0][j] + red[1][j]) + red[2][j]) + red[3][j];
+    return;
+  }
   const int jj = threadIdx.x & 63, s = threadIdx.x >> 6;
   const int e = blockIdx.x * 64 + jj;
   float acc = 0.0f;
@@ -902,7 +947,6 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
   if (bad) atomicOr(a.wbad, 1);
 }
 
-__global__ void clear_flag_kernel(int* p) { *p = 0; }
 
 template <int MODE>
 hipError_t conv32_t(bool bf16, const Conv32Args& a, int batch, hipStream_t s) {
@@ -915,12 +959,12 @@ hipError_t conv32_t(bool bf16, const Conv32Args& a, int batch, hipStream_t s) {
 struct Tiling {
   int tiles_x, per_sample, total, per_wg, wgs;
 };
-Tiling wgrad_tiling(int batch, int H, int W) {
+Tiling wgrad_tiling(int batch, int H, int W, int most) {
   Tiling t;
   t.tiles_x = (W + 15) / 16;
   t.per_sample = t.tiles_x * ((H + GH - 1) / GH);
   t.total = batch * t.per_sample;
-  t.per_wg = (t.total + WGRAD_MAX_WORKGROUPS - 1) / WGRAD_MAX_WORKGROUPS;
+  t.per_wg = (t.total + most - 1) / most;
   t.wgs = (t.total + t.per_wg - 1) / t.per_wg;
   return t;
 }
@@ -931,7 +975,6 @@ Tiling wgrad_tiling(int batch, int H, int W) {
 // Launchers
 // ---------------------------------------------------------------------------
 hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, s, a.wbad);
   const int n = 3 * 8 * 9 * C + 3 * 18 * 64 + C * a.cin * 9 + 2 * C * 9;
   hipLaunchKernelGGL(prep_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a);
   return hipGetLastError();
@@ -988,48 +1031,51 @@ hipError_t launch_conv_head_backward(const float* dy, const float* w, float* out
 hipError_t launch_wgrad32(bool up, const float* in, const float* dout, float* part, float* grad, int batch, int H,
                           int W, hipStream_t s) {
   if (batch < 1 || H < 1 || W < 1 || (up && ((H | W) & 1))) return hipErrorInvalidValue;
-  const Tiling t = wgrad_tiling(batch, H, W);
+  const Tiling t = wgrad_tiling(batch, H, W, WGRAD_MAX_WORKGROUPS / 2);   // one workgroup per CU
   const Wgrad32Args a{in, dout, part, H, W, t.tiles_x, t.per_sample, t.total, t.per_wg};
   const void* k = up ? (const void*)wgrad32_kernel<true> : (const void*)wgrad32_kernel<false>;
-  const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SQ_LDS);
+  const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * SQ_LDS);
   if (e != hipSuccess) return e;
-  if (up) hipLaunchKernelGGL(wgrad32_kernel<true>, dim3(t.wgs), dim3(256), SQ_LDS, s, a);
-  else hipLaunchKernelGGL(wgrad32_kernel<false>, dim3(t.wgs), dim3(256), SQ_LDS, s, a);
+  if (up) hipLaunchKernelGGL(wgrad32_kernel<true>, dim3(t.wgs), dim3(SQ_THREADS), 2 * SQ_LDS, s, a);
+  else hipLaunchKernelGGL(wgrad32_kernel<false>, dim3(t.wgs), dim3(SQ_THREADS), 2 * SQ_LDS, s, a);
   hipLaunchKernelGGL(rows_sum_kernel<0>, dim3((SQ_ROW + 63) / 64), dim3(1024), 0, s, (const float*)part, t.wgs, SQ_ROW,
-                     9 * C * C, C, grad);
+                     9 * C * C, C, grad, (const float*)nullptr, 0);
   return hipGetLastError();
 }
 
 hipError_t launch_wgrad_first(int ci, const float* in, const float* dout, float* part, float* grad, int batch, int H,
                               int W, hipStream_t s) {
   if (batch < 1 || H < 1 || W < 1) return hipErrorInvalidValue;
-  const Tiling t = wgrad_tiling(batch, H, W);
+  const Tiling t = wgrad_tiling(batch, H, W, WGRAD_MAX_WORKGROUPS);
   const WgradThinArgs a{dout, in, part, H, W, t.tiles_x, t.per_sample, t.total, t.per_wg};
   const int row = thin_row(ci, false);
 #define CNN_WF(CI) \
-  if (ci == CI) hipLaunchKernelGGL((wgrad_thin_kernel<CI, false>), dim3(t.wgs), dim3(256), 0, s, a);
+  if (ci == CI) hipLaunchKernelGGL((wgrad_thin_kernel<CI, false>), dim3(t.wgs), dim3(256), 0, s, a, HeadBias{});
   CNN_WF(1) else CNN_WF(3) else CNN_WF(4) else return hipErrorInvalidValue;
 #undef CNN_WF
   hipLaunchKernelGGL(rows_sum_kernel<1>, dim3((row + 63) / 64), dim3(1024), 0, s, (const float*)part, t.wgs, row,
-                     row - C, ci, grad);
+                     row - C, ci, grad, (const float*)nullptr, 0);
   return hipGetLastError();
 }
 
 hipError_t launch_wgrad_head(const float* in, const float* dy, float* part, float* grad, int batch, int H, int W,
                              hipStream_t s) {
   if (batch < 1 || H < 1 || W < 1) return hipErrorInvalidValue;
-  const Tiling t = wgrad_tiling(batch, H, W);
+  const Tiling t = wgrad_tiling(batch, H, W, WGRAD_MAX_WORKGROUPS);
   const WgradThinArgs a{in, dy, part, H, W, t.tiles_x, t.per_sample, t.total, t.per_wg};
   const int row = thin_row(2, true);
-  hipLaunchKernelGGL((wgrad_thin_kernel<2, true>), dim3(t.wgs), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(rows_sum_kernel<2>, dim3((row + 63) / 64), dim3(1024), 0, s, (const float*)part, t.wgs, row, row,
-                     2, grad);
-  // the bias: 16 x 16 tiles, behind the rows just used (at most 512 of 1024 floats)
-  const int tx = (W + CT - 1) / CT, per_sample = tx * ((H + CT - 1) / CT), total = batch * per_sample;
-  const int per = (total + WGRAD_MAX_WORKGROUPS - 1) / WGRAD_MAX_WORKGROUPS, wgs = (total + per - 1) / per;
-  float* const bp = part + (size_t)WGRAD_MAX_WORKGROUPS * row;
-  hipLaunchKernelGGL(head_bias_kernel, dim3(wgs), dim3(256), 0, s, dy, bp, H, W, tx, per_sample, total, per);
-  hipLaunchKernelGGL(head_bias_sum_kernel, dim3(1), dim3(64), 0, s, (const float*)bp, wgs, grad + 2 * C * 9);
+  // the bias: 16 x 16 tiles, its rows behind the weights' (at most 512 of 1024 floats)
+  HeadBias hb;
+  hb.part = part + (size_t)WGRAD_MAX_WORKGROUPS * row;
+  hb.first = t.wgs;
+  hb.tiles_x = (W + CT - 1) / CT;
+  hb.tiles_per_sample = hb.tiles_x * ((H + CT - 1) / CT);
+  hb.total_tiles = batch * hb.tiles_per_sample;
+  hb.tiles_per_wg = (hb.total_tiles + WGRAD_MAX_WORKGROUPS - 1) / WGRAD_MAX_WORKGROUPS;
+  const int wgs = (hb.total_tiles + hb.tiles_per_wg - 1) / hb.tiles_per_wg;
+  hipLaunchKernelGGL((wgrad_thin_kernel<2, true>), dim3(t.wgs + wgs), dim3(256), 0, s, a, hb);
+  hipLaunchKernelGGL(rows_sum_kernel<2>, dim3((row + 63) / 64 + 1), dim3(1024), 0, s, (const float*)part, t.wgs, row,
+                     row, 2, grad, (const float*)hb.part, wgs);
   return hipGetLastError();
 }
 

@@ -233,8 +233,7 @@ int magpie_cnn_create(magpie_cnn** out, int in_ch, int width, int side, int max_
     return rc;
   }
   if (hipMemsetAsync(net->p, 0, net->n * sizeof(float), net->stream) != hipSuccess ||
-      hipMemsetAsync(net->m, 0, net->n * sizeof(float), net->stream) != hipSuccess ||
-      hipMemsetAsync(net->v, 0, net->n * sizeof(float), net->stream) != hipSuccess ||
+      cnn::launch_adam_reset(net->m, net->v, net->n, net->wbad, net->stream) != hipSuccess ||
       hipMemsetAsync(net->g, 0, net->n * sizeof(float), net->stream) != hipSuccess) {
     magpie_cnn_destroy(net);
     return fail(MAGPIE_ERR_HIP, "parameter init failed");
@@ -301,8 +300,7 @@ int magpie_cnn_set_params(magpie_cnn* net, const float* params, int on_device) {
   }
   rc = copy_in(net->p, params, net->n * sizeof(float), on_device, net->stream);
   if (rc) return rc;
-  MG_HIP(hipMemsetAsync(net->m, 0, net->n * sizeof(float), net->stream));
-  MG_HIP(hipMemsetAsync(net->v, 0, net->n * sizeof(float), net->stream));
+  MG_HIP(cnn::launch_adam_reset(net->m, net->v, net->n, net->wbad, net->stream));
   net->t = 0;
   return prep_weights(net);
 }
@@ -400,7 +398,7 @@ int magpie_cnn_adam_step(magpie_cnn* net, float lr, float beta1, float beta2, fl
   const double c1 = 1.0 / (1.0 - std::pow((double)beta1, (double)net->t));
   const double c2 = 1.0 / (1.0 - std::pow((double)beta2, (double)net->t));
   MG_HIP(cnn::launch_adam(net->p, net->g, net->m, net->v, net->n, lr, beta1, beta2, eps, (float)c1, (float)c2,
-                          net->stream));
+                          net->wbad, net->stream));
   return prep_weights(net);
 }
 
