@@ -1969,10 +1969,13 @@ __global__ __launch_bounds__(256) void level_constants_kernel(LevelArgs a) {
     return;
   }
   double mx = 0.0;
-#pragma unroll 8
-  for (int e = tid; e < m * m; e += 256) {
-    const double2 q = a.q64[e];
-    mx = fmax(mx, q.x * q.x + q.y * q.y);
+#pragma unroll 1
+  for (int e0 = tid; e0 < m * m; e0 += 256 * 16) {
+    double2 q[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) q[i] = e0 + 256 * i < m * m ? a.q64[e0 + 256 * i] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) mx = fmax(mx, q[i].x * q[i].x + q[i].y * q[i].y);
   }
   red[tid] = mx;
   __syncthreads();
@@ -2103,13 +2106,20 @@ __global__ __launch_bounds__(256) void probe_spectrum_cols_kernel(const double2*
   const int ky = tid / RB, kx = (tid % RB) * CB + j / RB + RA * (j % RB);
   double re = 0.0, im = 0.0, l1 = 0.0;
   int k = 0;
-#pragma unroll 8
-  for (int y = 0; y < M; ++y) {
-    const double2 w = W[k], t = tmp[y * M + kx];
-    re += t.x * w.x - t.y * w.y;
-    im += t.x * w.y + t.y * w.x;
-    l1 += l1s[y];
-    k = (k + ky) & (M - 1);
+  constexpr int YB = M < 32 ? M : 32;   // rows whose loads are in flight together
+#pragma unroll 1
+  for (int y0 = 0; y0 < M; y0 += YB) {
+    double2 t[YB];
+#pragma unroll
+    for (int y = 0; y < YB; ++y) t[y] = tmp[(y0 + y) * M + kx];
+#pragma unroll
+    for (int y = 0; y < YB; ++y) {
+      const double2 w = W[k];
+      re += t[y].x * w.x - t[y].y * w.y;
+      im += t[y].x * w.y + t[y].y * w.x;
+      l1 += l1s[y0 + y];
+      k = (k + ky) & (M - 1);
+    }
   }
   const double bound = 4.0 * M * 0x1p-52 * l1;
   qspec[e] = hypot(re, im) <= bound ? make_float2(0.0f, 0.0f) : make_float2((float)re, (float)im);
@@ -2344,23 +2354,37 @@ __global__ __launch_bounds__(256) void probe_partial_kernel(const float2* __rest
   }
 }
 
-// Pass 2: the chunks in order, then the probe step where the denominator is positive.
+// Pass 2: the chunks in order, then the probe step where the denominator is positive.  16
+// chunks' loads are in flight together.
 __global__ __launch_bounds__(64) void probe_apply_kernel(int mm, int chunks, double beta,
                                                          const double* __restrict__ part, double2* __restrict__ q64) {
   const int p = blockIdx.x * 64 + threadIdx.x;
   if (p >= mm) return;
+  const double* mxs = part + (size_t)chunks * 3 * mm;
+  double2 qq = q64[p];
   double nr = 0.0, ni = 0.0, dd = 0.0, mx = 0.0;
-#pragma unroll 8
-  for (int c = 0; c < chunks; ++c) {
-    const double* q = part + (size_t)c * 3 * mm;
-    nr += q[p];
-    ni += q[mm + p];
-    dd += q[2 * mm + p];
-    mx += part[(size_t)chunks * 3 * mm + c];
+  for (int c0 = 0; c0 < chunks; c0 += 16) {
+    double v[16][4];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int c = min(c0 + i, chunks - 1);
+      const double* q = part + (size_t)c * 3 * mm;
+      v[i][0] = q[p];
+      v[i][1] = q[mm + p];
+      v[i][2] = q[2 * mm + p];
+      v[i][3] = mxs[c];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (c0 + i < chunks) {
+        nr += v[i][0];
+        ni += v[i][1];
+        dd += v[i][2];
+        mx += v[i][3];
+      }
   }
   dd += beta * mx;
   if (dd > 0.0) {
-    double2 qq = q64[p];
     qq.x += nr / dd;
     qq.y += ni / dd;
     q64[p] = qq;
