@@ -12,18 +12,18 @@ namespace cnn {
 // Activations of the hidden layers are channels-last, [B][H][W][32]; the network's
 // input, output and output gradient are planes, [B][c][H][W].
 
-// Compute copies of the weights.  Square (32 -> 32) layers: fwd, FWD_VECS float4 each
-// ([chunk of four input channels][tap][co]), and frag, FRAG_VECS vectors of bf16 parts each
+// Compute copies of the weights.  Square (32 -> 32) layers: fwd, FWD_VECS float2 each
+// (the products' operands in lane order, see prep_kernel), and frag, FRAG_VECS vectors of bf16 parts each
 // for backward-data; the first layer keeps its order (first[32][cin][9]); the head becomes
 // head[32][9][2] and, transposed and flipped, head_t[32][2][9].  With bf16 the
 // copies hold the weights rounded to bf16.  *wbad: set where a square layer's weight is not finite (zero before the launch).
-constexpr int FWD_VECS = 8 * 9 * 32, FRAG_VECS = 18 * 3 * 64;
+constexpr int FWD_VECS = 4 * 9 * 2 * 64, FRAG_VECS = 18 * 3 * 64;
 struct PrepArgs {
   const float* p;               // parameter vector
   int64_t off_sq[3], off_first, off_head;   // offsets of the layers' weights
   int cin;
   bool bf16;
-  float4* fwd;                  // [3][FWD_VECS]
+  float2* fwd;                  // [3][FWD_VECS]
   uint4* frag;                  // [3][FRAG_VECS]
   float *first, *head, *head_t;
   int* wbad;
@@ -32,7 +32,7 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s);
 
 // Square layer, forward: out = relu(conv3x3(in) + bias) with zero padding 1 (H, W: the
 // output's size; up: in has half of it and is read through nearest 2x upsampling).
-hipError_t launch_conv32(bool up, const float* in, const float4* w, const float* bias, float* out, int batch, int H,
+hipError_t launch_conv32(bool up, const float* in, const float2* w, const float* bias, float* out, int batch, int H,
                          int W, hipStream_t s);
 // Square layer, backward-data of in (H x W): zero where omask <= 0; up: the sum of each
 // 2 x 2 block, out and omask of half the size.  w: the layer's weights as stored.

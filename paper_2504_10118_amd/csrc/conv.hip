@@ -4,11 +4,11 @@
 // network's input, output and output gradient keep their [B][c][H][W] planes).
 //
 // Forward: every output is the FP32 FMA chain over (input channel, tap) from the bias,
-// the 32 -> 32 layers as v_mfma_f32_32x32x1_2b_f32 products: with K = 1 each is one
-// rounding per output, so the matrix cores give the chain's own bits (tested), at twice
-// the rate of unpacked FP32 VALU.  The order is part of the interface: the phase output's
-// bias has gradient zero by the loss's phase alignment, so what Adam makes of it is this
-// rounding, and another summation would send the bias elsewhere.
+// the 32 -> 32 layers as v_mfma_f32_16x16x4_f32 products: the instruction adds its four
+// products one after another, k ascending, one rounding each, so the matrix cores give the
+// chain's own bits (tested), at twice the rate of unpacked FP32 VALU.  The order is part of
+// the interface: the phase output's bias has gradient zero by the loss's phase alignment, so
+// what Adam makes of it is this rounding, and another summation would send the bias elsewhere.
 //
 // Backward: the 32 -> 32 products run as v_mfma_f32_32x32x16_bf16 of FP32 operands split
 // exactly into three bf16 parts by truncation, x = x0 + x1 + x2 (8 + 8 + 8 significant
@@ -22,6 +22,7 @@
 // All reductions run in a fixed order: results are bitwise reproducible.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "cmath.h"
@@ -37,8 +38,8 @@ constexpr int HALO = CT + 2;
 constexpr int HP = HALO * HALO;     // staged pixels of a tile
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x32 __attribute__((ext_vector_type(32)));
 
 __device__ __forceinline__ f32x16 mfma(uint4 a, uint4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
@@ -73,83 +74,154 @@ __device__ __forceinline__ float round_bf16(float x) {
 // ---------------------------------------------------------------------------
 // 32 -> 32 convolution, forward
 // ---------------------------------------------------------------------------
-// One workgroup of four waves per 16 x 16 output tile.  The 18 x 18 x 32 halo is staged
-// as it is (128 bytes per pixel, its 16-byte chunks rotated by the pixel index so that a
-// read of 16 neighbouring pixels covers all banks), 41 KB: three workgroups per CU.  A wave
-// owns four rows, two blocks of 32 pixels (its lane halves), and per chunk of four input
-// channels reads nine taps of its pixels from LDS and the chunk's 9 x 32 x 4 weights from
-// memory (36 KB in all, shared through L1; the next chunk's are loaded while the current 36
-// products of 64 cycles run).  Bound: 2 * 9 * 32 * 32 flops per pixel at the FP32 matrix
-// rate, 61 us for 32 samples of 128 x 128.
-template <bool UP>
+// Tiles of 16 x 4 P output pixels, four waves, each wave P rows.  The chain of an output runs
+// over channels, taps within a channel: of the 36 steps of four channels, product p takes 4 p to
+// 4 p + 3, one per lane group, so every lane holds operands of its own tap and channel (with
+// K = 1 products the halves of a wave held the same weights, twice the reads per product).
+// The halo is staged with the channels c, c + 4, c + 8, ... of a pixel side by side, 136 bytes
+// per pixel: one 8-byte read gives the operand of the same product of two chunks of four
+// channels, and 16 neighbouring pixels cover all banks (two of a lane's taps read 32 pairs).
+// A weight or pixel register is loaded for the next two chunks right behind its last product
+// (held there by scheduling barriers), 72 P products ahead of its use.
+//
+// P = 4: 512 workgroups (two per CU) walk the tiles, the next tile's halo on its way into
+// registers while the products run.  Bound: 2 * 9 * 32 * 32 flops per pixel at the FP32
+// matrix rate, 61 us at 2.4 GHz for 32 samples of 128 x 128, 69 us at the 2.1 GHz that the
+// clock is at when a few such launches follow an idle time.  110 -> 88 us (a tile per
+// workgroup with the halo loaded and stored piece by piece took as long to stage under the
+// other workgroup's products as to multiply).
+// P = 1, 2: where the 16 x 16 tiles would leave CUs idle, one tile of 4 or 8 rows per
+// workgroup: up to 64 tiles 16 x 16 (one 128 x 128 sample) 17.0 -> 6.6 us with P = 1, up to
+// 128 tiles 17.7 -> 8.8 us with P = 2 (P = 1: 11.8, P = 4: 13.3); above, P = 4 is faster (192 tiles:
+// 14.0, with P = 2 16.5).
+constexpr int FWD_TAPS = 9 * 2 * 64;   // float2 of the weights of two chunks
+
+template <bool UP, int P>
 __global__ __launch_bounds__(256, 2) void conv32_forward_kernel(const float* __restrict__ in,
-                                                                const float4* __restrict__ w,
+                                                                const float2* __restrict__ w,
                                                                 const float* __restrict__ bias,
-                                                                float* __restrict__ out, int H, int W) {
-  __shared__ float4 T[HP * 8];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
-  const int x0 = blockIdx.x * CT, y0 = blockIdx.y * CT, b = blockIdx.z;
+                                                                float* __restrict__ out, int H, int W, int tx, int ty,
+                                                                int total) {
+  constexpr bool LOOP = P == 4;
+  constexpr int TH = 4 * P, HR = (TH + 2) * HALO, LP = 34, NL = (HR * 8 + 255) / 256;
+  __shared__ float2 T2[HR * LP / 2];
+  float* T = reinterpret_cast<float*>(T2);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, kk = lane >> 4;
   const int Hi = UP ? H >> 1 : H, Wi = UP ? W >> 1 : W;
-  const float* inb = in + (size_t)b * Hi * Wi * C;
-  // weights [chunk][tap][co] of four input channels; both lane halves hold the same
-  const float4* wl = w + n;
-  float4 wc[9], wn[9];
+  const mg::rsrc_t wrs = mg::make_rsrc(w, 4 * FWD_TAPS * sizeof(float2));
+  int wo = lane * (int)sizeof(float2);
+  float2 wr[9][2];
 #pragma unroll
-  for (int t = 0; t < 9; ++t) wn[t] = wl[t * C];
+  for (int p = 0; p < 9; ++p)
 #pragma unroll
-  for (int k = 0; k < (HP * 8 + 255) / 256; ++k) {
-    const int i = tid + 256 * k, p = i >> 3, yy = p / HALO, xx = p - yy * HALO;
-    const int gy = y0 + yy - 1, gx = x0 + xx - 1;
-    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (i < HP * 8) {
-      if (gy >= 0 && gy < H && gx >= 0 && gx < W)
-        v = reinterpret_cast<const float4*>(inb + ((size_t)(UP ? gy >> 1 : gy) * Wi + (UP ? gx >> 1 : gx)) * C)[i & 7];
-      T[8 * p + ((i & 7) ^ ((p >> 1) & 7))] = v;
-    }
+    for (int cb = 0; cb < 2; ++cb) wr[p][cb] = mg::bload2(wrs, wo, (p * 2 + cb) * 512);
+  // staged 16-byte piece k of this thread: its offset from the tile's first source pixel
+  int vo[NL];
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    const int p = (tid + 256 * k) >> 3, yy = p / HALO - 1, xx = p % HALO - 1;
+    vo[k] = ((UP ? yy >> 1 : yy) * Wi + (UP ? xx >> 1 : xx)) * (C * 4) + (tid & 7) * 16;
   }
-  // lane (h, n) holds channels 8 q + 4 h + (0..3) of pixel n of both blocks
-  f32x32 acc;
+  float4 hv[NL];
+  auto load = [&](int q) {
+    const int b = q / (tx * ty), r = q - b * (tx * ty), ry = r / tx, y0 = ry * TH, x0 = (r - ry * tx) * CT;
+    // the resource covers the tile's source rows that exist: a row above the image is a negative
+    // offset, one below lies past the end, and both read as zero
+    const int ys = UP ? y0 >> 1 : y0, yb = max(ys - 1, 0), rows = min(Hi - yb, (UP ? TH / 2 : TH) + 2);
+    const mg::rsrc_t rs = mg::make_rsrc(in + ((size_t)b * Hi + yb) * Wi * C, (unsigned)rows * Wi * (C * 4));
+    const int base = ((ys - yb) * Wi + (UP ? x0 >> 1 : x0)) * (C * 4);
+    if (x0 > 0 && x0 + CT < W) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float4 bb = *reinterpret_cast<const float4*>(bias + 8 * q + 4 * h);
-    const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
+      for (int k = 0; k < NL; ++k) hv[k] = mg::bload4(rs, base + vo[k], 0);
+    } else {
+      int t0 = tid;
+      asm volatile("" : "+v"(t0));   // the columns are formed again at an edge, not kept
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[4 * q + i] = acc[16 + 4 * q + i] = bv[i];
-  }
-  __syncthreads();
-  // pixel of this lane as a column of the product: block h, rows 4 wave + 2 h + (n >> 4)
-  const int p0 = (4 * wave + 2 * h + (n >> 4)) * HALO + (n & 15);
-#pragma unroll 1
-  for (int g = 0; g < 8; ++g) {
-    float4 xv[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      wc[t] = wn[t];
-      const int p = p0 + (t / 3) * HALO + t % 3;
-      xv[t] = T[8 * p + (g ^ ((p >> 1) & 7))];
-    }
-    const float4* wg = wl + (size_t)min(g + 1, 7) * 9 * C;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) wn[t] = wg[t * C];
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        const float av = c == 0 ? wc[t].x : c == 1 ? wc[t].y : c == 2 ? wc[t].z : wc[t].w;
-        const float bv = c == 0 ? xv[t].x : c == 1 ? xv[t].y : c == 2 ? xv[t].z : xv[t].w;
-        acc = __builtin_amdgcn_mfma_f32_32x32x1f32(av, bv, acc, 0, 0, 0);
+      for (int k = 0; k < NL; ++k) {
+        const int x = x0 + ((t0 + 256 * k) >> 3) % HALO - 1;
+        hv[k] = mg::bload4(rs, (unsigned)x < (unsigned)W ? base + vo[k] : -16, 0);
       }
-  }
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int y = y0 + 4 * wave + 2 * k + (n >> 4), x = x0 + (n & 15);
-    if (y < H && x < W) {
-      float4* dst = reinterpret_cast<float4*>(out + (((size_t)b * H + y) * W + x) * C + 4 * h);
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        dst[2 * q] = make_float4(fmaxf(acc[16 * k + 4 * q], 0.0f), fmaxf(acc[16 * k + 4 * q + 1], 0.0f),
-                                 fmaxf(acc[16 * k + 4 * q + 2], 0.0f), fmaxf(acc[16 * k + 4 * q + 3], 0.0f));
     }
+  };
+  int q = blockIdx.x;
+  load(q);
+  // this lane's operand of product p: step 4 p + kk of the 36
+  const float2* xa[9];
+#pragma unroll
+  for (int p = 0; p < 9; ++p) {
+    const int s = 4 * p + kk, c = s / 9, t = s - 9 * c;
+    xa[p] = T2 + ((P * wave + t / 3) * HALO + n + t % 3) * (LP / 2) + 4 * c;
+  }
+  int ko = kk;
+  for (; q < total; q += gridDim.x) {
+    // opaque offsets: the weights and the bias are read again for each tile, not all held in registers
+    asm volatile("" : "+v"(wo), "+v"(ko));
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const int i = tid + 256 * k;
+      if (i < HR * 8) {
+        float* d = T + (i >> 3) * LP + (i & 7);
+        d[0] = hv[k].x;
+        d[8] = hv[k].y;
+        d[16] = hv[k].z;
+        d[24] = hv[k].w;
+      }
+    }
+    float4 bb[2];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) bb[cb] = *reinterpret_cast<const float4*>(bias + 16 * cb + 4 * ko);
+    __syncthreads();
+    if (LOOP && q + (int)gridDim.x < total) load(q + gridDim.x);
+    // lane (kk, n) holds channels 16 cb + 4 kk + (0..3) of pixel n of row r
+    f32x4 acc[P][2];
+#pragma unroll
+    for (int r = 0; r < P; ++r)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) acc[r][cb] = f32x4{bb[cb].x, bb[cb].y, bb[cb].z, bb[cb].w};
+    float2 xr[9][P];
+#pragma unroll
+    for (int p = 0; p < 9; ++p)
+#pragma unroll
+      for (int r = 0; r < P; ++r) xr[p][r] = xa[p][r * HALO * (LP / 2)];
+#pragma unroll
+    for (int gp = 0; gp < 4; ++gp)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int p = 0; p < 9; ++p) {
+#pragma unroll
+          for (int r = 0; r < P; ++r)
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+              acc[r][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(u ? wr[p][cb].y : wr[p][cb].x,
+                                                                u ? xr[p][r].y : xr[p][r].x, acc[r][cb], 0, 0, 0);
+          if (u) {
+            if (gp < 3) {
+#pragma unroll
+              for (int r = 0; r < P; ++r) xr[p][r] = xa[p][r * HALO * (LP / 2) + gp + 1];
+            }
+            if (LOOP || gp < 3) {
+#pragma unroll
+              for (int cb = 0; cb < 2; ++cb)
+                wr[p][cb] = mg::bload2(wrs, wo, ((((gp + 1) & 3) * 9 + p) * 2 + cb) * 512);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+    if (LOOP) __syncthreads();   // the tile is read; the next one may overwrite it
+    const int b = q / (tx * ty), rr = q - b * (tx * ty), ry = rr / tx, y0 = ry * TH, x0 = (rr - ry * tx) * CT;
+#pragma unroll
+    for (int r = 0; r < P; ++r) {
+      const int y = y0 + P * wave + r, x = x0 + n;
+      if (y < H && x < W) {
+        float* d = out + (((size_t)b * H + y) * W + x) * C + 4 * kk;
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+          *reinterpret_cast<float4*>(d + 16 * cb) = make_float4(fmaxf(acc[r][cb][0], 0.0f), fmaxf(acc[r][cb][1], 0.0f),
+                                                                fmaxf(acc[r][cb][2], 0.0f), fmaxf(acc[r][cb][3], 0.0f));
+      }
+    }
+    if (!LOOP) break;
   }
 }
 
@@ -898,18 +970,21 @@ __global__ __launch_bounds__(1024) void rows_sum_kernel(const float* __restrict_
 // ---------------------------------------------------------------------------
 // Compute copies of the weights (all layers in one launch)
 // ---------------------------------------------------------------------------
-// Forward: [chunk of four input channels][tap][co] float4 per 32 -> 32 layer.  Backward-
+// Forward, per 32 -> 32 layer: [pair of chunks of four input channels][product p][half of co][lane]
+// float2, lane (kk, n) holding the weights of step 4 p + kk (channel, tap) and co = 16 half + n in
+// both chunks.  Backward-
 // data: fragments [tap][half of its input channels][part][lane] of eight bf16 values, lane
 // (h, co) holding input channels 16 half + 8 h + (0..7).
 __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
-  constexpr int NF = 3 * 8 * 9 * C, NB = 3 * 18 * 64;
+  constexpr int NF = 3 * FWD_VECS, NB = 3 * 18 * 64;
   const int i = blockIdx.x * 256 + threadIdx.x;
   bool bad = false;
   if (i < NF) {
-    const int layer = i / (8 * 9 * C), e = i - layer * (8 * 9 * C), co = e % C, t = (e / C) % 9, g = e / (9 * C);
-    const float* w = a.p + a.off_sq[layer] + (co * C + 4 * g) * 9 + t;
-    float4 v = make_float4(w[0], w[9], w[18], w[27]);
-    if (a.bf16) v = make_float4(round_bf16(v.x), round_bf16(v.y), round_bf16(v.z), round_bf16(v.w));
+    const int layer = i / FWD_VECS, e = i - layer * FWD_VECS, lane = e & 63, half = (e >> 6) & 1, gp = e / FWD_TAPS;
+    const int st = 4 * ((e >> 7) % 9) + (lane >> 4), c = st / 9, t = st - 9 * c, co = 16 * half + (lane & 15);
+    const float* w = a.p + a.off_sq[layer] + (co * C + 8 * gp + c) * 9 + t;
+    float2 v = make_float2(w[0], w[36]);
+    if (a.bf16) v = make_float2(round_bf16(v.x), round_bf16(v.y));
     a.fwd[i] = v;
   } else if (i < NF + NB) {
     const int j0 = i - NF, layer = j0 / (18 * 64), e = j0 - layer * (18 * 64), step = e >> 6, lane = e & 63;
@@ -975,17 +1050,30 @@ Tiling wgrad_tiling(int batch, int H, int W, int most) {
 // Launchers
 // ---------------------------------------------------------------------------
 hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
-  const int n = 3 * 8 * 9 * C + 3 * 18 * 64 + C * a.cin * 9 + 2 * C * 9;
+  const int n = 3 * FWD_VECS + 3 * 18 * 64 + C * a.cin * 9 + 2 * C * 9;
   hipLaunchKernelGGL(prep_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_conv32(bool up, const float* in, const float4* w, const float* bias, float* out, int batch, int H,
+template <int P>
+static void conv32_forward_t(bool up, const float* in, const float2* w, const float* bias, float* out, int batch, int H,
+                             int W, hipStream_t s) {
+  const int tx = (W + CT - 1) / CT, ty = (H + 4 * P - 1) / (4 * P), total = tx * ty * batch;
+  const dim3 grid(P == 4 ? std::min(total, 512) : total);
+  if (up)
+    hipLaunchKernelGGL((conv32_forward_kernel<true, P>), grid, dim3(256), 0, s, in, w, bias, out, H, W, tx, ty, total);
+  else
+    hipLaunchKernelGGL((conv32_forward_kernel<false, P>), grid, dim3(256), 0, s, in, w, bias, out, H, W, tx, ty, total);
+}
+
+hipError_t launch_conv32(bool up, const float* in, const float2* w, const float* bias, float* out, int batch, int H,
                          int W, hipStream_t s) {
   if (batch < 1 || H < 1 || W < 1 || (up && ((H | W) & 1))) return hipErrorInvalidValue;
-  const dim3 grid((W + CT - 1) / CT, (H + CT - 1) / CT, batch);
-  if (up) hipLaunchKernelGGL(conv32_forward_kernel<true>, grid, dim3(256), 0, s, in, w, bias, out, H, W);
-  else hipLaunchKernelGGL(conv32_forward_kernel<false>, grid, dim3(256), 0, s, in, w, bias, out, H, W);
+  // the fewest rows per workgroup that still give every CU at most one (see the kernel)
+  const long tiles = (long)batch * ((H + CT - 1) / CT) * ((W + CT - 1) / CT);
+  if (tiles <= 64) conv32_forward_t<1>(up, in, w, bias, out, batch, H, W, s);
+  else if (tiles <= 128) conv32_forward_t<2>(up, in, w, bias, out, batch, H, W, s);
+  else conv32_forward_t<4>(up, in, w, bias, out, batch, H, W, s);
   return hipGetLastError();
 }
 

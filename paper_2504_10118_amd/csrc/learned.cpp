@@ -37,7 +37,7 @@ struct magpie_cnn {
   int64_t off_w[N_LAYERS], off_b[N_LAYERS];
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
   int64_t t = 0;
-  float4* fwd = nullptr;     // compute copies of the weights (cnn::PrepArgs)
+  float2* fwd = nullptr;     // compute copies of the weights (cnn::PrepArgs)
   uint4* frag = nullptr;
   float* wthin = nullptr;    // first, head, head_t
   int* wbad = nullptr;

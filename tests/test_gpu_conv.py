@@ -67,6 +67,18 @@ def test_forward_is_the_fp32_chain(cin, side, nb, bf16):
     net.close()
 
 
+# tiles of 16 x 16 at the larger size: 9 (4 rows per workgroup), 90 (8 rows; 40 of the small layer: 4),
+# 180 (16 rows; 80: 8), 630 (workgroups with two tiles)
+@pytest.mark.parametrize("nb", [10, 20, 70])
+def test_forward_of_a_batch_is_that_of_its_samples(nb):
+    p, x, _ = _problem(700, 3, 18, nb)
+    net = _net(3, 18, nb, 0, p)
+    y = net.forward(x)
+    one = np.concatenate([net.forward(x[i:i + 1]) for i in range(nb)])
+    net.close()
+    assert np.array_equal(y.view(np.uint32), one.view(np.uint32))
+
+
 # (16 x 16 tiles, 16 x 8 tiles) at the two sizes: one ragged tile; exact; one pixel over; many runs
 @pytest.mark.parametrize("cin,side,nb,bf16", [(3, 2, 1, False), (1, 8, 2, True), (4, 18, 3, False), (3, 34, 33, False)])
 def test_gradients_at_tile_edges(cin, side, nb, bf16):
