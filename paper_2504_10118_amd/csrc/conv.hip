@@ -72,6 +72,64 @@ __device__ __forceinline__ float round_bf16(float x) {
 }
 
 // ---------------------------------------------------------------------------
+// The halo of a tile
+// ---------------------------------------------------------------------------
+// A tile of TH x 16 output pixels reads (TH + 2) x 18 pixels of a channels-last tensor (UP: of
+// half the size, each pixel taken twice), split into PPP pieces per pixel; thread tid takes the
+// pieces tid, tid + 256, ...: all its loads are issued together, without a branch.
+template <bool UP, int TH, int PPP>
+struct Halo {
+  static constexpr int PIXELS = (TH + 2) * HALO, N = (PIXELS * PPP + 255) / 256;
+  int vo[N];   // piece k: offset in bytes from the tile's first source pixel
+  __device__ __forceinline__ void init(int tid, int Wi) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int i = tid + 256 * k, p = i / PPP, yy = p / HALO - 1, xx = p % HALO - 1;
+      vo[k] = ((UP ? yy >> 1 : yy) * Wi + (UP ? xx >> 1 : xx)) * (C * 4) + i % PPP * (C * 4 / PPP);
+    }
+  }
+  // The source of a tile of the output (H x W): a resource that covers the source rows that
+  // exist, so that a row above the image is a negative offset, one below lies past the end, and
+  // both read as zero.
+  struct At {
+    mg::rsrc_t rs;
+    int base, x0, W;
+  };
+  static __device__ __forceinline__ At at(const float* in, int b, int y0, int x0, int H, int W) {
+    const int Hi = UP ? H >> 1 : H, Wi = UP ? W >> 1 : W;
+    const int ys = UP ? y0 >> 1 : y0, yb = max(ys - 1, 0), rows = min(Hi - yb, (UP ? TH / 2 : TH) + 2);
+    return {mg::make_rsrc(in + ((size_t)b * Hi + yb) * Wi * C, (unsigned)rows * Wi * (C * 4)),
+            ((ys - yb) * Wi + (UP ? x0 >> 1 : x0)) * (C * 4), x0, W};
+  }
+  // offset of piece k of thread tid (a column outside the image reads as zero)
+  __device__ __forceinline__ int offset(const At& t, int k, int tid) const {
+    const int x = t.x0 + (tid + 256 * k) / PPP % HALO - 1;
+    return (unsigned)x < (unsigned)t.W ? t.base + vo[k] : -C * 4;
+  }
+  // get(k, resource, offset) for every piece
+  template <typename F>
+  __device__ __forceinline__ void load(const At& t, int tid, F get) const {
+    if (t.x0 > 0 && t.x0 + CT < t.W) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) get(k, t.rs, t.base + vo[k]);
+    } else {
+      asm volatile("" : "+v"(tid));   // the columns are formed again at an edge, not kept
+#pragma unroll
+      for (int k = 0; k < N; ++k) get(k, t.rs, offset(t, k, tid));
+    }
+  }
+};
+
+// tile q of a batch: sample, first row and column
+struct TileAt {
+  int b, y0, x0;
+};
+__device__ __forceinline__ TileAt tile_at(int q, int tx, int ty, int th) {
+  const int b = q / (tx * ty), r = q - b * (tx * ty), ry = r / tx;
+  return {b, ry * th, (r - ry * tx) * CT};
+}
+
+// ---------------------------------------------------------------------------
 // 32 -> 32 convolution, forward
 // ---------------------------------------------------------------------------
 // Tiles of 16 x 4 P output pixels, four waves, each wave P rows.  The chain of an output runs
@@ -103,11 +161,11 @@ __global__ __launch_bounds__(256, 2) void conv32_forward_kernel(const float* __r
                                                                 float* __restrict__ out, int H, int W, int tx, int ty,
                                                                 int total) {
   constexpr bool LOOP = P == 4;
-  constexpr int TH = 4 * P, HR = (TH + 2) * HALO, LP = 34, NL = (HR * 8 + 255) / 256;
+  using HaloT = Halo<UP, 4 * P, 8>;
+  constexpr int TH = 4 * P, HR = HaloT::PIXELS, LP = 34, NL = HaloT::N;
   __shared__ float2 T2[HR * LP / 2];
   float* T = reinterpret_cast<float*>(T2);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, kk = lane >> 4;
-  const int Hi = UP ? H >> 1 : H, Wi = UP ? W >> 1 : W;
   const mg::rsrc_t wrs = mg::make_rsrc(w, 4 * FWD_TAPS * sizeof(float2));
   int wo = lane * (int)sizeof(float2);
   float2 wr[9][2];
@@ -115,33 +173,12 @@ __global__ __launch_bounds__(256, 2) void conv32_forward_kernel(const float* __r
   for (int p = 0; p < 9; ++p)
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) wr[p][cb] = mg::bload2(wrs, wo, (p * 2 + cb) * 512);
-  // staged 16-byte piece k of this thread: its offset from the tile's first source pixel
-  int vo[NL];
-#pragma unroll
-  for (int k = 0; k < NL; ++k) {
-    const int p = (tid + 256 * k) >> 3, yy = p / HALO - 1, xx = p % HALO - 1;
-    vo[k] = ((UP ? yy >> 1 : yy) * Wi + (UP ? xx >> 1 : xx)) * (C * 4) + (tid & 7) * 16;
-  }
+  HaloT halo;
+  halo.init(tid, UP ? W >> 1 : W);
   float4 hv[NL];
   auto load = [&](int q) {
-    const int b = q / (tx * ty), r = q - b * (tx * ty), ry = r / tx, y0 = ry * TH, x0 = (r - ry * tx) * CT;
-    // the resource covers the tile's source rows that exist: a row above the image is a negative
-    // offset, one below lies past the end, and both read as zero
-    const int ys = UP ? y0 >> 1 : y0, yb = max(ys - 1, 0), rows = min(Hi - yb, (UP ? TH / 2 : TH) + 2);
-    const mg::rsrc_t rs = mg::make_rsrc(in + ((size_t)b * Hi + yb) * Wi * C, (unsigned)rows * Wi * (C * 4));
-    const int base = ((ys - yb) * Wi + (UP ? x0 >> 1 : x0)) * (C * 4);
-    if (x0 > 0 && x0 + CT < W) {
-#pragma unroll
-      for (int k = 0; k < NL; ++k) hv[k] = mg::bload4(rs, base + vo[k], 0);
-    } else {
-      int t0 = tid;
-      asm volatile("" : "+v"(t0));   // the columns are formed again at an edge, not kept
-#pragma unroll
-      for (int k = 0; k < NL; ++k) {
-        const int x = x0 + ((t0 + 256 * k) >> 3) % HALO - 1;
-        hv[k] = mg::bload4(rs, (unsigned)x < (unsigned)W ? base + vo[k] : -16, 0);
-      }
-    }
+    const TileAt t = tile_at(q, tx, ty, TH);
+    halo.load(HaloT::at(in, t.b, t.y0, t.x0, H, W), tid, [&](int k, mg::rsrc_t rs, int off) { hv[k] = mg::bload4(rs, off, 0); });
   };
   int q = blockIdx.x;
   load(q);
@@ -209,12 +246,12 @@ __global__ __launch_bounds__(256, 2) void conv32_forward_kernel(const float* __r
           }
         }
     if (LOOP) __syncthreads();   // the tile is read; the next one may overwrite it
-    const int b = q / (tx * ty), rr = q - b * (tx * ty), ry = rr / tx, y0 = ry * TH, x0 = (rr - ry * tx) * CT;
+    const TileAt at = tile_at(q, tx, ty, TH);
 #pragma unroll
     for (int r = 0; r < P; ++r) {
-      const int y = y0 + P * wave + r, x = x0 + n;
+      const int y = at.y0 + P * wave + r, x = at.x0 + n;
       if (y < H && x < W) {
-        float* d = out + (((size_t)b * H + y) * W + x) * C + 4 * kk;
+        float* d = out + (((size_t)at.b * H + y) * W + x) * C + 4 * kk;
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb)
           *reinterpret_cast<float4*>(d + 16 * cb) = make_float4(fmaxf(acc[r][cb][0], 0.0f), fmaxf(acc[r][cb][1], 0.0f),
@@ -237,8 +274,13 @@ __global__ __launch_bounds__(256, 2) void conv32_forward_kernel(const float* __r
 // the weights come as prepared fragments (54 KB, shared through L1 and L2).
 // MODE 2: zero where omask <= 0.  3: sum of each 2 x 2 block (the adjoint of the
 // upsampling), zero where omask <= 0, written at half the size.
+// 512 workgroups (two per CU) walk the tiles: the next tile's halo is loaded, a piece every
+// other step, while the products run, and the masks with the last ones.  (A tile per
+// workgroup stood 9000 of its 33000 clocks at the loads, which all workgroups issued at once,
+// and 8000 at the masks, read one after another; the fragments three steps ahead spill.)
 // Bound: 2 * 9 * 32 * 32 flops per pixel at the six-product rate (23 us of MFMA issue for
-// 32 samples of 128 x 128), then the activations' traffic.
+// 32 samples of 128 x 128) and the activations' traffic (42 us, 23 with MODE 3): 76 -> 68 us,
+// MODE 3 70 -> 63 us.
 template <int WS>
 struct Pairs;
 template <>
@@ -305,124 +347,145 @@ __device__ __forceinline__ float lane_xor_f(float v, bool far) {
 }
 
 template <int MODE, int WS>
-__global__ __launch_bounds__(256, 2) void conv32_kernel(Conv32Args a) {
+__global__ __launch_bounds__(256, 2) void conv32_kernel(Conv32Args a, int tx, int ty, int total) {
+  using HaloT = Halo<false, CT, 4>;
+  constexpr int NS = HaloT::N;
   __shared__ uint4 T[3][HP * 4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int x0 = blockIdx.x * CT, y0 = blockIdx.y * CT, b = blockIdx.z;
-  const float* inb = a.in + (size_t)b * a.H * a.W * C;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
   const int wbad = *a.wbad;
-  const uint4* fr = a.frag + lane;
+  const mg::rsrc_t frs = mg::make_rsrc(a.frag, 18 * WS * 64 * sizeof(uint4));
+  int fo = lane * (int)sizeof(uint4);
+  auto frag = [&](int step, int s) { return __builtin_bit_cast(uint4, mg::bload4(frs, fo, (step * WS + s) * 1024)); };
 
   // staging: thread i takes 8 channels (chunk i & 3) of halo pixel i >> 2
-  constexpr int NS = (HP * 4 + 255) / 256;
-  float st[NS][8];
-#pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const int i = tid + 256 * k, p = i >> 2, yy = p / HALO, xx = p - yy * HALO;
-    const int gy = y0 + yy - 1, gx = x0 + xx - 1;
-    float4 lo = make_float4(0.0f, 0.0f, 0.0f, 0.0f), hi = lo;
-    if (i < HP * 4 && gy >= 0 && gy < a.H && gx >= 0 && gx < a.W) {
-      const float4* src = reinterpret_cast<const float4*>(inb + ((size_t)gy * a.W + gx) * C) + 2 * (i & 3);
-      lo = src[0];
-      hi = src[1];
-    }
-    st[k][0] = lo.x; st[k][1] = lo.y; st[k][2] = lo.z; st[k][3] = lo.w;
-    st[k][4] = hi.x; st[k][5] = hi.y; st[k][6] = hi.z; st[k][7] = hi.w;
-  }
-  // fragments are loaded PF steps ahead of their products: they come from L2 (54 KB per
-  // tile and wave, more than L1 holds)
-  constexpr int PF = 3;
-  uint4 wf[PF + 1][WS];
-#pragma unroll
-  for (int k = 0; k < PF; ++k)
-#pragma unroll
-    for (int s = 0; s < WS; ++s) wf[k][s] = fr[(k * WS + s) * 64];
-  float probe = 0.0f;
-#pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const int i = tid + 256 * k, p = i >> 2;
-    uint4 s[3];
-    split8(st[k], s, probe);
-    if (i < HP * 4) {
-      const int at = 4 * p + ((i & 3) ^ ((p >> 2) & 3));
-#pragma unroll
-      for (int q = 0; q < 3; ++q) T[q][at] = s[q];
-    }
-  }
-  if (__syncthreads_or(!(probe == 0.0f) || wbad)) {
-    conv32_scalar<MODE, WS>(a, b, y0, x0);
-    return;
-  }
-
-  const int h = lane >> 5, n = lane & 31;
-  f32x16 acc[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[k][r] = 0.0f;
-  const int p0 = (4 * wave + (n >> 4)) * HALO + (n & 15);
-  // software pipeline, held by scheduling barriers: step i issues the weights of step i +
-  // PF and the LDS reads of step i + 1 before its own twelve products
-  uint4 x[2][2][3];
-  auto read = [&](int step, uint4 (&xs)[2][3]) {
-    const int t = step >> 1, kh = step & 1;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int p = p0 + (2 * k + t / 3) * HALO + t % 3;
-      const int at = 4 * p + ((2 * kh + h) ^ ((p >> 2) & 3));
-#pragma unroll
-      for (int q = 0; q < 3; ++q) xs[k][q] = T[q][at];
-    }
+  HaloT halo;
+  halo.init(tid, a.W);
+  float4 st[NS][2];
+  auto source = [&](int q) {
+    const TileAt t = tile_at(q, tx, ty, CT);
+    return HaloT::at(a.in, t.b, t.y0, t.x0, a.H, a.W);
   };
-  read(0, x[0]);
+  int to = tid;
+  auto load = [&](const typename HaloT::At& t, int k) {
+    const int off = halo.offset(t, k, to);
+    st[k][0] = mg::bload4(t.rs, off, 0);
+    st[k][1] = mg::bload4(t.rs, off, 16);
+  };
+  int q0 = blockIdx.x;
+  {
+    const typename HaloT::At src = source(q0);
 #pragma unroll
-  for (int step = 0; step < 18; ++step) {
-    if (step + PF < 18) {
-#pragma unroll
-      for (int s = 0; s < WS; ++s) wf[(step + PF) % (PF + 1)][s] = fr[((step + PF) * WS + s) * 64];
-    }
-    if (step + 1 < 18) read(step + 1, x[(step + 1) & 1]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int j = 0; j < Pairs<WS>::N; ++j)
-#pragma unroll
-      for (int k = 0; k < 2; ++k)
-        acc[k] = mfma(wf[step % (PF + 1)][Pairs<WS>::w[j]], x[step & 1][k][Pairs<WS>::x[j]], acc[k]);
-    __builtin_amdgcn_sched_barrier(0);
+    for (int k = 0; k < NS; ++k) load(src, k);
   }
-
-  // lane (h, n) holds channels 8 q + 4 h + (0..3) of pixel n of each block
+  const int p0 = (4 * wave + (n >> 4)) * HALO + (n & 15);
+#pragma unroll 1
+  for (; q0 < total; q0 += gridDim.x) {
+    asm volatile("" : "+v"(fo), "+v"(to));   // the fragments are read again for each tile
+    // fragments are loaded PF steps ahead of their products: they come from L2 (54 KB per
+    // tile and wave, more than L1 holds); a piece of the next halo every SPREAD steps
+    constexpr int PF = 2, SPREAD = 2;
+    uint4 wf[PF + 1][WS];
+    float probe = 0.0f;
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int y = y0 + 4 * wave + 2 * k + (n >> 4), x = x0 + (n & 15);
-    const bool in = y < a.H && x < a.W;
+    for (int k = 0; k < NS; ++k) {
+      const int i = tid + 256 * k, p = i >> 2;
+      const float v[8] = {st[k][0].x, st[k][0].y, st[k][0].z, st[k][0].w, st[k][1].x, st[k][1].y, st[k][1].z, st[k][1].w};
+      uint4 s[3];
+      split8(v, s, probe);
+      if (i < HP * 4) {
+        const int at = 4 * p + ((i & 3) ^ ((p >> 2) & 3));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c0 = 8 * q + 4 * h;
-      float4 v = make_float4(acc[k][4 * q], acc[k][4 * q + 1], acc[k][4 * q + 2], acc[k][4 * q + 3]);
-      if constexpr (MODE == 2) {
-        if (in) {
-          const size_t at = (((size_t)b * a.H + y) * a.W + x) * C + c0;
-          const float4 mk = *reinterpret_cast<const float4*>(a.omask + at);
-          v = make_float4(mk.x > 0.0f ? v.x : 0.0f, mk.y > 0.0f ? v.y : 0.0f, mk.z > 0.0f ? v.z : 0.0f,
-                          mk.w > 0.0f ? v.w : 0.0f);
-          *reinterpret_cast<float4*>(a.out + at) = v;
-        }
-      } else {
-        // 2 x 2 sums: the horizontal neighbour, then the row below
-        v = make_float4(v.x + lane_xor_f(v.x, false), v.y + lane_xor_f(v.y, false), v.z + lane_xor_f(v.z, false),
-                        v.w + lane_xor_f(v.w, false));
-        v = make_float4(v.x + lane_xor_f(v.x, true), v.y + lane_xor_f(v.y, true), v.z + lane_xor_f(v.z, true),
-                        v.w + lane_xor_f(v.w, true));
-        if (in && !(n & 17)) {
-          const size_t at = (((size_t)b * (a.H >> 1) + (y >> 1)) * (a.W >> 1) + (x >> 1)) * C + c0;
-          const float4 mk = *reinterpret_cast<const float4*>(a.omask + at);
-          v = make_float4(mk.x > 0.0f ? v.x : 0.0f, mk.y > 0.0f ? v.y : 0.0f, mk.z > 0.0f ? v.z : 0.0f,
-                          mk.w > 0.0f ? v.w : 0.0f);
-          *reinterpret_cast<float4*>(a.out + at) = v;
-        }
+        for (int q = 0; q < 3; ++q) T[q][at] = s[q];
       }
     }
+#pragma unroll
+    for (int k = 0; k < PF; ++k)
+#pragma unroll
+      for (int s = 0; s < WS; ++s) wf[k][s] = frag(k, s);
+    const bool bad = __syncthreads_or(!(probe == 0.0f) || wbad);
+    // the last tile's own halo is loaded again, unused, rather than a branch around each load
+    const typename HaloT::At next = source(min(q0 + (int)gridDim.x, total - 1));
+    const TileAt tl = tile_at(q0, tx, ty, CT);
+    if (bad) {
+      conv32_scalar<MODE, WS>(a, tl.b, tl.y0, tl.x0);
+#pragma unroll
+      for (int k = 0; k < NS; ++k) load(next, k);
+      __syncthreads();
+      continue;
+    }
+
+    f32x16 acc[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[k][r] = 0.0f;
+    // lane (h, n) holds channels 8 q + 4 h + (0..3) of pixel n of each block; the masks are loaded
+    // with the last products still to come
+    size_t at[2];
+    bool in[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int y = tl.y0 + 4 * wave + 2 * k + (n >> 4), x = tl.x0 + (n & 15);
+      in[k] = y < a.H && x < a.W && (MODE == 2 || !(n & 17));
+      const int sh = MODE == 2 ? 0 : 1, ys = min(y, a.H - 1) >> sh, xs = min(x, a.W - 1) >> sh;
+      at[k] = (((size_t)tl.b * (a.H >> sh) + ys) * (a.W >> sh) + xs) * C + 4 * h;
+    }
+    float4 mk[2][4];
+    // software pipeline, held by scheduling barriers: step i issues the weights of step i +
+    // PF and the LDS reads of step i + 1 before its own twelve products
+    uint4 x[2][2][3];
+    auto read = [&](int step, uint4 (&xs)[2][3]) {
+      const int t = step >> 1, kh = step & 1;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int p = p0 + (2 * k + t / 3) * HALO + t % 3;
+        const int at = 4 * p + ((2 * kh + h) ^ ((p >> 2) & 3));
+#pragma unroll
+        for (int q = 0; q < 3; ++q) xs[k][q] = T[q][at];
+      }
+    };
+    read(0, x[0]);
+#pragma unroll
+    for (int step = 0; step < 18; ++step) {
+      if (step + PF < 18) {
+#pragma unroll
+        for (int s = 0; s < WS; ++s) wf[(step + PF) % (PF + 1)][s] = frag(step + PF, s);
+      }
+      if (step + 1 < 18) read(step + 1, x[(step + 1) & 1]);
+      if (step % SPREAD == 0 && step / SPREAD < NS) load(next, step / SPREAD);
+      if (step == 18 - PF) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) mk[k][q] = *reinterpret_cast<const float4*>(a.omask + at[k] + 8 * q);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < Pairs<WS>::N; ++j)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          acc[k] = mfma(wf[step % (PF + 1)][Pairs<WS>::w[j]], x[step & 1][k][Pairs<WS>::x[j]], acc[k]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();   // the tile is read; the next one may overwrite it
+
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float4 v = make_float4(acc[k][4 * q], acc[k][4 * q + 1], acc[k][4 * q + 2], acc[k][4 * q + 3]);
+        if constexpr (MODE == 3) {
+          // 2 x 2 sums: the horizontal neighbour, then the row below
+          v = make_float4(v.x + lane_xor_f(v.x, false), v.y + lane_xor_f(v.y, false), v.z + lane_xor_f(v.z, false),
+                          v.w + lane_xor_f(v.w, false));
+          v = make_float4(v.x + lane_xor_f(v.x, true), v.y + lane_xor_f(v.y, true), v.z + lane_xor_f(v.z, true),
+                          v.w + lane_xor_f(v.w, true));
+        }
+        const float4 m = mk[k][q];
+        v = make_float4(m.x > 0.0f ? v.x : 0.0f, m.y > 0.0f ? v.y : 0.0f, m.z > 0.0f ? v.z : 0.0f,
+                        m.w > 0.0f ? v.w : 0.0f);
+        if (in[k]) *reinterpret_cast<float4*>(a.out + at[k] + 8 * q) = v;
+      }
   }
 }
 
@@ -479,19 +542,21 @@ __global__ __launch_bounds__(256) void conv_thin_kernel(const float* __restrict_
 // ---------------------------------------------------------------------------
 // One workgroup per 16 x 16 tile, one pixel per thread; the halo is staged as it is (128
 // bytes per pixel, chunks rotated against bank conflicts), the weights w[c][t][o] are
-// uniform.  576 FMAs per 128 bytes read: bound by the read of the activations.
+// uniform.  576 FMAs per 128 bytes read: bound by the read of the activations (13 us for 32
+// samples of 128 x 128; 29.7 -> 22.2 us with the halo's loads in flight together).
 __global__ __launch_bounds__(256) void conv_head_kernel(const float* __restrict__ in, const float* __restrict__ w,
                                                         const float* __restrict__ bias, float* __restrict__ out,
                                                         int H, int W) {
   __shared__ float4 T[HP * 8];
   const int x0 = blockIdx.x * CT, y0 = blockIdx.y * CT, b = blockIdx.z;
-  const float* inb = in + (size_t)b * H * W * C;
-  for (int i = threadIdx.x; i < HP * 8; i += 256) {
-    const int p = i >> 3, yy = p / HALO, xx = p - yy * HALO, gy = y0 + yy - 1, gx = x0 + xx - 1;
-    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (gy >= 0 && gy < H && gx >= 0 && gx < W)
-      v = reinterpret_cast<const float4*>(inb + ((size_t)gy * W + gx) * C)[i & 7];
-    T[8 * p + ((i & 7) ^ ((p >> 1) & 7))] = v;
+  Halo<false, CT, 8> halo;
+  float4 hv[halo.N];
+  halo.init(threadIdx.x, W);
+  halo.load(halo.at(in, b, y0, x0, H, W), threadIdx.x, [&](int k, mg::rsrc_t rs, int off) { hv[k] = mg::bload4(rs, off, 0); });
+#pragma unroll
+  for (int k = 0; k < halo.N; ++k) {
+    const int i = threadIdx.x + 256 * k, p = i >> 3;
+    if (i < HP * 8) T[8 * p + ((i & 7) ^ ((p >> 1) & 7))] = hv[k];
   }
   __syncthreads();
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
@@ -1025,9 +1090,10 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
 
 template <int MODE>
 hipError_t conv32_t(bool bf16, const Conv32Args& a, int batch, hipStream_t s) {
-  const dim3 grid((a.W + CT - 1) / CT, (a.H + CT - 1) / CT, batch);
-  if (bf16) hipLaunchKernelGGL((conv32_kernel<MODE, 1>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((conv32_kernel<MODE, 3>), grid, dim3(256), 0, s, a);
+  const int tx = (a.W + CT - 1) / CT, ty = (a.H + CT - 1) / CT, total = tx * ty * batch;
+  const dim3 grid(std::min(total, 512));
+  if (bf16) hipLaunchKernelGGL((conv32_kernel<MODE, 1>), grid, dim3(256), 0, s, a, tx, ty, total);
+  else hipLaunchKernelGGL((conv32_kernel<MODE, 3>), grid, dim3(256), 0, s, a, tx, ty, total);
   return hipGetLastError();
 }
 

@@ -136,6 +136,31 @@ def test_infinite_output_gradient(bf16):
     assert np.linalg.norm(g[fin] - want[fin]) <= 2e-5 * np.linalg.norm(want[fin])
 
 
+def test_infinite_output_gradient_in_a_batch():
+    """630 tiles on workgroups that take two each: an infinite value in the first tile of some leaves the
+    second one's products right.  Gradients add over samples, to 2e-5 of their norm as above."""
+    cin, side, nb, bad = 1, 18, 70, 3
+    p, x, rng = _problem(800, cin, side, nb)
+    dy = rng.normal(size=(nb, 2, 2 * side, 2 * side)).astype(np.float32)
+    rest = dy.copy()
+    rest[bad] = 0
+    dy[bad, 1, 7, 9] = np.inf
+    net = _net(cin, side, nb, 0, p)
+
+    def grads(xs, ds):
+        net.forward(xs)
+        net.backward(ds)
+        return net.get_grads().astype(np.float64)
+
+    g, g_rest, one = grads(x, dy), grads(x, rest), grads(x[bad:bad + 1], dy[bad:bad + 1])
+    net.close()
+    fin = np.isfinite(one)
+    assert 0 < fin.sum() < one.size
+    assert np.array_equal(np.isnan(g), np.isnan(one)) and np.array_equal(np.isinf(g), np.isinf(one))
+    want = g_rest[fin] + one[fin]
+    assert np.linalg.norm(g[fin] - want) <= 2e-5 * np.linalg.norm(want)
+
+
 def test_refused_mask_keeps_the_output_gradient():
     """A loss with a refused mask fails and leaves the last valid loss's output gradient in place."""
     from paper_2504_10118_amd import MagpieError
