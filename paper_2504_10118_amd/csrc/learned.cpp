@@ -4,6 +4,8 @@
 // with its flat-start fallback.
 #include "../../include/magpie_learned.h"
 
+#include <type_traits>
+
 #include "cnn.h"
 #include "context.h"
 
@@ -35,6 +37,7 @@ struct magpie_cnn {
   int64_t n = 0;
   int co[N_LAYERS], ci[N_LAYERS];
   int64_t off_w[N_LAYERS], off_b[N_LAYERS];
+  char* slab = nullptr;      // parameters, weights' copies and sums: one allocation
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
   int64_t t = 0;
   float2* fwd = nullptr;     // compute copies of the weights (cnn::PrepArgs)
@@ -198,14 +201,33 @@ int magpie_cnn_create(magpie_cnn** out, int in_ch, int width, int side, int max_
   }
   const size_t B = (size_t)max_batch, S = side, S2 = 2 * (size_t)side;
   const size_t lo = B * WIDTH * S * S, hi = B * WIDTH * S2 * S2;
-  rc = dev_alloc(&net->p, (size_t)net->n);
-  if (!rc) rc = dev_alloc(&net->g, (size_t)net->n);
-  if (!rc) rc = dev_alloc(&net->m, (size_t)net->n);
-  if (!rc) rc = dev_alloc(&net->v, (size_t)net->n);
-  if (!rc) rc = dev_alloc(&net->fwd, (size_t)3 * cnn::FWD_VECS);
-  if (!rc) rc = dev_alloc(&net->frag, (size_t)3 * cnn::FRAG_VECS);
-  if (!rc) rc = dev_alloc(&net->wthin, (size_t)(WIDTH * in_ch * 9 + 2 * 2 * WIDTH * 9));
-  if (!rc) rc = dev_alloc(&net->wbad, 1);
+  // the buffers other than activations share one allocation: sized in a first pass, handed out
+  // in a second
+  size_t used = 0;
+  auto slice = [&](auto*& q, size_t count) {
+    if (net->slab) q = reinterpret_cast<std::remove_reference_t<decltype(q)>>(net->slab + used);
+    used += (count * sizeof(*q) + 255) & ~(size_t)255;
+  };
+  auto slices = [&]() {
+    used = 0;
+    slice(net->p, (size_t)net->n);
+    slice(net->g, (size_t)net->n);
+    slice(net->m, (size_t)net->n);
+    slice(net->v, (size_t)net->n);
+    slice(net->fwd, (size_t)3 * cnn::FWD_VECS);
+    slice(net->frag, (size_t)3 * cnn::FRAG_VECS);
+    slice(net->wthin, (size_t)(WIDTH * in_ch * 9 + 2 * 2 * WIDTH * 9));
+    slice(net->wbad, 1);
+    slice(net->part, (size_t)cnn::WGRAD_MAX_WORKGROUPS * cnn::SQ_ROW);
+    slice(net->lpart, (size_t)cnn::cmse_blocks(max_batch, (int)(S2 * S2)));
+    slice(net->lhead, 1);
+    slice(net->mask, S2 * S2);
+    slice(net->rot, B);
+    slice(net->ip_part, B * (size_t)cnn::cmse_ip_blocks((int)(S2 * S2)));
+  };
+  slices();
+  rc = dev_alloc(&net->slab, used);
+  if (!rc) slices();
   if (!rc) rc = dev_alloc(&net->x, B * in_ch * S * S);
   if (!rc) rc = dev_alloc(&net->a1, lo);
   if (!rc) rc = dev_alloc(&net->a2, lo);
@@ -217,17 +239,11 @@ int magpie_cnn_create(magpie_cnn** out, int in_ch, int width, int side, int max_
   if (!rc) rc = dev_alloc(&net->f1, hi);
   if (!rc) rc = dev_alloc(&net->y, B * 2 * S2 * S2);
   if (!rc) rc = dev_alloc(&net->dy, B * 2 * S2 * S2);
-  if (!rc) rc = dev_alloc(&net->part, (size_t)cnn::WGRAD_MAX_WORKGROUPS * cnn::SQ_ROW);
-  if (!rc) rc = dev_alloc(&net->lpart, (size_t)cnn::cmse_blocks(max_batch, (int)(S2 * S2)));
-  if (!rc) rc = dev_alloc(&net->lhead, 1);
   if (!rc && hipHostMalloc((void**)&net->lres, sizeof(*net->lres), hipHostMallocDefault) != hipSuccess) {
     net->lres = nullptr;
     rc = fail(MAGPIE_ERR_OOM, "pinned host allocation failed");
   }
   if (!rc) rc = dev_alloc(&net->tgt, B * S2 * S2);
-  if (!rc) rc = dev_alloc(&net->mask, S2 * S2);
-  if (!rc) rc = dev_alloc(&net->rot, B);
-  if (!rc) rc = dev_alloc(&net->ip_part, B * (size_t)cnn::cmse_ip_blocks((int)(S2 * S2)));
   if (rc) {
     magpie_cnn_destroy(net);
     return rc;
@@ -252,14 +268,7 @@ int magpie_cnn_destroy(magpie_cnn* net) {
   if (!net) return MAGPIE_OK;
   hipSetDevice(net->device);
   if (net->stream) hipStreamSynchronize(net->stream);
-  dev_free(net->p);
-  dev_free(net->g);
-  dev_free(net->m);
-  dev_free(net->v);
-  dev_free(net->fwd);
-  dev_free(net->frag);
-  dev_free(net->wthin);
-  dev_free(net->wbad);
+  dev_free(net->slab);
   dev_free(net->x);
   dev_free(net->a1);
   dev_free(net->a2);
@@ -271,14 +280,8 @@ int magpie_cnn_destroy(magpie_cnn* net) {
   dev_free(net->f1);
   dev_free(net->l0);
   dev_free(net->l1);
-  dev_free(net->part);
-  dev_free(net->lpart);
-  dev_free(net->lhead);
   if (net->lres) hipHostFree(net->lres);
   dev_free(net->tgt);
-  dev_free(net->mask);
-  dev_free(net->rot);
-  dev_free(net->ip_part);
   if (net->own_stream && net->stream) hipStreamDestroy(net->stream);
   delete net;
   return MAGPIE_OK;
