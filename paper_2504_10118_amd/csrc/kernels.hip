@@ -667,12 +667,25 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const
   // Row gather: load j of thread tid reads row tid / M + j * TPB / M, column
   // tid % M: one per-lane offset, and a uniform per-load row step.
   constexpr int GR = TPB / M;   // rows per load of the workgroup
+  // reference value of the window: its centre pixel (see the spectrum term after
+  // the forward transform, which reads it again past the next barrier
+  // rather than holding it in registers through the column pass).  It has a word of its
+  // own, stored by the thread that gathers it: read from the tile behind the barrier, it
+  // could already be overwritten by the wave of its column, which starts its pass there.
+  static_assert((M / 2) % GR == 0 && (M / 2) / GR == RA / 2, "thread M / 2 gathers the centre with load RA / 2");
+  __shared__ float2 s_zc_;
+  float2* s_zc = &s_zc_;
+  if constexpr (CHAIN) s_zc = cg->zc;
   auto row_gather = [&]() {
     const int gvo = ((tid / M) * a.n_cols + (tid & (M - 1))) * (int)sizeof(float2);
     const int gso = GR * a.n_cols * (int)sizeof(float2);
     float2* const dst = T + (tid / M) * P + (tid & (M - 1));
+    float2 zz[RA];
 #pragma unroll
-    for (int j = 0; j < RA; ++j) dst[j * GR * P] = bload2p<ZPOL>(zr, gvo, j * gso);
+    for (int j = 0; j < RA; ++j) zz[j] = bload2p<ZPOL>(zr, gvo, j * gso);
+#pragma unroll
+    for (int j = 0; j < RA; ++j) dst[j * GR * P] = zz[j];
+    if (tid == M / 2) *s_zc = zz[RA / 2];
   };
   // The same with the previous minibatch's update: every wave finds its windows that
   // overlap this one, 64 records at a time (one per lane), and adds their staged updates
@@ -739,6 +752,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const
     float2* const dst = T + r0 * P + x;
 #pragma unroll
     for (int j = 0; j < RA; ++j) dst[j * GR * P] = zz[j];
+    if (tid == M / 2) *s_zc = zz[RA / 2];
   };
   if constexpr (PREV) row_gather_prev();
   else row_gather();
@@ -755,14 +769,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const
   load_cst();
   if constexpr (!LAZY) load_sd();
   __syncthreads();
-  // reference value of the window: its centre pixel (see the spectrum term after
-  // the forward transform, which reads it back from s_zc past the next barrier
-  // rather than holding it in registers through the column pass)
-  __shared__ float2 s_zc_;
-  float2* s_zc = &s_zc_;
-  if constexpr (CHAIN) s_zc = cg->zc;
-  const float2 zc = T[(M / 2) * P + M / 2];
-  if (tid == 0) *s_zc = zc;
+  const float2 zc = *s_zc;
 #pragma unroll
   for (int n1 = 0; n1 < RA; ++n1) {
     float2 qv;
