@@ -11,13 +11,19 @@
 // what Adam makes of it is this rounding, and another summation would send the bias elsewhere.
 //
 // Backward: the 32 -> 32 products run as v_mfma_f32_32x32x16_bf16 of FP32 operands split
-// exactly into three bf16 parts by truncation, x = x0 + x1 + x2 (8 + 8 + 8 significant
-// bits): the six products x0 w0, x0 w1, x1 w0, x0 w2, x1 w1, x2 w0 carry the FP32 product
-// to about 2^-23, and are accumulated in FP32 smallest first.  bf16 weights are their own
-// first part, so three products are exact.  A product of split parts is not the FP32
-// product where a value is infinite (inf - inf in its second part), so a workgroup that
-// stages a non-finite value, or whose weights hold one, takes the scalar FMA form of its
-// tile instead.
+// exactly into three bf16 parts, x = x0 + x1 + x2, each the rest rounded to nearest (|x1| <=
+// 2^-8, |x2| <= 2^-17 of x's power of two, of either sign).  Eight of the nine products are
+// formed; the ninth, x2 w2, is below 2^-34 of the product.  bf16 weights are their own first
+// part, so three products are exact.  What such an instruction adds to an accumulator is
+// rounded to nearest where the accumulator is the larger, but an accumulator smaller than the
+// products is cut off towards minus infinity at their low end (measured), so the first parts'
+// products and the others are summed apart or one behind the other, see below.  Relative error
+// against FP64 of the same operands, 32 samples of 128 x 128 (one FP32 FMA chain per output:
+// in parentheses): weight gradients 1.4e-7 to 1.8e-7 (4.3e-7 to 5.2e-7); backward-data 0.7e-7
+// to 0.95e-7 (1.7e-7 to 3.0e-7), with bf16 weights 1.0e-7 to 1.8e-7.  A product of split parts
+// is not the FP32 product where a value is infinite (inf - inf in its second part) or rounds
+// to infinity, so a workgroup that stages such a value, or whose weights hold one, takes the
+// scalar FMA form of its tile instead.
 //
 // All reductions run in a fixed order: results are bitwise reproducible.
 #include <hip/hip_runtime.h>
@@ -46,24 +52,31 @@ __device__ __forceinline__ f32x16 mfma(uint4 a, uint4 b, f32x16 c) {
                                                  0);
 }
 
-// bf16 pairs (even element in the low half) of two FP32 values' upper halves
-__device__ __forceinline__ uint32_t pack_hi(float even, float odd) {
-  return __builtin_amdgcn_perm(__float_as_uint(odd), __float_as_uint(even), 0x07060302u);
+// bf16 pairs (even element in the low half) of two FP32 values, rounded to nearest
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float even, float odd) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{even, odd}, bf16x2));
 }
-__device__ __forceinline__ float upper(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
 
-// the three bf16 parts of eight values; `probe` becomes NaN if one is not finite
+// the three bf16 parts of eight values; `probe` becomes NaN if a first part is not finite (a
+// value is not, or rounds to infinity)
 __device__ __forceinline__ void split8(const float* v, uint4 (&s)[3], float& probe) {
-  float r[8], q[8];
+  uint32_t p[3][4];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    probe = fmaf(v[j], 0.0f, probe);
-    r[j] = v[j] - upper(v[j]);
-    q[j] = r[j] - upper(r[j]);
+  for (int j = 0; j < 4; ++j) {
+    float even = v[2 * j], odd = v[2 * j + 1];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      p[q][j] = pack_bf16(even, odd);
+      const float pe = __uint_as_float(p[q][j] << 16), po = __uint_as_float(p[q][j] & 0xffff0000u);
+      if (q == 0) probe = fmaf(pe, 0.0f, fmaf(po, 0.0f, probe));
+      even -= pe;
+      odd -= po;
+    }
   }
-  s[0] = make_uint4(pack_hi(v[0], v[1]), pack_hi(v[2], v[3]), pack_hi(v[4], v[5]), pack_hi(v[6], v[7]));
-  s[1] = make_uint4(pack_hi(r[0], r[1]), pack_hi(r[2], r[3]), pack_hi(r[4], r[5]), pack_hi(r[6], r[7]));
-  s[2] = make_uint4(pack_hi(q[0], q[1]), pack_hi(q[2], q[3]), pack_hi(q[4], q[5]), pack_hi(q[6], q[7]));
+#pragma unroll
+  for (int q = 0; q < 3; ++q) s[q] = make_uint4(p[q][0], p[q][1], p[q][2], p[q][3]);
 }
 
 __device__ __forceinline__ float round_bf16(float x) {
@@ -272,27 +285,48 @@ __global__ __launch_bounds__(256, 2) void conv32_forward_kernel(const float* __r
 // products.  Products are D[co][pixel] += W[co][ci] X[ci][pixel] per tap and half of
 // the input channels; a wave owns four rows of the tile (two blocks of 2 x 16 pixels), and
 // the weights come as prepared fragments (54 KB, shared through L1 and L2).
+// FP32 weights: the seven smaller products of all 18 steps come first and the first parts'
+// product, three steps at a time, last, so that a sum takes 18 roundings at its own size
+// (relative error 1.5e-7 to 2.5e-7 -> 0.65e-7 to 0.95e-7); the weights' first parts, read twice,
+// are in LDS (18 KB, which still leaves two workgroups per CU: fragments from L2 for both
+// passes 82 us, MODE 3 78).
 // MODE 2: zero where omask <= 0.  3: sum of each 2 x 2 block (the adjoint of the
 // upsampling), zero where omask <= 0, written at half the size.
 // 512 workgroups (two per CU) walk the tiles: the next tile's halo is loaded, a piece every
 // other step, while the products run, and the masks with the last ones.  (A tile per
 // workgroup stood 9000 of its 33000 clocks at the loads, which all workgroups issued at once,
-// and 8000 at the masks, read one after another; the fragments three steps ahead spill.)
-// Bound: 2 * 9 * 32 * 32 flops per pixel at the six-product rate (23 us of MFMA issue for
-// 32 samples of 128 x 128) and the activations' traffic (42 us, 23 with MODE 3): 76 -> 68 us,
-// MODE 3 70 -> 63 us.
+// and 8000 at the masks, read one after another; the fragments three steps ahead spill, and
+// so do the first parts' sums in registers of their own.)
+// Bound: 2 * 9 * 32 * 32 flops per pixel at the eight-product rate (31 us of MFMA issue for
+// 32 samples of 128 x 128, 12 with bf16 weights) and the activations' traffic (42 us, 23 with
+// MODE 3): 75 us, MODE 3 73 (six products of truncated parts 68 and 64).
 template <int WS>
 struct Pairs;
 template <>
 struct Pairs<3> {
-  static constexpr int N = 6;
-  static constexpr int x[6] = {2, 1, 0, 1, 0, 0}, w[6] = {0, 1, 2, 0, 1, 0};
+  static constexpr int N = 8;
+  static constexpr int x[8] = {2, 1, 2, 1, 0, 1, 0, 0}, w[8] = {1, 2, 0, 1, 2, 0, 1, 0};
 };
 template <>
 struct Pairs<1> {
   static constexpr int N = 3;
   static constexpr int x[3] = {2, 1, 0}, w[3] = {0, 0, 0};
 };
+
+// The products of one K step, added to acc in two sums that start from zero, the first parts'
+// product and the others, largest first: an accumulator that is smaller than the products is cut
+// off (towards minus infinity) at the products' low end, and a larger one takes a rounding for
+// each product, so neither form fits a running sum.  The adds are held here: the sums of
+// several steps do not fit the registers.
+__device__ __forceinline__ void add_products(const uint4 (&w)[3], const uint4 (&x)[3], f32x16& acc) {
+  const f32x16 zero = {};
+  const f32x16 first = mfma(w[0], x[0], zero);
+  f32x16 t = {};
+#pragma unroll
+  for (int j = Pairs<3>::N - 2; j >= 0; --j) t = mfma(w[Pairs<3>::w[j]], x[Pairs<3>::x[j]], t);
+  acc = (acc + first) + t;
+  asm volatile("" : "+v"(acc));
+}
 
 struct Conv32Args {
   const float* in;        // [B][H][W][32]
@@ -350,12 +384,17 @@ template <int MODE, int WS>
 __global__ __launch_bounds__(256, 2) void conv32_kernel(Conv32Args a, int tx, int ty, int total) {
   using HaloT = Halo<false, CT, 4>;
   constexpr int NS = HaloT::N;
+  constexpr bool TWO = WS == 3;
+  constexpr int G0 = TWO ? 1 : 0, WG = WS - G0;   // parts of the weights that come as fragments
   __shared__ uint4 T[3][HP * 4];
+  __shared__ uint4 W0[TWO ? 18 * 64 : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
   const int wbad = *a.wbad;
   const mg::rsrc_t frs = mg::make_rsrc(a.frag, 18 * WS * 64 * sizeof(uint4));
   int fo = lane * (int)sizeof(uint4);
   auto frag = [&](int step, int s) { return __builtin_bit_cast(uint4, mg::bload4(frs, fo, (step * WS + s) * 1024)); };
+  if constexpr (TWO)
+    for (int i = tid; i < 18 * 64; i += 256) W0[i] = a.frag[(i >> 6) * 192 + (i & 63)];
 
   // staging: thread i takes 8 channels (chunk i & 3) of halo pixel i >> 2
   HaloT halo;
@@ -384,7 +423,8 @@ __global__ __launch_bounds__(256, 2) void conv32_kernel(Conv32Args a, int tx, in
     // fragments are loaded PF steps ahead of their products: they come from L2 (54 KB per
     // tile and wave, more than L1 holds); a piece of the next halo every SPREAD steps
     constexpr int PF = 2, SPREAD = 2;
-    uint4 wf[PF + 1][WS];
+    constexpr int STEPS = TWO ? 24 : 18;
+    uint4 wf[PF + 1][WG], w0[2][3];
     float probe = 0.0f;
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
@@ -401,7 +441,7 @@ __global__ __launch_bounds__(256, 2) void conv32_kernel(Conv32Args a, int tx, in
 #pragma unroll
     for (int k = 0; k < PF; ++k)
 #pragma unroll
-      for (int s = 0; s < WS; ++s) wf[k][s] = frag(k, s);
+      for (int s = 0; s < WG; ++s) wf[k][s] = frag(k, G0 + s);
     const bool bad = __syncthreads_or(!(probe == 0.0f) || wbad);
     // the last tile's own halo is loaded again, unused, rather than a branch around each load
     const typename HaloT::At next = source(min(q0 + (int)gridDim.x, total - 1));
@@ -434,37 +474,49 @@ __global__ __launch_bounds__(256, 2) void conv32_kernel(Conv32Args a, int tx, in
     // software pipeline, held by scheduling barriers: step i issues the weights of step i +
     // PF and the LDS reads of step i + 1 before its own twelve products
     uint4 x[2][2][3];
-    auto read = [&](int step, uint4 (&xs)[2][3]) {
-      const int t = step >> 1, kh = step & 1;
+    auto read = [&](int step, uint4 (&xs)[2][3], uint4 (&ws)[3]) {
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int p = p0 + (2 * k + t / 3) * HALO + t % 3;
-        const int at = 4 * p + ((2 * kh + h) ^ ((p >> 2) & 3));
+      for (int q = 0; q < 3; ++q) {
+        const int i = step < 18 ? step : 3 * (step - 18) + q, t = i >> 1, kh = i & 1;
+        if (TWO && (step >= 18 || q == 0)) ws[q] = W0[i * 64 + lane];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) xs[k][q] = T[q][at];
+        for (int k = 0; k < 2; ++k) {
+          const int p = p0 + (2 * k + t / 3) * HALO + t % 3;
+          xs[k][q] = T[step < 18 ? q : 0][4 * p + ((2 * kh + h) ^ ((p >> 2) & 3))];
+        }
       }
     };
-    read(0, x[0]);
+    read(0, x[0], w0[0]);
 #pragma unroll
-    for (int step = 0; step < 18; ++step) {
+    for (int step = 0; step < STEPS; ++step) {
       if (step + PF < 18) {
 #pragma unroll
-        for (int s = 0; s < WS; ++s) wf[(step + PF) % (PF + 1)][s] = frag(step + PF, s);
+        for (int s = 0; s < WG; ++s) wf[(step + PF) % (PF + 1)][s] = frag(step + PF, G0 + s);
       }
-      if (step + 1 < 18) read(step + 1, x[(step + 1) & 1]);
+      if (step + 1 < STEPS) read(step + 1, x[(step + 1) & 1], w0[(step + 1) & 1]);
       if (step % SPREAD == 0 && step / SPREAD < NS) load(next, step / SPREAD);
-      if (step == 18 - PF) {
+      if (step == (TWO ? 18 : 18 - PF)) {
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
           for (int q = 0; q < 4; ++q) mk[k][q] = *reinterpret_cast<const float4*>(a.omask + at[k] + 8 * q);
       }
       __builtin_amdgcn_sched_barrier(0);
+      const uint4 (&xs)[2][3] = x[step & 1];
+      if (TWO && step >= 18) {
 #pragma unroll
-      for (int j = 0; j < Pairs<WS>::N; ++j)
+        for (int q = 0; q < 3; ++q)
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-          acc[k] = mfma(wf[step % (PF + 1)][Pairs<WS>::w[j]], x[step & 1][k][Pairs<WS>::x[j]], acc[k]);
+          for (int k = 0; k < 2; ++k) acc[k] = mfma(w0[step & 1][q], xs[k][q], acc[k]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < Pairs<WS>::N - (TWO ? 1 : 0); ++j)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const int w = Pairs<WS>::w[j];
+            acc[k] = mfma(w < G0 ? w0[step & 1][0] : wf[step % (PF + 1)][w - G0], xs[k][Pairs<WS>::x[j]], acc[k]);
+          }
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();   // the tile is read; the next one may overwrite it
@@ -590,7 +642,7 @@ __global__ __launch_bounds__(256) void conv_head_kernel(const float* __restrict_
 // ---------------------------------------------------------------------------
 // Weight gradients
 // ---------------------------------------------------------------------------
-// Workgroups of four waves walk runs of 16 x 8 pixel tiles.  The tensors are staged
+// Workgroups walk runs of 16 x 8 pixel tiles.  The tensors are staged
 // transposed: channel by channel, 16 consecutive pixels of a row as split bf16 values
 // (a staging thread reads eight pixels of its channel, 32 lanes reading the 128
 // contiguous bytes of a pixel), so a row of a tile is one K = 16 step of
@@ -599,7 +651,7 @@ constexpr int GH = 8;                                  // tile rows
 constexpr int A_PITCH = GH * 32 + 16;                  // bytes per channel of a staged tile without halo
 constexpr int B_ROW = 48;                              // bytes per row of the halo tile (24 pixels, 18 used)
 constexpr int B_PITCH = (GH + 2) * B_ROW + 16;         // odd multiples of 16 bytes: no bank conflicts
-constexpr int SQ_LDS = 3 * C * (A_PITCH + B_PITCH);    // 74 KB: twice per CU
+constexpr int SQ_LDS = 3 * C * (A_PITCH + B_PITCH);    // 74 KB: one of a workgroup's two buffers
 
 struct Wgrad32Args {
   const float* in;      // [B][Hi][Wi][32]
@@ -671,13 +723,14 @@ __device__ __noinline__ void wgrad32_scalar(const Wgrad32Args& a, int t_begin, i
 // 32 x 32 channels.  A workgroup of twelve waves per CU: wave (rg, dy) takes rows 2 rg and
 // 2 rg + 1 of the tile and the three taps of row dy, their horizontal shifts formed in
 // registers from one row read (three 32 x 32 sums, 48 registers).  Tiles are staged into
-// two LDS buffers in turn, the next tile's values loaded to registers before the current
+// two LDS buffers in turn (147 KB), the next tile's values loaded to registers before the current
 // one's products and split and stored after them, so that neither memory latency nor
-// the staging's arithmetic stands between the products.  (Four waves with all nine taps
-// each, 144 registers of sums, two workgroups per CU and one buffer each: 85 us at 32 samples
-// of 128 x 128, 110 through the upsampling; the products alone 23.)  The row groups' sums
+// the staging's arithmetic stands between the products.  The row groups' sums
 // are added in order through LDS at the end of the run.
-
+// 32 samples of 128 x 128: 101 us, through the upsampling 99 (six products of truncated
+// parts added to the running sums: 90 and 84, with a relative error of 7.4e-7 and 6.2e-7 against
+// 1.8e-7 and 1.5e-7, see the top of this file; all eight in one sum per step, added once: 96 and
+// 99, 2.2e-7 and 1.9e-7).
 template <bool UP>
 __global__ __launch_bounds__(SQ_THREADS, 3) void wgrad32_kernel(Wgrad32Args a) {
   extern __shared__ uint4 smem[];
@@ -691,11 +744,12 @@ __global__ __launch_bounds__(SQ_THREADS, 3) void wgrad32_kernel(Wgrad32Args a) {
     for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
   float bsum = 0.0f, probe = 0.0f;   // this thread's share of channel tid & 31's bias gradient
   const int t_begin = blockIdx.x * a.tiles_per_wg, t_end = min(a.total_tiles, t_begin + a.tiles_per_wg);
-  const int sc = tid & 31, sg = tid >> 5;
+  int to = tid;   // the loops' own copy: index arithmetic is formed again for each tile, not held in registers
   // Staging: thread tid takes channel sc of pixel groups sg (0 .. 23) and sg + 24: groups
   // 0 .. 15 are the 8 x 2 of dout, 16 .. 45 the 10 x 3 of in (the third of 2 pixels).
   float v[2][8];
   auto load = [&](int tile) {
+    const int sc = to & 31, sg = to >> 5;
     const int b = tile / a.tiles_per_sample, tr = tile - b * a.tiles_per_sample;
     const int y0 = (tr / a.tiles_x) * GH, x0 = (tr % a.tiles_x) * 16;
     const float* inb = a.in + (size_t)b * Hi * Wi * C;
@@ -710,6 +764,7 @@ __global__ __launch_bounds__(SQ_THREADS, 3) void wgrad32_kernel(Wgrad32Args a) {
     }
   };
   auto store = [&](int buf) {
+    const int sc = to & 31, sg = to >> 5;
     unsigned char* const As = reinterpret_cast<unsigned char*>(smem) + buf * SQ_LDS;   // dout
     unsigned char* const Bs = As + 3 * C * A_PITCH;                                    // in, with halo
 #pragma unroll
@@ -733,6 +788,7 @@ __global__ __launch_bounds__(SQ_THREADS, 3) void wgrad32_kernel(Wgrad32Args a) {
   }
   __syncthreads();
   for (int tile = t_begin; tile < t_end; ++tile) {
+    asm volatile("" : "+v"(to));
     const int buf = (tile - t_begin) & 1;
     const unsigned char* const As = reinterpret_cast<const unsigned char*>(smem) + buf * SQ_LDS;
     const unsigned char* const Bs = As + 3 * C * A_PITCH;
@@ -741,22 +797,27 @@ __global__ __launch_bounds__(SQ_THREADS, 3) void wgrad32_kernel(Wgrad32Args a) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const int row = 2 * rg + k;
-      uint4 g[3], x[3][3];   // x: [dx][part]
+      uint4 g[3], d[3];
+      uint32_t d4[3];
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
         g[q] = *reinterpret_cast<const uint4*>(As + (q * C + n) * A_PITCH + row * 32 + h * 16);
         const unsigned char* src = Bs + (q * C + n) * B_PITCH + (row + dy) * B_ROW + h * 16;
-        const uint4 d = *reinterpret_cast<const uint4*>(src);
-        const uint32_t d4 = *reinterpret_cast<const uint32_t*>(src + 16);
-        x[0][q] = d;
-        x[1][q] = make_uint4(__builtin_amdgcn_alignbit(d.y, d.x, 16), __builtin_amdgcn_alignbit(d.z, d.y, 16),
-                             __builtin_amdgcn_alignbit(d.w, d.z, 16), __builtin_amdgcn_alignbit(d4, d.w, 16));
-        x[2][q] = make_uint4(d.y, d.z, d.w, d4);
+        d[q] = *reinterpret_cast<const uint4*>(src);
+        d4[q] = *reinterpret_cast<const uint32_t*>(src + 16);
       }
 #pragma unroll
-      for (int j = 0; j < 6; ++j)
+      for (int dx = 0; dx < 3; ++dx) {
+        uint4 x[3];
 #pragma unroll
-        for (int dx = 0; dx < 3; ++dx) acc[dx] = mfma(g[Pairs<3>::w[j]], x[dx][Pairs<3>::x[j]], acc[dx]);
+        for (int q = 0; q < 3; ++q) {
+          if (dx == 0) x[q] = d[q];
+          else if (dx == 2) x[q] = make_uint4(d[q].y, d[q].z, d[q].w, d4[q]);
+          else x[q] = make_uint4(__builtin_amdgcn_alignbit(d[q].y, d[q].x, 16), __builtin_amdgcn_alignbit(d[q].z, d[q].y, 16),
+                                 __builtin_amdgcn_alignbit(d[q].w, d[q].z, 16), __builtin_amdgcn_alignbit(d4[q], d[q].w, 16));
+        }
+        add_products(g, x, acc[dx]);
+      }
     }
     if (more) store(buf ^ 1);
     __syncthreads();
@@ -951,8 +1012,7 @@ __global__ __launch_bounds__(256) void wgrad_thin_kernel(WgradThinArgs a, HeadBi
 #pragma unroll
         for (int q = 0; q < 3; ++q)
           x[q] = *reinterpret_cast<const uint4*>(Ts + q * CN * 3 * COPY + toff[nb] + row * 32);
-#pragma unroll
-        for (int j = 0; j < 6; ++j) acc[nb] = mfma(g[Pairs<3>::w[j]], x[Pairs<3>::x[j]], acc[nb]);
+        add_products(g, x, acc[nb]);
       }
     }
     __syncthreads();
