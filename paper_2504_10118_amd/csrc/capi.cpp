@@ -715,19 +715,22 @@ static int prepare_merged(magpie_ctx* c, int B, bool* merged) {
   const double span_r = c->scan_r1 - c->scan_r0 + 1, span_c = c->scan_c1 - c->scan_c0 + 1;
   const double overlap = (double)B * 4.0 * c->m * c->m / (span_r * span_c);
   if (c->m <= 16 ? overlap > 6.0 : (overlap > 2.5 || B > 128)) return MAGPIE_OK;
+  // where the second buffers do not fit, two launches per minibatch run without them
+  const std::string kept = g_last_error;
+  auto without = [&]() {
+    (void)hipGetLastError();   // the launches that follow check it
+    g_last_error = kept;
+    return MAGPIE_OK;
+  };
   const size_t need = (size_t)B * c->m * c->m;
   if (need > c->stage2_cap) {
     MG_HIP(hipStreamSynchronize(c->stream));
     dev_free(c->stage2);
     c->stage2_cap = 0;
-    int rc = dev_alloc(&c->stage2, need);
-    if (rc) return rc;
+    if (dev_alloc(&c->stage2, need)) return without();
     c->stage2_cap = need;
   }
-  if (!c->z2) {
-    int rc = dev_alloc(&c->z2, (size_t)c->nr * c->nc);
-    if (rc) return rc;
-  }
+  if (!c->z2 && dev_alloc(&c->z2, (size_t)c->nr * c->nc)) return without();
   *merged = true;
   return MAGPIE_OK;
 }
