@@ -511,7 +511,7 @@ static int ensure_epoch_buffers(magpie_ctx* c, int n_epochs, int batch, size_t r
     dev_free(c->stage);
     // the probe-step partials are sized with the staging: reallocated on next use
     dev_free(c->pnum);
-      dev_free(c->pmax);
+    dev_free(c->pmax);
     dev_free(c->pacc);
     c->pcap = 0;
     rc = dev_alloc(&c->stage, need_stage);
@@ -526,7 +526,7 @@ static int ensure_epoch_buffers(magpie_ctx* c, int n_epochs, int batch, size_t r
     MG_HIP(hipStreamSynchronize(c->stream));
     drop_graph(c);
     dev_free(c->pnum);
-      dev_free(c->pmax);
+    dev_free(c->pmax);
     dev_free(c->pacc);
     rc = dev_alloc(&c->pnum, need_stage);
     if (!rc) rc = dev_alloc(&c->pmax, (size_t)B * mg::MAX_WAVES);
@@ -702,7 +702,8 @@ static int prepare_epochs(magpie_ctx* c, int n_epochs, int batch, uint64_t seed,
 // Whether this context's epochs of minibatch size B take merged launches, and their buffers.
 static int prepare_merged(magpie_ctx* c, int B, bool* merged) {
   *merged = false;
-  if (c->timing || (c->flags & (MAGPIE_UPDATE_PROBE | MAGPIE_PHASE_RECYCLE)) || B > mg::ACC_SCAN_MAX ||
+  if (c->timing || B > mg::ACC_SCAN_MAX ||
+      (c->flags & (MAGPIE_UPDATE_PROBE | MAGPIE_PHASE_RECYCLE | MAGPIE_GRAPH | MAGPIE_PERSISTENT)) ||
       !mg::merged_valid(c->m, c->rb) || B <= mg::chain_limit(c->m, c->rb, c->L))
     return MAGPIE_OK;
   // windows of the previous minibatch that overlap a window, on average: what a merged step
@@ -1416,13 +1417,20 @@ int magpie_autotune_batch(magpie_ctx* c, const int32_t* candidates, int n_candid
   rc = ensure_epoch_buffers(c, trial_epochs, bmax, 16);
   if (!rc) rc = ensure_pinned(c, 8);
   if (rc) return rc;
-  const size_t nz = (size_t)c->nr * c->nc;
-  float2* zsave = nullptr;
-  rc = dev_alloc(&zsave, nz);
-  if (rc) return rc;
-  const uint64_t ep = c->epoch_index;
   const bool timing = c->timing;
   c->timing = false;
+  for (int i = 0; i < n_candidates && !rc; ++i) {
+    bool merged;
+    rc = prepare_merged(c, std::min(candidates[i], c->n_pos), &merged);
+  }
+  const size_t nz = (size_t)c->nr * c->nc;
+  float2* zsave = nullptr;
+  if (!rc) rc = dev_alloc(&zsave, nz);
+  if (rc) {
+    c->timing = timing;
+    return rc;
+  }
+  const uint64_t ep = c->epoch_index;
   hipError_t e = hipMemcpyAsync(zsave, c->z, nz * sizeof(float2), hipMemcpyDeviceToDevice, c->stream);
   double phi0 = 0.0;
   if (e != hipSuccess) rc = fail(MAGPIE_ERR_HIP, "autotune_batch save failed");

@@ -33,3 +33,20 @@ def test_run_without_the_merged_launches_buffers(tmp_path):
     n, launches, equal = hip_calls.run(tmp_path, REFUSED)
     assert launches == [2 * n + 2, 4 * n, 4 * n]   # two chunks of one epoch
     assert equal == [True, True, True]
+
+
+AUTOTUNE = r"""
+c = Case(np.random.default_rng(1301), 240, 250, 16, 9, noise=0.05)
+g = c.gpu(3, 0.5)
+calls.start()
+g.autotune_batch([8, 16, 64, 32, 128], 1)
+print(json.dumps(calls.stop()))
+"""
+
+
+def test_batch_autotuner_allocates_before_its_trials(tmp_path):
+    """Every allocation of magpie_autotune_batch precedes its first launch, so none falls into a
+    candidate's timing."""
+    trace = hip_calls.run(tmp_path, AUTOTUNE)
+    assert "k" in trace and "m" in trace
+    assert "m" not in trace[trace.index("k"):]
