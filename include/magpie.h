@@ -266,7 +266,9 @@ int magpie_get_epoch_index(magpie_ctx* ctx, uint64_t* epoch_index);
 int magpie_set_epoch_index(magpie_ctx* ctx, uint64_t epoch_index);
 
 /*
- * Kernel timing for measurement.  While enabled, magpie_run_epochs brackets
+ * Kernel timing for measurement.  While enabled, magpie_run_epochs launches a
+ * step and an accumulation kernel for every minibatch (small minibatches, which
+ * otherwise run in one launch each or many in one, to the same results) and brackets
  * every launch of the per-position step kernel and of the accumulation
  * kernel with HIP events on the context's stream.  magpie_get_timing
  * synchronises, returns the summed event times (milliseconds), the number
@@ -307,8 +309,8 @@ int magpie_get_tuning(magpie_ctx* ctx, int* threads_per_transform, int* tile_row
  * compiled FFT plan (step kernel) and then every tile height (accumulation
  * kernel), each after one untimed epoch of the same variant, keeps the fastest
  * of each, and restores the object and the epoch counter (the trials' updates
- * are discarded).  Outputs (nullable): mean
- * per-launch times in microseconds of the chosen variants.
+ * are discarded).  The trials are timed epochs (see magpie_set_timing).  Outputs
+ * (nullable): mean per-launch times in microseconds of the chosen variants.
  * Errors: BAD_STATE, INVALID_ARG, HIP.
  */
 int magpie_autotune(magpie_ctx* ctx, int batch, int trial_epochs, double* step_us, double* accum_us);
