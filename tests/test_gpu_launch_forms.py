@@ -50,3 +50,55 @@ def test_batch_autotuner_allocates_before_its_trials(tmp_path):
     trace = hip_calls.run(tmp_path, AUTOTUNE)
     assert "k" in trace and "m" in trace
     assert "m" not in trace[trace.index("k"):]
+
+
+# m, rows, cols, step, levels, batch, epochs: on both sides of the rules' lines
+FORMS = [
+    (16, 90, 131, 9, 3, 8, 10, "chained"),
+    (16, 90, 131, 9, 3, 9, 2, "merged"),
+    (16, 240, 250, 9, 5, 256, 10, "merged"),
+    (16, 100, 110, 3, 2, 128, 1, "two"),        # 12 windows of a minibatch overlap another
+    (32, 128, 128, 12, 2, 4, 10, "chained"),
+    (32, 128, 128, 12, 2, 8, 3, "merged"),
+    (32, 128, 128, 12, 2, 16, 3, "two"),
+    (32, 128, 128, 12, 6, 1, 2, "chained"),     # V-cycle through LDS
+    (32, 128, 128, 12, 6, 2, 2, "merged"),
+    (32, 500, 490, 17, 6, 128, 2, "merged"),    # the largest minibatch of its plan
+    (32, 500, 490, 17, 3, 100, 10, "merged"),
+    (32, 403, 390, 17, 6, 128, 2, "two"),
+    (64, 180, 190, 16, 3, 1, 2, "chained"),
+    (64, 180, 190, 16, 3, 2, 2, "two"),
+]
+
+EQUAL = r"""
+out = []
+for m, rows, cols, step, levels, batch, epochs, form in arg:
+    c = Case(np.random.default_rng(1303 + m + batch), rows, cols, m, step, noise=0.05)
+    c.offs[0] = c.offs[1]                        # one position measured twice
+    c.offs[-1] = (rows - m, cols - m)            # a window in the corner
+    got = []
+    for timing in (False, True):
+        g = c.gpu(levels, 0.5)
+        g.set_timing(timing)
+        calls.start()
+        g.run_epochs(epochs, batch, seed=7)
+        trace = calls.stop()
+        got.append((g.get_object().view(np.uint32), g.step_phi(), trace.count('k'), trace.count('t')))
+        g.close()
+    (za, pa, ka, ta), (zb, pb, kb, tb) = got
+    out.append([(c.n_pos + batch - 1) // batch, ka, ta, tb, bool(np.array_equal(za, zb) and np.array_equal(pa, pb))])
+print(json.dumps(out))
+"""
+
+
+def test_launch_forms_and_their_results(tmp_path):
+    """Each case takes the form named, by its number of launches, and gives the objects and per-position
+    objectives of timed epochs (two launches per minibatch) bit for bit."""
+    for case, (n, untimed, stray, timed, equal) in zip(FORMS, hip_calls.run(tmp_path, EQUAL, FORMS)):
+        epochs, form = case[6], case[7]
+        chunks = 1 + -(-(epochs - 1) // 8)       # of 1, 8, 8, ... epochs
+        want = {"chained": chunks, "merged": n * epochs + chunks, "two": 2 * n * epochs}[form]
+        print(case, n, untimed, timed, flush=True)
+        assert timed == 2 * n * epochs and stray == 0, case
+        assert untimed == want, case
+        assert equal, case
