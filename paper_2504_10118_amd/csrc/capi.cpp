@@ -870,18 +870,23 @@ int mgrt::launch_epochs(magpie_ctx* c, int n_epochs, int B, int batches_per_epoc
     for (int e = 0; e < n_epochs; ++e) MG_HIP(hipGraphLaunch(c->gexec, c->stream));
     return MAGPIE_OK;
   }
-  // minibatches of few positions: all of them in one launch of one workgroup
+  // minibatches of few positions: many in one launch of one workgroup
   if (!c->timing && B <= mg::chain_limit(m, c->rb, c->L) && !probe_step && !sa.phase && nbatch == (N + B - 1) / B) {
     mg::ChainArgs q{};
     q.step = sa;
-    q.step.pos = buf.posrec;
     q.step.stage_wt = 0;
     q.z = c->z;
     q.w0f = c->w0f;
     q.n_pos = N;
     q.batch = B;
-    q.n_minibatches = n_epochs * nbatch;
-    MG_HIP(mg::launch_chain(m, c->rb, q, c->stream));
+    const int64_t total = (int64_t)n_epochs * nbatch;
+    for (int64_t i = 0; i < total; i += mg::CHAIN_MINIBATCHES) {
+      const int e = (int)(i / nbatch), t = (int)(i % nbatch);
+      q.step.pos = buf.posrec + (size_t)e * N + (size_t)t * B;
+      q.left = N - t * B;
+      q.n_minibatches = (int)std::min<int64_t>(mg::CHAIN_MINIBATCHES, total - i);
+      MG_HIP(mg::launch_chain(m, c->rb, q, c->stream));
+    }
     return MAGPIE_OK;
   }
   if (buf.stage2) {

@@ -84,15 +84,19 @@ struct AccumArgs {
 };
 
 // Consecutive minibatches of `batch` positions (the last of an epoch may be short) in one
-// launch of one workgroup: step.pos holds the records of whole epochs of n_pos positions,
-// n_minibatches counts over them; step's object is read and z (the same array) updated.
+// launch of one workgroup: step.pos holds the records of the rest of an epoch (left positions)
+// and then of whole epochs of n_pos positions, n_minibatches counts over them; step's object
+// is read and z (the same array) updated.
 struct ChainArgs {
   StepArgs step;
   float2* z;
   const float* w0f;
-  int n_pos, batch, n_minibatches;
+  int n_pos, batch, left, n_minibatches;
   int spare;   // set by the launch: groups without a position only help with the sums
 };
+// Minibatches of a chained launch at most (16 to 65 ms of one CU): whoever waits for the GPU in
+// between waits for no more than that.
+constexpr int CHAIN_MINIBATCHES = 4096;
 
 constexpr int ACC_TILE_W = 32;   // accumulation tile width (two rows per wave)
 // one pixel per thread: a 32 x TH tile takes 32 TH threads (TH / 2 waves)

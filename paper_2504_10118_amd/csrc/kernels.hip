@@ -1233,7 +1233,7 @@ __global__ __launch_bounds__((chain_groups_c<M, RBv>() * M * RBv)) void chain_ke
   cg.zc = &szc[group];
   cg.tid = (int)threadIdx.x - group * TPB;
   // records of a minibatch, loaded a minibatch ahead
-  int base = 0, left = q.n_pos;   // first record of the minibatch after the loaded one; positions left in its epoch
+  int base = 0, left = q.left;   // first record of the minibatch after the loaded one; positions left in its epoch
   auto fetch = [&](int buf) {
     const int n = min(q.batch, left);
     if ((int)threadIdx.x < n) srec[buf][threadIdx.x] = a.pos[base + threadIdx.x];
@@ -1413,7 +1413,8 @@ static hipError_t launch_chain_p(const ChainArgs& q, hipStream_t s) {
 
 hipError_t launch_chain(int m, int rb, const ChainArgs& q, hipStream_t s) {
   if (q.n_minibatches <= 0) return hipSuccess;
-  if (q.batch < 1 || q.batch > chain_limit(m, rb, q.step.levels)) return hipErrorInvalidValue;
+  if (q.batch < 1 || q.batch > chain_limit(m, rb, q.step.levels) || q.left < 1 || q.left > q.n_pos)
+    return hipErrorInvalidValue;
 #define MG_CH(MM, RR) if (m == MM && rb == RR) return launch_chain_p<MM, RR>(q, s);
   MG_FOR_EACH_PLAN(MG_CH)
 #undef MG_CH

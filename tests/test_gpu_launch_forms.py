@@ -102,3 +102,38 @@ def test_launch_forms_and_their_results(tmp_path):
         assert timed == 2 * n * epochs and stray == 0, case
         assert untimed == want, case
         assert equal, case
+
+
+LONG = r"""
+c = Case(np.random.default_rng(1304), 60, 66, 16, 7, noise=0.05)
+got = []
+for form in ("noalloc", "epochs", "timed"):
+    g = c.gpu(3, 0.5)
+    g.set_timing(form == "timed")
+    calls.start()
+    (g.run_epochs_noalloc if form == "noalloc" else g.run_epochs)(200, 1, seed=7)
+    trace = calls.stop()
+    got.append((g.get_object().view(np.uint32), trace.count('k')))
+    g.close()
+big = Case(np.random.default_rng(1305), 230, 236, 16, 3, noise=0.05)
+for timing in (False, True):
+    g = big.gpu(3, 0.5)
+    g.set_timing(timing)
+    calls.start()
+    g.run_epochs(1, 1, seed=7)
+    trace = calls.stop()
+    got.append((g.get_object().view(np.uint32), trace.count('k')))
+    g.close()
+same = [bool(np.array_equal(got[i][0], got[2][0])) for i in range(2)] + [bool(np.array_equal(got[3][0], got[4][0]))]
+print(json.dumps([c.n_pos, got[0][1], got[1][1], big.n_pos, got[3][1], same]))
+"""
+
+
+def test_long_chains_are_cut(tmp_path):
+    """A chained launch takes at most 4096 minibatches, in the middle of an epoch too."""
+    n, noalloc, epochs, big, one_epoch, same = hip_calls.run(tmp_path, LONG)
+    assert 200 * n > 4096 and 4096 % n and big > 4096
+    assert noalloc == 1 + -(-200 * n // 4096)        # the permutations of one chunk, then the chain
+    assert epochs == 26                              # 1 epoch, then 24 chunks of 8 and one of 7
+    assert one_epoch == -(-big // 4096)
+    assert same == [True, True, True]
