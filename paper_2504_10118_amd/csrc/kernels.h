@@ -92,7 +92,6 @@ struct ChainArgs {
   float2* z;
   const float* w0f;
   int n_pos, batch, left, n_minibatches;
-  int spare;   // set by the launch: groups without a position only help with the sums
 };
 // Minibatches of a chained launch at most (16 to 65 ms of one CU): whoever waits for the GPU in
 // between waits for no more than that.

@@ -518,8 +518,15 @@ struct ChainGroup {
   float2* zc;
   int tid, k;
   int2 off;
-  bool active;   // false: the group repeats another group's position and records nothing
 };
+// The workgroup barriers of step_body with one grid or the in-wave V-cycle, each passed once by
+// every wave.  A chained launch's groups without a position pass STEP_BARRIERS of them meanwhile,
+// so step_body has no barrier on that way that is not one of these.
+enum StepBarrier { GATHERED, COLUMNS_DONE, ROWS_DONE, STEP_BARRIERS };
+template <StepBarrier>
+__device__ __forceinline__ void step_barrier() {
+  __syncthreads();
+}
 
 // PREV: the object read is the one before the previous minibatch's update, which the gather
 // applies to its window itself (the merged launch: see merged_kernel).
@@ -768,7 +775,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const
   }
   load_cst();
   if constexpr (!LAZY) load_sd();
-  __syncthreads();
+  step_barrier<GATHERED>();
   const float2 zc = *s_zc;
 #pragma unroll
   for (int n1 = 0; n1 < RA; ++n1) {
@@ -828,7 +835,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const
     for (int i = 0; i < CST_PER; ++i)
       if (2 * (tid + i * TPB) < nCst) dst[tid + i * TPB] = cst[i];
   }
-  __syncthreads();
+  step_barrier<COLUMNS_DONE>();
 
   // ---- forward, rows (col = ky now): stage A over x = RB*n1 + g
   if constexpr (LAZY) load_sd();
@@ -922,9 +929,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const
       }
     }
     }
-    bool active = true;
-    if constexpr (CHAIN) active = cg->active;
-    if (a.phi_part && active) {
+    if (a.phi_part) {
       const double tot = wave_sum<LANES, XV>((double)phis);
       if ((tid & 63) == 0) a.phi_part[(size_t)k * MAX_WAVES + wave] = tot * (0.5 / ((double)M * (double)M));
     }
@@ -956,7 +961,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a, const int wg, const
     // v[n1] = row ky = col at x = RB*n1 + g; transpose back into T[ky][x] (own rows)
 #pragma unroll
     for (int n1 = 0; n1 < RA; ++n1) T[col * P + RB * n1 + g] = v[n1];
-    __syncthreads();
+    step_barrier<ROWS_DONE>();
 
     // ---- inverse, columns (col = x): stage B^-1 over k2, conj twiddle, exchange, stage A^-1
 #pragma unroll
@@ -1179,14 +1184,11 @@ static size_t lds_bytes_m() {
 // of the updates over the windows' pixels and the object's update, with workgroup
 // barriers in between: data stays on one CU, so nothing has to be written back between
 // minibatches.  With one grid or the in-wave V-cycle the workgroup has all its groups even
-// if the minibatch has fewer positions: the spare ones share the sums (q.spare).  A pixel is handled for the first window that covers it, and its sums run over
-// the covering windows in processing order, so the results are those of the step and
-// accumulation launches bit for bit.
+// if the minibatch has fewer positions: the spare ones share the sums.  A pixel is handled
+// for the first window that covers it, and its sums run over the covering windows in
+// processing order, so the results are those of the step and accumulation launches bit for bit.
 // ---------------------------------------------------------------------------
 constexpr int CHAIN_MAX = 16;   // groups of a workgroup
-// Workgroup barriers of step_body with one grid or the in-wave V-cycle (after the gather and
-// before each transpose's reads): what a spare group waits at meanwhile.
-constexpr int STEP_BARRIERS = 3;
 
 template <int M, int RB>
 constexpr bool chain_ok() {
@@ -1248,12 +1250,12 @@ __global__ __launch_bounds__((chain_groups_c<M, RBv>() * M * RBv)) void chain_ke
   for (int i = 0; i < q.n_minibatches; ++i) {
     const int count = next;
     const int4* rec = srec[i & 1];
-    cg.active = group < count;
-    const int4 r = rec[cg.active ? group : 0];
+    const bool active = group < count;
+    const int4 r = rec[active ? group : 0];
     cg.k = __builtin_amdgcn_readfirstlane(r.x);
     cg.off = make_int2(__builtin_amdgcn_readfirstlane(r.y), __builtin_amdgcn_readfirstlane(r.z));
     if (i + 1 < q.n_minibatches) next = fetch((i + 1) & 1);
-    if (cg.active || !q.spare) {
+    if (active) {
       step_body<M, RBv, MODE_STEP, false, true>(a, 0, &cg);
     } else {
 #pragma unroll
@@ -1399,14 +1401,14 @@ static hipError_t launch_chain_p(const ChainArgs& q, hipStream_t s) {
   if constexpr (chain_groups_c<M, RB>() < 1) {
     return hipErrorInvalidValue;
   } else {
-    ChainArgs a = q;
-    a.spare = (q.step.levels <= 1 || q.step.levels - 1 <= inwave_depth<M, RB>()) ? 1 : 0;
-    const int groups = a.spare ? chain_groups_c<M, RB>() : q.batch;
+    // the V-cycle through LDS has barriers of its own: no spare groups, single positions
+    const bool spare = q.step.levels - 1 <= inwave_depth<M, RB>();
+    const int groups = spare ? chain_groups_c<M, RB>() : 1;
     const size_t lds = q.batch * chain_tile_bytes<M, RB>() + chain_shared_bytes<M, RB>();
     const hipError_t e = hipFuncSetAttribute((const void*)chain_kernel<M, RB>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((chain_kernel<M, RB>), dim3(1), dim3(groups * M * RB), lds, s, a);
+    hipLaunchKernelGGL((chain_kernel<M, RB>), dim3(1), dim3(groups * M * RB), lds, s, q);
     return hipGetLastError();
   }
 }
